@@ -164,7 +164,8 @@ int pack_links(cola_handle_t *h, const void *U, void *dst[4], double *dev_out, h
     return COLA_OK;
 }
 
-// The clover blocks A = 1 - kappa csw sum sigma F[W] and A^-1 from the canonical field W.
+// The clover blocks A = 1 - kappa csw sum sigma F[W] and A^-1 from the field W, packed with
+// 18 reals.
 int build_clover(cola_handle_t *h, const void *W, hipStream_t st) {
     const Geom &g = h->g;
     const size_t cb = (size_t)2 * 36 * g.S;
@@ -198,7 +199,7 @@ int cola_set_gauge(cola_handle_t *h, const void *U, void *stream) {
     h->su3_dev = d;
     h->su3 = d <= 1e-12;
     if (h->csw != 0.0) {
-        const int rc = build_clover(h, U, st);
+        const int rc = build_clover(h, h->gauge[(int)LinkFmt::F64_18], st);
         if (rc != COLA_OK) {
             h->gauge_set = false;
             return rc;
@@ -220,7 +221,7 @@ int cola_set_fat_gauge(cola_handle_t *h, const void *F, void *stream) {
         return set_error(h, COLA_EINVAL, "smeared links are not SU(3) (deviation " +
                                              std::to_string(d) + ")");
     if (h->csw != 0.0) {
-        const int rc = build_clover(h, F, st);
+        const int rc = build_clover(h, h->fat[(int)LinkFmt::F64_18], st);
         if (rc != COLA_OK) {
             h->gauge_set = false;
             return rc;

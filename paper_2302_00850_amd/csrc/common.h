@@ -57,6 +57,32 @@ struct Geom {
     FastDiv div_xh, div_y, div_z;
 };
 
+// An order of the checkerboard sites of one parity in which neighbours in t stay close: a
+// tile of all x, ty x tz, walked through t, then the next tile (the extents are even, so
+// 2 x 2 always divides).  For the kernels on 18-real FP64 links, whose timeslices (576 bytes
+// a site) do not fit an XCD's L2: plain order brings every link in again for its t
+// neighbours.
+struct TileOrder {
+    int ty, tz;
+    FastDiv cols, lt, lxh, dty, nty;
+};
+
+inline TileOrder tile_order(const Geom &g) {
+    TileOrder o{};
+    for (int tz : {4, 2})
+        for (int ty : {8, 4, 2})
+            if (o.ty == 0 && g.L[1] % ty == 0 && g.L[2] % tz == 0) {
+                o.ty = ty;
+                o.tz = tz;
+            }
+    o.cols = make_fastdiv((uint32_t)(g.Lxh * o.ty * o.tz));
+    o.lt = make_fastdiv((uint32_t)g.L[3]);
+    o.lxh = make_fastdiv((uint32_t)g.Lxh);
+    o.dty = make_fastdiv((uint32_t)o.ty);
+    o.nty = make_fastdiv((uint32_t)(g.L[1] / o.ty));
+    return o;
+}
+
 enum class SpinorFmt : int { F64 = 0, F32 = 1, F16 = 2 };
 enum class LinkFmt : int { F64_18 = 0, F64_12 = 1, F32_12 = 2, F16_12 = 3 };
 

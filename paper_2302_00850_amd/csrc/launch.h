@@ -149,9 +149,9 @@ hipError_t launch_eig_scale_grad(void *x, void *y, void *g, double s, double mu,
 
 // --- clover
 // Builds A = 1 - kappa csw sum sigma F (two 6x6 chiral blocks) and A^-1 per site from
-// the canonical FP64 links; writes FP64 and FP32 packed copies.  bad counts sites
+// the packed 18-real FP64 links; writes FP64 and FP32 packed copies.  bad counts sites
 // whose blocks were not positive definite.
-hipError_t launch_clover_build(const Geom &g, const void *U, double kappa, double csw,
+hipError_t launch_clover_build(const Geom &g, const void *gauge64_18, double kappa, double csw,
                                void *a64, void *ainv64, void *a32, void *ainv32, int *bad,
                                hipStream_t st);
 
