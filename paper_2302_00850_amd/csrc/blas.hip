@@ -77,13 +77,13 @@ struct XrFn {
     void *r;
     const void *ap;
     size_t bx, bp, br, ba;
-    const double *rho, *pi, *pi2;
+    const double *rho, *pi;
     const int *active;
     int S, R;
     __device__ double operator()(const Loc &l) const {
         using TX = typename SpinorT<FX>::real;
         using TR = typename SpinorT<FR>::real;
-        const double den = pi[l.r] + (pi2 ? pi2[l.r] : 0.0);
+        const double den = pi[l.r];
         const double al = active[l.r] && den != 0.0 ? rho[l.r] / den : 0.0;
         const auto X = view<FX>(x, bx, l, S, R);
         const auto P = view<FP>(p, bp, l, S, R);
@@ -432,8 +432,7 @@ __global__ void ms_init_kernel(MsState *st, MsShifts sh, int nshift, double tol2
 //             (alpha beta^old (zeta_q^old - zeta_q) + zeta_q^old alpha^old (1 + sigma_q alpha))
 //   alpha_q = alpha zeta_q'/zeta_q, beta_q = beta (zeta_q'/zeta_q)^2; shifts done
 //   (zeta_q^2 |r|^2 <= tol^2 |b|^2) stay frozen.
-__global__ void ms_advance_kernel(MsState *st, const double *rho_new_p, const double *pi_p,
-                                  const double *pi2_p) {
+__global__ void ms_advance_kernel(MsState *st, const double *rho_new_p, const double *pi_p) {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     MsCoef &k = st->coef;
     if (st->finished || st->status != COLA_OK) {
@@ -441,7 +440,7 @@ __global__ void ms_advance_kernel(MsState *st, const double *rho_new_p, const do
         return;
     }
     const double rho = st->rho, rho_new = *rho_new_p;
-    const double pi = *pi_p + (pi2_p ? *pi2_p : 0.0);
+    const double pi = *pi_p;
     const double alpha = rho / pi, beta = rho_new / rho;
     if (!isfinite(alpha) || !isfinite(beta) || !(pi > 0.0)) {
         st->status = COLA_BREAKDOWN;
@@ -493,8 +492,8 @@ hipError_t launch_ms_init(MsState *state, const double *sigma, int nshift, doubl
 }
 
 hipError_t launch_ms_advance(MsState *state, const double *rho_new, const double *pi,
-                             const double *pi2, hipStream_t st) {
-    hipLaunchKernelGGL(ms_advance_kernel, dim3(1), dim3(64), 0, st, state, rho_new, pi, pi2);
+                             hipStream_t st) {
+    hipLaunchKernelGGL(ms_advance_kernel, dim3(1), dim3(64), 0, st, state, rho_new, pi);
     return hipGetLastError();
 }
 
@@ -519,14 +518,13 @@ hipError_t launch_scalar_copy(double *a, const double *b, int n, hipStream_t st)
 
 hipError_t launch_cg_xr(const BlasShape &b, SpinorFmt fx, SpinorFmt fp, SpinorFmt fr,
                         SpinorFmt fap, void *x, const void *p, void *r, const void *ap,
-                        const double *rho, const double *pi, const double *pi2,
-                        const int *active, const Reduce &red, hipStream_t st) {
+                        const double *rho, const double *pi, const int *active, const Reduce &red, hipStream_t st) {
     // supported combinations: all equal, or (x FP32, p FP16, r FP32, Ap FP16)
     if (fx == fp && fp == fr && fr == fap) {
         DISPATCH_FMT(fx, F,
                      XrFn<F, F, F, F> fn{x, p, r, ap, block_bytes(F, b.S, b.R), block_bytes(F, b.S, b.R),
                                          block_bytes(F, b.S, b.R), block_bytes(F, b.S, b.R),
-                                         rho, pi, pi2, active, b.S, b.R};
+                                         rho, pi, active, b.S, b.R};
                      return run(fn, b, &red, st));
     }
     if (fx == SpinorFmt::F32 && fp == SpinorFmt::F16 && fr == SpinorFmt::F32 &&
@@ -535,7 +533,7 @@ hipError_t launch_cg_xr(const BlasShape &b, SpinorFmt fx, SpinorFmt fp, SpinorFm
             x, p, r, ap,
             block_bytes(SpinorFmt::F32, b.S, b.R), block_bytes(SpinorFmt::F16, b.S, b.R),
             block_bytes(SpinorFmt::F32, b.S, b.R), block_bytes(SpinorFmt::F16, b.S, b.R),
-            rho, pi, pi2, active, b.S, b.R};
+            rho, pi, active, b.S, b.R};
         return run(fn, b, &red, st);
     }
     return hipErrorInvalidValue;

@@ -94,7 +94,7 @@ enum Epilogue : int {
     EPI_XPAY_CLOV = 4,   // out = C (x + a D in)
     // CG step fused into the last hop of the normal operator: with o = x + a D in
     // (EPI_XPAY_CG) or C x + a D in (EPI_CLOV_XPAY_CG), and per rhs
-    // alpha = active ? rho / (pi + pi2) : 0:  cg_x += alpha cg_p,  cg_r -= alpha o;
+    // alpha = active ? rho / pi : 0:  cg_x += alpha cg_p,  cg_r -= alpha o;
     // o itself is not stored and the fused norm is |cg_r|^2
     EPI_XPAY_CG = 5,
     EPI_CLOV_XPAY_CG = 6
@@ -107,6 +107,11 @@ struct Cplx64 {
 struct HopArgs {
     Geom g;
     int parity;      // output parity
+    // both: the launch computes both output parities of a full-lattice field.  The vector
+    // pointers are the fields' even blocks, the odd ones pstride bytes on; `parity` is
+    // ignored and the norms are sums over both parities.
+    int both;
+    size_t pstride;
     int dagger;      // 0: D, 1: D^H
     int nrhs;        // R
     int groups;      // R / rhs-per-thread
@@ -141,7 +146,7 @@ struct HopArgs {
     // and its per-rhs scalars
     void *cg_x, *cg_r;
     const void *cg_p;
-    const double *cg_rho, *cg_pi, *cg_pi2;
+    const double *cg_rho, *cg_pi;
     const int *cg_active;
 };
 

@@ -125,7 +125,8 @@ int get_vec(cola_handle_t *h, const std::string &tag, size_t bytes, void **out);
 Reduce reduce_into(cola_handle_t *h, int slot);
 inline double *scal_slot(cola_handle_t *h, int slot) { return h->scal + slot * kMaxRhs; }
 
-// one half-lattice hop launch with epilogue
+// one half-lattice hop launch with epilogue; both: the two half lattices of full-lattice
+// fields in one launch (parity ignored, the vectors are full fields, the norm is their sum)
 struct HopCall {
     void *out;
     const void *in;
@@ -139,11 +140,12 @@ struct HopCall {
     // EPI_XPAY_CG / EPI_CLOV_XPAY_CG: the CG vectors and per-rhs scalars
     void *cg_x = nullptr, *cg_r = nullptr;
     const void *cg_p = nullptr;
-    const double *cg_rho = nullptr, *cg_pi = nullptr, *cg_pi2 = nullptr;
+    const double *cg_rho = nullptr, *cg_pi = nullptr;
     const int *cg_active = nullptr;
     // fixed: no launch-shape tuning, no timing events, no occupancy queries (the
     // non-allocating entry point); the shape is the cached or the default one
     bool fixed = false;
+    bool both = false;
 };
 int hop(cola_handle_t *h, const HopCall &c, int prec, int nrhs, hipStream_t st);
 

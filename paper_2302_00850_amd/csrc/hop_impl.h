@@ -192,7 +192,7 @@ __device__ __forceinline__ void hop_dir(const HopArgs &a, int p, uint32_t i, con
         C u[3][3];
         if constexpr (SHL && LF == LinkFmt::F32_12)
             read_staged(staged + (2 * MU + DIR) * kStageWords, u);
-        else if (a.groups == 1)  // one lane per site: each link is read by one lane only
+        else if (a.groups == 1 && !a.both)  // one lane per site: each link is read once
             load_link<LF, T, true, kCpolNT>(a.gauge, g.S, dir == 0 ? p : 1 - p, mu,
                                             dir == 0 ? i : n, u);
         else
@@ -251,13 +251,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK ? 3
     __shared__ __attribute__((aligned(16))) uint32_t stage[SHL ? kStageSites * kStageSite : 4];
     __shared__ __attribute__((aligned(16))) float cstage[SCL ? kStageSites * kClovStage : 4];
     const Geom &g = a.g;
-    const int p = a.parity;
-    const SpinorBlock<SF, true> in(a.in, g.S, a.nrhs);
-    const SpinorBlock<SF, true> out(a.out, g.S, a.nrhs);
-    const SpinorBlock<SF, true> xin(a.x ? a.x : a.out, g.S, a.nrhs);
-    const SpinorBlock<SF, true> cgx(a.cg_x ? a.cg_x : a.out, g.S, a.nrhs);
-    const SpinorBlock<SF, true> cgr(a.cg_r ? a.cg_r : a.out, g.S, a.nrhs);
-    const SpinorBlock<SF, true> cgp(a.cg_p ? a.cg_p : a.out, g.S, a.nrhs);
     const T sg_f = a.dagger ? (T)1 : (T)-1;
     double nrm[RPT];
 #pragma unroll
@@ -268,14 +261,25 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK ? 3
     // blocks, and its blocks stride over that range only: neighbouring sites stay in
     // that XCD's L2 whether the grid covers the work once or loops over it.
     uint32_t c0, c1, cstep, cfirst;
-    xcd_range(blockIdx.x, gridDim.x, (a.total + blockDim.x - 1) / blockDim.x, &c0, &c1, &cstep);
+    // With both parities in the launch the chunks alternate between them: the two parities
+    // of a range of sites run side by side and share their links and spinors in the L2.
+    const uint32_t nch = (a.total + blockDim.x - 1) / blockDim.x;
+    xcd_range(blockIdx.x, gridDim.x, a.both ? 2 * nch : nch, &c0, &c1, &cstep);
     cfirst = c0;
     const uint32_t ncol = (uint32_t)g.s3;  // checkerboard sites of one timeslice
     // Lane w owns rhs group j of spatial column c in time chunk k and walks the chunk's
     // timeslices: the spinors its t-neighbours need were fetched one step earlier.  The
     // trip count is the same for every lane of a block (lanes past the end idle), so the
     // staging barriers are reached by all.
-    for (uint32_t ch = cfirst; ch < c1; ch += cstep) {
+    for (uint32_t pch = cfirst; pch < c1; pch += cstep) {
+    const uint32_t ch = a.both ? pch >> 1 : pch;
+    const int p = a.both ? (int)(pch & 1u) : a.parity;
+    const size_t po = a.both && p ? a.pstride : 0, no = a.both && !p ? a.pstride : 0;
+    auto view = [&](const void *base, size_t o) {
+        return SpinorBlock<SF, true>((const char *)(base ? base : a.out) + o, g.S, a.nrhs);
+    };
+    const auto in = view(a.in, no), out = view(a.out, po), xin = view(a.x, po);
+    const auto cgx = view(a.cg_x, po), cgr = view(a.cg_r, po), cgp = view(a.cg_p, po);
     // WALK: the input sites of the lane's index at t - 1, t, t + 1
     Fetched<SF, 1> rp, rc, rn;
     for (int tt = 0; tt < a.tchunk; ++tt) {
@@ -449,7 +453,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK ? 3
             }
             if constexpr (CG) {
                 // x += alpha p, r -= alpha o; o becomes the stored r (for the norm)
-                const double den = a.cg_pi[rr] + (a.cg_pi2 ? a.cg_pi2[rr] : 0.0);
+                const double den = a.cg_pi[rr];
                 const T al = (T)(a.cg_active[rr] && den != 0.0 ? a.cg_rho[rr] / den : 0.0);
                 {
                     C xv[12], pv[12];

@@ -49,7 +49,7 @@ struct MsCoef {
     int active[kRedMaxWidth];
 };
 // The shift recursion's state in device memory: a one-thread kernel advances it each
-// iteration from the base CG's rho', pi (+ pi2) and writes the coefficients the update
+// iteration from the base CG's rho', pi and writes the coefficients the update
 // kernel reads, so an iteration needs no host round trip.
 struct MsState {
     double zeta[kRedMaxWidth], zold[kRedMaxWidth], sigma[kRedMaxWidth];
@@ -65,9 +65,9 @@ struct MsState {
 // (p_q = b)
 hipError_t launch_ms_init(MsState *state, const double *sigma, int nshift, double tol2,
                           const double *bnorm, hipStream_t st);
-// one iteration of the recursion from the base rho' and pi (pi2 null: one block)
+// one iteration of the recursion from the base rho' and pi
 hipError_t launch_ms_advance(MsState *state, const double *rho_new, const double *pi,
-                             const double *pi2, hipStream_t st);
+                             hipStream_t st);
 hipError_t launch_ms_update(const BlasShape &sh, void *x, void *p, const void *r,
                             const MsCoef *k, hipStream_t st);
 // result_q = |b - ax_q - sigma_q x_q|^2 (b a one-rhs field, ax and x with R = sh.R)
@@ -78,11 +78,10 @@ hipError_t launch_scalar_add(double *a, const double *b, int n, hipStream_t st);
 // a[i] = b[i] for i < n <= 64
 hipError_t launch_scalar_copy(double *a, const double *b, int n, hipStream_t st);
 // x += alpha p, r -= alpha Ap, result = |r|^2 ;
-// alpha_q = active_q ? rho_q / (pi_q + pi2_q) : 0   (pi2 may be null)
+// alpha_q = active_q ? rho_q / pi_q : 0
 hipError_t launch_cg_xr(const BlasShape &b, SpinorFmt fx, SpinorFmt fp, SpinorFmt fr,
                         SpinorFmt fap, void *x, const void *p, void *r, const void *ap,
-                        const double *rho, const double *pi, const double *pi2,
-                        const int *active, const Reduce &red, hipStream_t st);
+                        const double *rho, const double *pi, const int *active, const Reduce &red, hipStream_t st);
 // p = r + beta p ; beta_q = active_q ? rho_new_q / rho_q : 0
 hipError_t launch_cg_p(const BlasShape &b, SpinorFmt fr, SpinorFmt fp, const void *r, void *p,
                        const double *rho_new, const double *rho, const int *active,

@@ -139,12 +139,13 @@ hipEvent_t take_event(cola_handle_t *h) {
 }
 
 // Launch shape for one hop launch: T site columns x groups lanes per block.
-void shape_for(const TuneEntry &t, int Vh, int nrhs, int *groups, int *T, int *grid, int *block) {
+void shape_for(const TuneEntry &t, int Vh, int nrhs, bool both, int *groups, int *T, int *grid,
+               int *block) {
     *groups = nrhs / t.rpt;
     *T = t.sites_per_block;
     *block = *T * *groups;
     const long cols = Vh / t.tchunk;
-    long g = (cols + *T - 1) / *T;
+    long g = (cols + *T - 1) / *T * (both ? 2 : 1);
     if (t.grid > 0 && t.grid < g) g = t.grid;  // t.grid < 0: resident cap applied later
     if (g > kMaxGrid) g = kMaxGrid;
     *grid = (int)std::max(1L, g);
@@ -320,10 +321,12 @@ int fill_and_launch(cola_handle_t *h, const HopCall &c, int prec, int nrhs, cons
     memset(&a, 0, sizeof a);
     a.g = h->g;
     a.parity = c.parity;
+    a.both = c.both ? 1 : 0;
+    a.pstride = c.both ? spinor_block_bytes(h->g, spinor_fmt(prec), nrhs) : 0;
     a.dagger = c.dagger;
     a.nrhs = nrhs;
     int groups, T, grid, block;
-    shape_for(te, h->g.Vh, nrhs, &groups, &T, &grid, &block);
+    shape_for(te, h->g.Vh, nrhs, c.both, &groups, &T, &grid, &block);
     a.groups = groups;
     a.div_groups = make_fastdiv((uint32_t)groups);
     a.epi = c.epi;
@@ -338,7 +341,6 @@ int fill_and_launch(cola_handle_t *h, const HopCall &c, int prec, int nrhs, cons
     a.cg_p = c.cg_p;
     a.cg_rho = c.cg_rho;
     a.cg_pi = c.cg_pi;
-    a.cg_pi2 = c.cg_pi2;
     a.cg_active = c.cg_active;
     a.gauge = h->gauge[(int)link_fmt(prec)];
     a.gauge_fat = h->flic ? h->fat[(int)link_fmt(prec)] : nullptr;
@@ -537,7 +539,8 @@ int hop(cola_handle_t *h, const HopCall &c, int prec, int nrhs, hipStream_t st) 
     const int key_epi = c.epi == EPI_XPAY_CG ? EPI_XPAY
                         : c.epi == EPI_CLOV_XPAY_CG ? EPI_CLOV_XPAY
                                                     : c.epi;
-    const std::string key = tune_key(h, prec, nrhs, key_epi, c.norm_result != nullptr);
+    const std::string key =
+        tune_key(h, prec, nrhs, key_epi, c.norm_result != nullptr) + (c.both ? ":b" : "");
     TuneEntry te;
     auto it = h->tune.find(key);
     if (it != h->tune.end() && (h->tune_mode != 2 || cg || c.fixed)) {
@@ -580,6 +583,7 @@ int hop(cola_handle_t *h, const HopCall &c, int prec, int nrhs, hipStream_t st) 
     if (timed) {
         double b, f;
         hop_work(h, prec, nrhs, c.epi, &b, &f);
+        if (c.both) b *= 2, f *= 2;
         h->pending.push_back({e0, e1});
         h->pending_bytes.push_back(b);
         h->pending_flops.push_back(f);
@@ -633,7 +637,6 @@ int apply_op(cola_handle_t *h, void *out, const void *in, int op, int parity, in
     const void *A = f64 ? h->clov64 : h->clov32;
     const void *Ainv = f64 ? h->clovinv64 : h->clovinv32;
     const double k = h->kappa;
-    auto blk = [bb](const void *base, int p) { return (void *)((const char *)base + p * bb); };
 
     switch (op) {
         case COLA_OP_HOP:
@@ -645,18 +648,16 @@ int apply_op(cola_handle_t *h, void *out, const void *in, int op, int parity, in
         }
         case COLA_OP_M:
         case COLA_OP_MDAG: {
-            // out_p = A_pp in_p - kappa D_{p,1-p} in_{1-p}
-            const int dag = op == COLA_OP_MDAG;
-            for (int p = 0; p < 2; ++p) {
-                HopCall c{blk(out, p), blk(in, 1 - p), p, dag};
-                c.epi = clover ? EPI_CLOV_XPAY : EPI_XPAY;
-                c.x = blk(in, p);
-                c.a = -k;
-                c.clov = A;
-                c.fixed = fixed;
-                COLA_TRY(hop(h, c, prec, nrhs, st));
-            }
-            return COLA_OK;
+            // out_p = A_pp in_p - kappa D_{p,1-p} in_{1-p}, both parities in one launch
+            HopCall c{out, in, 0, op == COLA_OP_MDAG ? 1 : 0};
+            c.both = true;
+            c.epi = clover ? EPI_CLOV_XPAY : EPI_XPAY;
+            c.x = in;
+            c.a = -k;
+            c.clov = A;
+            c.norm_result = norm_result;
+            c.fixed = fixed;
+            return hop(h, c, prec, nrhs, st);
         }
         case COLA_OP_MDAGM: {
             void *t = ws;

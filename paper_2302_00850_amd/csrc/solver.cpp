@@ -37,12 +37,10 @@ enum Slot {
     RHO = 0,
     RHO_NEW = 1,
     PI = 2,
-    PI2 = 3,
-    BNORM = 4,
-    SCALE = 5,
-    TRUE_RES = 6,
-    TMP = 7,
-    RHO_EVEN = 8  // |r|^2 of the even block (full-lattice fused CG step)
+    BNORM = 3,
+    SCALE = 4,
+    TRUE_RES = 5,
+    TMP = 6
 };
 
 struct Ctx {
@@ -73,74 +71,47 @@ int vec(const Ctx &c, const char *tag, SpinorFmt f, void **out) {
     return get_vec(c.h, t, c.bytes(f), out);
 }
 
-// out = A in, |first factor output|^2 -> PI (+PI2 on the full lattice)
+// out = A in, |first factor output|^2 -> PI
 int normal(const Ctx &c, int prec, void *out, const void *in) {
     if (!c.full)
         return apply_op(c.h, out, in, COLA_OP_SCHUR_DAGSCHUR, 0, prec, c.R, c.st, c.slot(PI));
     cola_handle_t *h = c.h;
     const SpinorFmt sf = spinor_fmt(prec);
-    const size_t bb = spinor_block_bytes(h->g, sf, c.R);
     void *t;
     COLA_TRY(get_vec(h, "cg_full_t_" + std::to_string((int)sf) + "_" + std::to_string(c.R),
-                     2 * bb, &t));
-    const bool clover = h->csw != 0.0;
-    const void *A = sf == SpinorFmt::F64 ? h->clov64 : h->clov32;
-    for (int p = 0; p < 2; ++p) {
-        HopCall hc{(char *)t + p * bb, (const char *)in + (1 - p) * bb, p, 0};
-        hc.epi = clover ? EPI_CLOV_XPAY : EPI_XPAY;
-        hc.x = (const char *)in + p * bb;
-        hc.a = -h->kappa;
-        hc.clov = A;
-        hc.norm_result = c.slot(p == 0 ? PI : PI2);
-        COLA_TRY(hop(h, hc, prec, c.R, c.st));
-    }
+                     c.bytes(sf), &t));
+    COLA_TRY(apply_op(h, t, in, COLA_OP_M, -1, prec, c.R, c.st, c.slot(PI)));
     return apply_op(h, out, t, COLA_OP_MDAG, -1, prec, c.R, c.st);
 }
 
 // One CG step: Ap = A p, pi = <p, Ap>, then x += alpha p, r -= alpha Ap and
 // rho_new = |r|^2.  With x, r and p in the operator's storage the update runs inside the
-// last hops (Ap is never stored): the last hop of S^dag S on the even-odd system, the two
-// parity hops of M^dag on the full lattice; COLA_CG_FUSE=0 selects the separate update
+// last hop (Ap is never stored): the last hop of S^dag S on the even-odd system, the hop of
+// M^dag on the full lattice; COLA_CG_FUSE=0 selects the separate update
 // kernel.
 int full_normal_cg_step(const Ctx &c, int prec, void *x, void *r, void *pv) {
     cola_handle_t *h = c.h;
     const SpinorFmt sf = spinor_fmt(prec);
-    const size_t bb = spinor_block_bytes(h->g, sf, c.R);
     void *t;
     COLA_TRY(get_vec(h, "cg_full_t_" + std::to_string((int)sf) + "_" + std::to_string(c.R),
-                     2 * bb, &t));
+                     c.bytes(sf), &t));
     const bool clover = h->csw != 0.0;
-    const void *A = sf == SpinorFmt::F64 ? h->clov64 : h->clov32;
-    auto blk = [bb](const void *base, int q) { return (char *)base + q * bb; };
-    // t = M p, |t_e|^2 -> PI, |t_o|^2 -> PI2
-    for (int q = 0; q < 2; ++q) {
-        HopCall hc{blk(t, q), blk(pv, 1 - q), q, 0};
-        hc.epi = clover ? EPI_CLOV_XPAY : EPI_XPAY;
-        hc.x = blk(pv, q);
-        hc.a = -h->kappa;
-        hc.clov = A;
-        hc.norm_result = c.slot(q == 0 ? PI : PI2);
-        COLA_TRY(hop(h, hc, prec, c.R, c.st));
-    }
-    // per parity: the M^dag hop with the update of x and r; |r_e|^2 + |r_o|^2 -> RHO_NEW
-    for (int q = 0; q < 2; ++q) {
-        HopCall hc{blk(r, q), blk(t, 1 - q), q, 1};
-        hc.epi = clover ? EPI_CLOV_XPAY_CG : EPI_XPAY_CG;
-        hc.x = blk(t, q);
-        hc.a = -h->kappa;
-        hc.clov = A;
-        hc.norm_result = c.slot(q == 0 ? RHO_EVEN : RHO_NEW);
-        hc.cg_x = blk(x, q);
-        hc.cg_r = blk(r, q);
-        hc.cg_p = blk(pv, q);
-        hc.cg_rho = c.slot(RHO);
-        hc.cg_pi = c.slot(PI);
-        hc.cg_pi2 = c.slot(PI2);
-        hc.cg_active = h->active;
-        COLA_TRY(hop(h, hc, prec, c.R, c.st));
-    }
-    COLA_HIP(h, launch_scalar_add(c.slot(RHO_NEW), c.slot(RHO_EVEN), c.R, c.st));
-    return COLA_OK;
+    COLA_TRY(apply_op(h, t, pv, COLA_OP_M, -1, prec, c.R, c.st, c.slot(PI)));
+    // M^dag t with the update of x and r, both parities in one launch
+    HopCall hc{r, t, 0, 1};
+    hc.both = true;
+    hc.epi = clover ? EPI_CLOV_XPAY_CG : EPI_XPAY_CG;
+    hc.x = t;
+    hc.a = -h->kappa;
+    hc.clov = sf == SpinorFmt::F64 ? h->clov64 : h->clov32;
+    hc.norm_result = c.slot(RHO_NEW);
+    hc.cg_x = x;
+    hc.cg_r = r;
+    hc.cg_p = pv;
+    hc.cg_rho = c.slot(RHO);
+    hc.cg_pi = c.slot(PI);
+    hc.cg_active = h->active;
+    return hop(h, hc, prec, c.R, c.st);
 }
 
 int cg_step(const Ctx &c, int prec, SpinorFmt fx, void *x, void *r, void *pv, void *ap) {
@@ -154,13 +125,7 @@ int cg_step(const Ctx &c, int prec, SpinorFmt fx, void *x, void *r, void *pv, vo
                                     h->active, c.slot(RHO_NEW));
     COLA_TRY(normal(c, prec, ap, pv));
     COLA_HIP(h, launch_cg_xr(c.shape(), fx, fp, fx, fp, x, pv, r, ap, c.slot(RHO), c.slot(PI),
-                             c.full ? c.slot(PI2) : nullptr, h->active,
-                             reduce_into(h, RHO_NEW), c.st));
-    return COLA_OK;
-}
-
-int zero_pi2(const Ctx &c) {
-    COLA_HIP(c.h, hipMemsetAsync(c.slot(PI2), 0, sizeof(double) * kMaxRhs, c.st));
+                             h->active, reduce_into(h, RHO_NEW), c.st));
     return COLA_OK;
 }
 
@@ -361,7 +326,6 @@ int solve_reliable(const Ctx &c, int sloppy_prec, const cola_cg_params_t &p, voi
     if (!same) COLA_HIP(h, launch_convert(sh, fs, SpinorFmt::F64, rs, r64, nullptr, 0, &red_rho, c.st));
     else COLA_HIP(h, hipMemcpyAsync(c.slot(RHO), c.slot(TRUE_RES), sizeof(double) * c.R, hipMemcpyDeviceToDevice, c.st));
     COLA_HIP(h, launch_convert(sh, fs, fs, ps, rs, nullptr, 0, nullptr, c.st));
-    if (!c.full) COLA_TRY(zero_pi2(c));
     const Reduce red_new = reduce_into(h, RHO_NEW);
     int last_rel = 0;
     int it = 0;
@@ -639,8 +603,7 @@ int solve_defect(const Ctx &c, int inner_prec, const cola_cg_params_t &p, void *
                                    c.st));
         COLA_HIP(h, launch_convert(sh, fp, fxr, pv, rs, nullptr, 0, nullptr, c.st));
         COLA_HIP(h, hipMemsetAsync(xs, 0, c.bytes(fxr), c.st));
-        if (!c.full) COLA_TRY(zero_pi2(c));
-        int its = 0, st = COLA_OK;
+            int its = 0, st = COLA_OK;
         if (p.block)
             COLA_TRY(inner_block_cg(c, prec, x32, r32, itol2, p.max_iter - o->iterations, act,
                                     check, &its, &st));
@@ -868,7 +831,6 @@ int cg_multishift_impl(cola_handle_t *h, void *x, const void *b, int nshift, con
     COLA_TRY(read_slot(c, BNORM, &bnorm));
     COLA_HIP(h, hipMemcpyAsync(c.slot(RHO), c.slot(BNORM), sizeof(double),
                                hipMemcpyDeviceToDevice, st));
-    if (full) COLA_TRY(zero_pi2(c));
     COLA_TRY(write_active(c, std::vector<int>{1}));
     const double thr = p->tol * p->tol * bnorm;
     const int check = p->check_interval > 0 ? p->check_interval : default_check(c, 8);
@@ -887,10 +849,8 @@ int cg_multishift_impl(cola_handle_t *h, void *x, const void *b, int nshift, con
         COLA_TRY(normal(c, COLA_FP64, ap, p64));
         COLA_HIP(h, launch_cg_xr(sh1, SpinorFmt::F64, SpinorFmt::F64, SpinorFmt::F64,
                                  SpinorFmt::F64, xb, p64, r64, ap, c.slot(RHO), c.slot(PI),
-                                 full ? c.slot(PI2) : nullptr, h->active,
-                                 reduce_into(h, RHO_NEW), st));
-        COLA_HIP(h, launch_ms_advance(state, c.slot(RHO_NEW), c.slot(PI),
-                                      full ? c.slot(PI2) : nullptr, st));
+                                 h->active, reduce_into(h, RHO_NEW), st));
+        COLA_HIP(h, launch_ms_advance(state, c.slot(RHO_NEW), c.slot(PI), st));
         COLA_HIP(h, launch_ms_update(shn, xs, ps, r64, &state->coef, st));
         COLA_HIP(h, launch_cg_p(sh1, SpinorFmt::F64, SpinorFmt::F64, r64, p64, c.slot(RHO_NEW),
                                 c.slot(RHO), h->active, st));
