@@ -151,16 +151,6 @@ void shape_for(const TuneEntry &t, int Vh, int nrhs, bool both, int *groups, int
     *grid = (int)std::max(1L, g);
 }
 
-// Longest power-of-two time chunk (<= 16, dividing Lt) that still leaves about
-// 2^18 lanes of work, so a lattice fills the 256 CUs.
-int default_tchunk(const Geom &g, int groups) {
-    int tc = 1;
-    while (tc * 2 <= 16 && g.L[3] % (tc * 2) == 0 &&
-           (double)g.Vh * groups / (tc * 2) >= 262144.0)
-        tc *= 2;
-    return tc;
-}
-
 // A spatial tile must divide the y and z extents (tile_y = 0: no tiling).
 bool tile_ok(const Geom &g, int ty, int tz) {
     if (ty == 0 && tz == 0) return true;
@@ -241,7 +231,26 @@ int write_table(const std::string &path, const std::map<std::string, TuneEntry> 
     return rename(tmp.c_str(), path.c_str()) == 0 ? (int)t.size() : -1;
 }
 
-TuneEntry default_entry(const Geom &g, int prec, int nrhs) {
+// The largest spatial tile (ty x tz columns of all x, dividing the lattice, tz >= 2) whose
+// timeslice holds at most `most` checkerboard sites; the squarer one of equals.  0 x 0 when
+// there is none.
+void best_tile(const Geom &g, int most, int *ty, int *tz) {
+    *ty = *tz = 0;
+    for (int y = 2; y <= g.L[1]; ++y)
+        for (int z = 2; z <= g.L[2]; ++z) {
+            if (g.L[1] % y || g.L[2] % z || g.Lxh * y * z > most) continue;
+            const int now = y * z, had = *ty * *tz;
+            if (now > had || (now == had && abs(y - z) < abs(*ty - *tz))) {
+                *ty = y;
+                *tz = z;
+            }
+        }
+}
+
+// Launch shapes.  Tiles are walked through t, so that the timeslices in flight of a tile and
+// their links stay in one XCD's L2; the tile sizes below are where the times measured over
+// all divisors of 24^3 x 48, 32^3 x 64 and 48^3 x 96 are flat or lowest.
+TuneEntry default_entry(const Geom &g, int prec, int nrhs, bool both) {
     TuneEntry t;
     t.rpt = 1;
     const int G = nrhs;
@@ -249,53 +258,55 @@ TuneEntry default_entry(const Geom &g, int prec, int nrhs) {
     while (T * 2 * G <= 256) T *= 2;
     t.sites_per_block = T;
     t.grid = 0;
-    t.tchunk = default_tchunk(g, G);
-    // Spatial tiles ((y, z) columns walked through t).  Multi-rhs hops: the largest of
-    // 8x8, 8x4 and 4x4 whose timeslice holds at most 1024 sites (Lx/2 ty tz), so that a
-    // few timeslices of a tile stay in one XCD's L2 while it walks t.  Measured: 8x8 on
-    // 32^3 x 64 gave the fastest 12-rhs FP16 solve (8x4 and 4x8 0.4-1.6% slower, 4x4 4%);
-    // on 48^3 x 96, 8x4 and 4x4 ran the 12-rhs FP32 clover solve 9-10% faster than 16x8.
-    // Lattices no candidate divides keep the time-chunk order.
-    int ty = 0, tz = 0;
-    const bool f64 = prec == COLA_FP64 || prec == COLA_FP64_12;
-    if (nrhs >= 4) {
-        const int cand[3][2] = {{8, 8}, {8, 4}, {4, 4}};
-        for (const auto &c : cand) {
-            if (g.Lxh * c[0] * c[1] <= 1024 && tile_ok(g, c[0], c[1])) {
-                ty = c[0];
-                tz = c[1];
-                break;
-            }
-        }
+    if (nrhs == 1) {
+        // 8192 sites, or 4096 where both parities run side by side.  M^dag M (both): FP64
+        // 48^3 x 96 7.12 ms with 16x16 tiles of 64-site blocks, 5.06 with 24x6 (256); 32^3 x
+        // 64 1.14 and 1.04 ms with 16x16 (256); 24^3 x 48 410 us untiled, 353 with 24x12;
+        // FP32 48^3 x 96 3.05 ms untiled, 2.36; FP16 1.60 ms with 16x8, 1.35.  S^dag S (one
+        // parity): FP64 48^3 x 96 7.30 -> 6.81 ms, 32^3 x 64 1.27 -> 1.23; FP32 2.94 -> 2.78
+        // ms and 528 -> 515 us.  Blocks of 256 sites where that leaves each CU several of
+        // them, else 64.
+        best_tile(g, both ? 4096 : 8192, &t.tile_y, &t.tile_z);
+        t.sites_per_block = (double)g.Vh * (both ? 2 : 1) >= 524288.0 ? 256 : 64;
+        return t;
     }
-    // single-rhs hops: the tuner's picks on 32^3 x 64 (16x16 tiles of 64-site blocks for
-    // FP64, 16x8 tiles for FP16, plain order in 128-site blocks for FP32)
-    if (nrhs == 1 && f64) ty = 16, tz = 16, t.sites_per_block = 64;
-    if (nrhs == 1 && prec == COLA_FP16) ty = 16, tz = 8;
-    if (nrhs == 1 && prec == COLA_FP32) t.tchunk = 1, t.sites_per_block = 128;
-    if (ty > 0 && tile_ok(g, ty, tz)) {
-        t.tile_y = ty;
-        t.tile_z = tz;
-        t.tchunk = 1;
+    if (prec == COLA_FP64 || prec == COLA_FP64_12) {
+        // FP64 (2304 bytes a site with 12 rhs).  12 rhs, S^dag S: 24^3 x 48 2.76 ms with
+        // 12x6, 2.82 with 8x8; 32^3 x 64 9.2 ms with 8x4 and 8x8; clover S 48^3 x 96 29.4
+        // ms with 8x4, 28.7 with 6x6; with 2 to 8 rhs 12x6 or 12x12 are the fastest on 24^3
+        // x 48.  M^dag M (both): 24^3 x 48 2.86 ms with 8x8, 2.73 with 6x4; 32^3 x 64 9.74
+        // ms with 8x8, 8.95 with 4x4; up to 8 rhs 12x6 as for one parity.
+        best_tile(g, both && nrhs > 8 ? 288 : 900, &t.tile_y, &t.tile_z);
+        return t;
     }
-    t.stage = nrhs >= 8 && stage_ok(g, prec, nrhs, t) ? 1 : 0;
-    // FP32 and FP16 with staged links walk time with the neighbours of the lane's index
-    // in registers: tiles walked in chunks of up to 8 timeslices.  Measured on the
-    // 48^3 x 96 12-rhs FP32 clover hop: 8x8 and 16x4 tiles in 8-slice chunks ran 12%
-    // faster than the best shape without the walk, 4x4 and 8x4 tiles 5-6%; on 32^3 x 64
-    // FP16 the plain hop 7% faster.
-    if ((prec == COLA_FP32 || prec == COLA_FP16) && t.stage && t.rpt == 1) {
-        const int wt[4][2] = {{8, 8}, {16, 4}, {8, 4}, {4, 4}};
-        for (const auto &c : wt) {
-            if (!tile_ok(g, c[0], c[1])) continue;
-            int tc = 8;
-            while (g.L[3] % tc) tc /= 2;
-            t.tile_y = c[0];
-            t.tile_z = c[1];
-            t.tchunk = tc;
-            break;
-        }
+    // FP32 and FP16: the site's links staged in LDS from four rhs on.  M, 20 x 18 x 14 x 30
+    // clover FP32: 5 rhs 114 us unstaged, 87 staged; 4 rhs 83 and 72; 3 rhs 63 unstaged, 68
+    // staged.  24^3 x 48: 6 rhs 493 and 403 us, 4 rhs 322 and 316.
+    t.stage = nrhs >= 4 && stage_ok(g, prec, nrhs, t) ? 1 : 0;
+    if (t.stage) {
+        // With staged links the lanes can walk time with the neighbours of their index in
+        // registers: chunks of 8 timeslices where at least 12 rounds of resident blocks
+        // remain, of 4 where 4 rounds do, else no walk.  S^dag S with 12 rhs: FP32 24^3 x 48
+        // 1.29 ms with 8x8 in chunks of 8, 1.19 with 12x12 in 4; 32^3 x 64 3.99 and 3.78
+        // with 16x8 in 4; clover S 48^3 x 96 11.24 and 11.09 with 12x6 in 8; FP16 24^3 x 48
+        // 790 and 712 us.  5 to 8 rhs on 24^3 x 48 (2 to 3 rounds): 0 to 7% faster without
+        // the walk.  Both parities (M^dag M): FP32 24^3 x 48 1.21 ms with 12x6.
+        best_tile(g, both ? 1024 : 2048, &t.tile_y, &t.tile_z);
+        const double blocks = (double)g.Vh * (both ? 2 : 1) / T;
+        t.tchunk = blocks / 8 >= 12 * 1024.0 ? 8 : blocks / 4 >= 4 * 1024.0 ? 4 : 1;
+        while (g.L[3] % t.tchunk) t.tchunk /= 2;
+        return t;
     }
+    // two and three rhs per site (M, 24^3 x 48 FP16: 92 us untiled in 256-lane blocks, 78
+    // with 12x12 tiles of 64-site blocks)
+    if (T > 64) t.sites_per_block = 64;
+    best_tile(g, 2048, &t.tile_y, &t.tile_z);
+    return t;
+}
+
+// The default shape, or the one COLA_HOP_SHAPE pins.
+TuneEntry untuned_entry(const Geom &g, int prec, int nrhs, bool both) {
+    TuneEntry t = default_entry(g, prec, nrhs, both);
     // Measurement knob: COLA_HOP_SHAPE="rpt,sites_per_block,grid,tchunk" pins the
     // untuned launch shape (ignored unless every field is valid for this launch).
     if (const char *env = getenv("COLA_HOP_SHAPE")) {
@@ -555,7 +566,7 @@ int hop(cola_handle_t *h, const HopCall &c, int prec, int nrhs, hipStream_t st) 
         const std::string path = tune_cache_path();
         if (!path.empty()) write_table(path, ts.table);
     } else if (!stored_entry(h, key, prec, nrhs, !c.fixed, &te)) {
-        te = default_entry(h->g, prec, nrhs);
+        te = untuned_entry(h->g, prec, nrhs, c.both);
     }
     // a resident grid needs an occupancy query (cached in a host map): the fixed mode
     // takes the plain grid instead, which gives bitwise the same output
