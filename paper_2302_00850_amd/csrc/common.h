@@ -139,6 +139,8 @@ struct HopArgs {
     // the site's links staged in LDS by its first eight lanes (groups >= 8, one rhs per
     // lane, sites_per_block <= 32, 12-real FP16 / FP32 links)
     int stage_links;
+    // a wavefront per direction (hop_dirs.h): blocks of sites_per_block sites, groups = nrhs
+    int by_dirs;
     // host only: when set, the launcher stores the kernel's resident blocks per CU here
     // instead of launching
     int *occupancy;
@@ -165,6 +167,9 @@ constexpr int kRedCounters = kRedGroups + 1;
 
 // Sites of one block when the hop stages each site's links in LDS.
 constexpr int kStageSites = 32;
+
+// Lanes (site, rhs) of one block of the hop with a wavefront per direction.
+constexpr int kDirsSites = 64;
 
 // Link chunk counts per format.
 constexpr int link_chunks(LinkFmt f) {

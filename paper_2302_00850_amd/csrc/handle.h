@@ -28,7 +28,8 @@ struct TuneEntry {
     int tchunk = 1;  // timeslices walked by one lane
     int tile_y = 0;  // spatial tile (all x-rows x tile_y x tile_z); 0 = lexicographic
     int tile_z = 0;
-    int stage = 0;   // links staged in LDS by the lanes of a site (see stage_ok)
+    int stage = 0;   // 1: links staged in LDS by the lanes of a site (see stage_ok); 2: a
+                     // wavefront per direction (see dirs_ok)
     double ms = 0;
 };
 

@@ -167,8 +167,17 @@ bool stage_ok(const Geom &g, int prec, int nrhs, const TuneEntry &t) {
            bytes < 2147483648.0;
 }
 
+// The hop with a wavefront per direction (stage = 2): FP64 and FP32, one rhs per lane, whole
+// sites of at most kDirsSites lanes per block, one block per sites_per_block sites.
+bool dirs_ok(const Geom &g, int prec, int nrhs, const TuneEntry &e) {
+    return prec != COLA_FP16 && e.rpt == 1 && e.grid == 0 && e.tchunk == 1 && e.tile_y == 0 &&
+           e.tile_z == 0 && e.sites_per_block >= 1 && e.sites_per_block * nrhs <= kDirsSites &&
+           2.0 * ((double)g.Vh / e.sites_per_block + 1) <= kMaxGrid;
+}
+
 // A launch shape the hop kernels accept for this lattice, precision and rhs count.
 bool shape_valid(const Geom &g, int prec, int nrhs, const TuneEntry &e) {
+    if (e.stage == 2) return dirs_ok(g, prec, nrhs, e);
     const bool f64 = prec == COLA_FP64 || prec == COLA_FP64_12;
     return (e.rpt >= 1 && e.rpt <= 4) && nrhs % e.rpt == 0 && (e.rpt == 1 || !f64) &&
            e.sites_per_block >= 1 && (e.sites_per_block & (e.sites_per_block - 1)) == 0 &&
@@ -250,7 +259,7 @@ void best_tile(const Geom &g, int most, int *ty, int *tz) {
 // Launch shapes.  Tiles are walked through t, so that the timeslices in flight of a tile and
 // their links stay in one XCD's L2; the tile sizes below are where the times measured over
 // all divisors of 24^3 x 48, 32^3 x 64 and 48^3 x 96 are flat or lowest.
-TuneEntry default_entry(const Geom &g, int prec, int nrhs, bool both) {
+TuneEntry plain_entry(const Geom &g, int prec, int nrhs, bool both) {
     TuneEntry t;
     t.rpt = 1;
     const int G = nrhs;
@@ -304,9 +313,35 @@ TuneEntry default_entry(const Geom &g, int prec, int nrhs, bool both) {
     return t;
 }
 
+// Launches of few lanes (sites of one parity x rhs) take the hop with a wavefront per
+// direction, up to where it was measured no slower (us, this against plain_entry's shape; m:
+// both parities, s: D_eo D_oe):
+//   one rhs FP32  16^3 x 32 s 16.6 / 28.8, 24^3 x 48 s 72 / 95, m 69 / 73, 28^3 x 48 s 125 / 161,
+//                 32^3 x 64 s 302 / 266; with clover 28^3 x 48 s 183 / 220, 20^3 x 32 m 42 / 41,
+//                 24^3 x 32 m 70 / 66
+//   one rhs FP64  16^3 x 32 s 37 / 43, m 28 / 40, 24^3 x 32 s 126 / 140, 24^3 x 48 s 224 / 208,
+//                 28^3 x 48 m 280 / 294; with clover 20^3 x 32 s 99 / 104, 24^3 x 32 s 182 / 179
+//   several rhs   12^3 x 16 FP32 5 rhs s 17 / 23, 12 rhs m 36 / 30; FP64 8 rhs s 39 / 42,
+//                 12 rhs with clover s 79 / 77
+bool few_lanes(const Geom &g, int prec, int nrhs, bool both, bool clover) {
+    const bool f32 = prec == COLA_FP32;
+    const double lanes = (double)g.Vh * nrhs;
+    if (nrhs > 1) return lanes <= (f32 ? 65536 : 131072);
+    if (clover && (both || !f32)) return lanes <= 131072;
+    return lanes <= (f32 || both ? 600000 : 262144);
+}
+
+TuneEntry default_entry(const Geom &g, int prec, int nrhs, bool both, bool clover) {
+    TuneEntry t;
+    t.stage = 2;
+    t.sites_per_block = kDirsSites / nrhs;
+    if (few_lanes(g, prec, nrhs, both, clover) && dirs_ok(g, prec, nrhs, t)) return t;
+    return plain_entry(g, prec, nrhs, both);
+}
+
 // The default shape, or the one COLA_HOP_SHAPE pins.
-TuneEntry untuned_entry(const Geom &g, int prec, int nrhs, bool both) {
-    TuneEntry t = default_entry(g, prec, nrhs, both);
+TuneEntry untuned_entry(const Geom &g, int prec, int nrhs, bool both, bool clover) {
+    TuneEntry t = default_entry(g, prec, nrhs, both, clover);
     // Measurement knob: COLA_HOP_SHAPE="rpt,sites_per_block,grid,tchunk" pins the
     // untuned launch shape (ignored unless every field is valid for this launch).
     if (const char *env = getenv("COLA_HOP_SHAPE")) {
@@ -317,7 +352,7 @@ TuneEntry untuned_entry(const Geom &g, int prec, int nrhs, bool both) {
         if ((n == 4 || n == 6 || n == 7) && shape_valid(g, prec, nrhs, e)) {
             // staging as asked where possible, else the default rule
             const bool ok = stage_ok(g, prec, nrhs, e);
-            e.stage = e.stage < 0 ? (ok ? 1 : 0) : (e.stage && ok ? 1 : 0);
+            if (e.stage != 2) e.stage = e.stage < 0 ? (ok ? 1 : 0) : (e.stage && ok ? 1 : 0);
             t = e;
         }
     }
@@ -363,7 +398,11 @@ int fill_and_launch(cola_handle_t *h, const HopCall &c, int prec, int nrhs, cons
     a.div_ncol = make_fastdiv((uint32_t)h->g.s3);
     a.tile_y = te.tile_y;
     a.tile_z = te.tile_z;
-    a.stage_links = te.stage;
+    a.stage_links = te.stage == 1;
+    if (te.stage == 2) {
+        a.by_dirs = 1;
+        block = 8 * kDirsSites;
+    }
     if (te.tile_y > 0) {
         const Geom &g = h->g;
         a.div_tcols = make_fastdiv((uint32_t)(g.Lxh * te.tile_y * te.tile_z));
@@ -420,7 +459,7 @@ bool stored_entry(cola_handle_t *h, const std::string &key, int prec, int nrhs, 
     if (it == ts.table.end()) return false;
     TuneEntry e = it->second;
     if (!shape_valid(h->g, prec, nrhs, e)) return false;
-    if (e.stage && !stage_ok(h->g, prec, nrhs, e)) e.stage = 0;
+    if (e.stage == 1 && !stage_ok(h->g, prec, nrhs, e)) e.stage = 0;
     *out = e;
     return true;
 }
@@ -461,10 +500,16 @@ int tune_hop(cola_handle_t *h, const HopCall &c, int prec, int nrhs, TuneEntry *
             }
         }
     }
+    {
+        TuneEntry t;
+        t.stage = 2;
+        t.sites_per_block = kDirsSites / nrhs;
+        if (dirs_ok(h->g, prec, nrhs, t)) cand.push_back(t);
+    }
     // each shape also with the site's links staged in LDS, where that applies
     const size_t n0 = cand.size();
     for (size_t k = 0; k < n0; ++k) {
-        if (!stage_ok(h->g, prec, nrhs, cand[k])) continue;
+        if (cand[k].stage == 2 || !stage_ok(h->g, prec, nrhs, cand[k])) continue;
         TuneEntry t = cand[k];
         t.stage = 1;
         cand.push_back(t);
@@ -566,13 +611,15 @@ int hop(cola_handle_t *h, const HopCall &c, int prec, int nrhs, hipStream_t st) 
         const std::string path = tune_cache_path();
         if (!path.empty()) write_table(path, ts.table);
     } else if (!stored_entry(h, key, prec, nrhs, !c.fixed, &te)) {
-        te = untuned_entry(h->g, prec, nrhs, c.both);
+        te = untuned_entry(h->g, prec, nrhs, c.both,
+                           c.epi != EPI_NONE && c.epi != EPI_XPAY && c.epi != EPI_XPAY_CG);
     }
     // a resident grid needs an occupancy query (cached in a host map): the fixed mode
     // takes the plain grid instead, which gives bitwise the same output
     if (c.fixed && te.grid < 0) te.grid = 0;
     // FLIC hops: one rhs per lane, both links loaded per lane
     if (h->flic) {
+        if (te.stage == 2) te = plain_entry(h->g, prec, nrhs, c.both);
         te.rpt = 1;
         te.stage = 0;
     }
