@@ -145,7 +145,7 @@ struct HopArgs {
     // instead of launching
     int *occupancy;
     // CG epilogues: the solver's vectors (parity `parity` blocks of the launch format)
-    // and its per-rhs scalars
+    // and its per-rhs scalars; cg_x null: only r is updated (cg_p is not read)
     void *cg_x, *cg_r;
     const void *cg_p;
     const double *cg_rho, *cg_pi;

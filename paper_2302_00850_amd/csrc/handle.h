@@ -153,7 +153,7 @@ int hop(cola_handle_t *h, const HopCall &c, int prec, int nrhs, hipStream_t st);
 // One CG step on the even-odd normal system S^dag S, with the update fused into the
 // last hop: pi = |S p|^2, then with alpha = rho / pi per active rhs,
 //   x += alpha p,  r -= alpha S^dag S p,  rho_new = |r|^2.
-// x, r, p: even-parity blocks in the storage of prec.
+// x, r, p: even-parity blocks in the storage of prec (x null: no x update).
 int schur_normal_cg_step(cola_handle_t *h, int prec, int nrhs, hipStream_t st, void *x, void *r,
                          const void *p, const double *rho, double *pi, const int *active,
                          double *rho_new);

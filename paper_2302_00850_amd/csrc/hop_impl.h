@@ -455,7 +455,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK ? 3
                 // x += alpha p, r -= alpha o; o becomes the stored r (for the norm)
                 const double den = a.cg_pi[rr];
                 const T al = (T)(a.cg_active[rr] && den != 0.0 ? a.cg_rho[rr] / den : 0.0);
-                {
+                if (a.cg_x) {
                     C xv[12], pv[12];
                     cgx.load(i, rr, xv);
                     cgp.load(i, rr, pv);

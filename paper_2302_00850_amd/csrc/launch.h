@@ -41,8 +41,8 @@ struct BlasShape {
 };
 BlasShape blas_shape(const Geom &g, int nrhs, int nblk);
 
-// Multi-shift CG, FP64, shifts as the rhs of the x and p fields (R = sh.R) and the
-// shared residual r a one-rhs field: for active shifts q,
+// Multi-shift CG, FP64, each shift's x and p a one-rhs field, one after the other, and the
+// shared residual r: for active shifts q,
 //   x_q += alpha_q p_q ;  p_q = zeta_q r + beta_q p_q
 struct MsCoef {
     double alpha[kRedMaxWidth], zeta[kRedMaxWidth], beta[kRedMaxWidth];
@@ -68,8 +68,13 @@ hipError_t launch_ms_init(MsState *state, const double *sigma, int nshift, doubl
 // one iteration of the recursion from the base rho' and pi
 hipError_t launch_ms_advance(MsState *state, const double *rho_new, const double *pi,
                              hipStream_t st);
-hipError_t launch_ms_update(const BlasShape &sh, void *x, void *p, const void *r,
-                            const MsCoef *k, hipStream_t st);
+// the shifts' update on fields of n complex values, and base_p = r + (rho_new / rho) base_p
+// when base_p is not null
+hipError_t launch_ms_update(void *x, void *p, const void *r, void *base_p, const MsCoef *k,
+                            int nshift, const double *rho_new, const double *rho, size_t n,
+                            hipStream_t st);
+// the shifts' fields into the rhs of one packed field: out[e nshift + q] = x[q n + e]
+hipError_t launch_ms_gather(void *out, const void *x, int nshift, size_t n, hipStream_t st);
 // result_q = |b - ax_q - sigma_q x_q|^2 (b a one-rhs field, ax and x with R = sh.R)
 hipError_t launch_ms_residual(const BlasShape &sh, const void *b, const void *ax, const void *x,
                               const double *sigma, const Reduce &red, hipStream_t st);

@@ -89,7 +89,8 @@ int normal(const Ctx &c, int prec, void *out, const void *in) {
 // last hop (Ap is never stored): the last hop of S^dag S on the even-odd system, the hop of
 // M^dag on the full lattice; COLA_CG_FUSE=0 selects the separate update
 // kernel.
-int full_normal_cg_step(const Ctx &c, int prec, void *x, void *r, void *pv) {
+int full_normal_cg_step(const Ctx &c, int prec, void *x, void *r, void *pv, const double *rho,
+                        double *rho_new) {
     cola_handle_t *h = c.h;
     const SpinorFmt sf = spinor_fmt(prec);
     void *t;
@@ -104,11 +105,11 @@ int full_normal_cg_step(const Ctx &c, int prec, void *x, void *r, void *pv) {
     hc.x = t;
     hc.a = -h->kappa;
     hc.clov = sf == SpinorFmt::F64 ? h->clov64 : h->clov32;
-    hc.norm_result = c.slot(RHO_NEW);
+    hc.norm_result = rho_new;
     hc.cg_x = x;
     hc.cg_r = r;
     hc.cg_p = pv;
-    hc.cg_rho = c.slot(RHO);
+    hc.cg_rho = rho;
     hc.cg_pi = c.slot(PI);
     hc.cg_active = h->active;
     return hop(h, hc, prec, c.R, c.st);
@@ -119,7 +120,7 @@ int cg_step(const Ctx &c, int prec, SpinorFmt fx, void *x, void *r, void *pv, vo
     const SpinorFmt fp = spinor_fmt(prec);
     const char *env = getenv("COLA_CG_FUSE");
     const bool fuse = fx == fp && !(env && env[0] == '0');
-    if (fuse && c.full) return full_normal_cg_step(c, prec, x, r, pv);
+    if (fuse && c.full) return full_normal_cg_step(c, prec, x, r, pv, c.slot(RHO), c.slot(RHO_NEW));
     if (fuse)
         return schur_normal_cg_step(h, prec, c.R, c.st, x, r, pv, c.slot(RHO), c.slot(PI),
                                     h->active, c.slot(RHO_NEW));
@@ -790,10 +791,10 @@ int cg_solve_impl(cola_handle_t *h, void *x, const void *b, int nrhs, const cola
 //   zeta_q' = zeta_q zeta_q^old alpha^old /
 //             (alpha beta^old (zeta_q^old - zeta_q) + zeta_q^old alpha^old (1 + sigma_q alpha))
 //   x_q += alpha zeta_q'/zeta_q p_q ;  p_q = zeta_q' r' + beta (zeta_q'/zeta_q)^2 p_q
-// (zeta = zeta^old = 1, alpha^old = 1, beta^old = 0, p_q = b at the start).  The
-// shifts' x and p live as the rhs of one packed field; the scalar recursion runs on
-// the host from the base alpha and beta read back each iteration.  A shift stops once
-// zeta_q^2 |r|^2 <= tol^2 |b|^2; its true residual is then checked against twice that.
+// (zeta = zeta^old = 1, alpha^old = 1, beta^old = 0, p_q = b at the start).  Each shift's x
+// and p are one-rhs fields; the scalar recursion runs on the device.  The base CG's own x is
+// not needed, so its last hop updates r only.  A shift stops once zeta_q^2 |r|^2 <= tol^2
+// |b|^2; its true residual is then checked against twice that.
 int cg_multishift_impl(cola_handle_t *h, void *x, const void *b, int nshift, const double *sigma,
                        const cola_cg_params_t *p, cola_cg_result_t *res, hipStream_t st) {
     const auto t0 = std::chrono::steady_clock::now();
@@ -801,12 +802,10 @@ int cg_multishift_impl(cola_handle_t *h, void *x, const void *b, int nshift, con
     Ctx c{h, st, 1, full};
     Ctx cn{h, st, nshift, full};
     const BlasShape sh1 = c.shape(), shn = cn.shape();
-    void *b64, *r64, *p64, *ap, *xb, *xs, *ps, *axs;
+    void *b64, *r64, *p64, *xs, *ps, *axs;
     COLA_TRY(vec(c, "b64", SpinorFmt::F64, &b64));
     COLA_TRY(vec(c, "r64", SpinorFmt::F64, &r64));
     COLA_TRY(vec(c, "ms_p", SpinorFmt::F64, &p64));
-    COLA_TRY(vec(c, "ms_ap", SpinorFmt::F64, &ap));
-    COLA_TRY(vec(c, "ms_xb", SpinorFmt::F64, &xb));
     COLA_TRY(vec(cn, "ms_xs", SpinorFmt::F64, &xs));
     COLA_TRY(vec(cn, "ms_ps", SpinorFmt::F64, &ps));
     COLA_TRY(vec(cn, "ms_axs", SpinorFmt::F64, &axs));
@@ -814,7 +813,6 @@ int cg_multishift_impl(cola_handle_t *h, void *x, const void *b, int nshift, con
     const size_t b1 = c.bytes(SpinorFmt::F64), bn_ = cn.bytes(SpinorFmt::F64);
     COLA_HIP(h, hipMemcpyAsync(r64, b64, b1, hipMemcpyDeviceToDevice, st));
     COLA_HIP(h, hipMemcpyAsync(p64, b64, b1, hipMemcpyDeviceToDevice, st));
-    COLA_HIP(h, hipMemsetAsync(xb, 0, b1, st));
     COLA_HIP(h, hipMemsetAsync(xs, 0, bn_, st));
     COLA_HIP(h, hipMemsetAsync(ps, 0, bn_, st));
     // the shift recursion lives on the device (MsState): init writes the first update's
@@ -826,7 +824,9 @@ int cg_multishift_impl(cola_handle_t *h, void *x, const void *b, int nshift, con
     MsState *state = (MsState *)state_v;
     COLA_HIP(h, launch_norm2(sh1, SpinorFmt::F64, b64, reduce_into(h, BNORM), st));
     COLA_HIP(h, launch_ms_init(state, sigma, nshift, p->tol * p->tol, c.slot(BNORM), st));
-    COLA_HIP(h, launch_ms_update(shn, xs, ps, r64, &state->coef, st));
+    const size_t n = b1 / sizeof(Cplx64);
+    double *rho = c.slot(RHO), *rho_new = c.slot(RHO_NEW);
+    COLA_HIP(h, launch_ms_update(xs, ps, r64, nullptr, &state->coef, nshift, rho_new, rho, n, st));
     double bnorm = 0.0;
     COLA_TRY(read_slot(c, BNORM, &bnorm));
     COLA_HIP(h, hipMemcpyAsync(c.slot(RHO), c.slot(BNORM), sizeof(double),
@@ -846,15 +846,14 @@ int cg_multishift_impl(cola_handle_t *h, void *x, const void *b, int nshift, con
             status = COLA_NOT_CONVERGED;
             break;
         }
-        COLA_TRY(normal(c, COLA_FP64, ap, p64));
-        COLA_HIP(h, launch_cg_xr(sh1, SpinorFmt::F64, SpinorFmt::F64, SpinorFmt::F64,
-                                 SpinorFmt::F64, xb, p64, r64, ap, c.slot(RHO), c.slot(PI),
-                                 h->active, reduce_into(h, RHO_NEW), st));
-        COLA_HIP(h, launch_ms_advance(state, c.slot(RHO_NEW), c.slot(PI), st));
-        COLA_HIP(h, launch_ms_update(shn, xs, ps, r64, &state->coef, st));
-        COLA_HIP(h, launch_cg_p(sh1, SpinorFmt::F64, SpinorFmt::F64, r64, p64, c.slot(RHO_NEW),
-                                c.slot(RHO), h->active, st));
-        COLA_TRY(rotate_rho(c));
+        if (full)
+            COLA_TRY(full_normal_cg_step(c, COLA_FP64, nullptr, r64, p64, rho, rho_new));
+        else
+            COLA_TRY(schur_normal_cg_step(h, COLA_FP64, 1, st, nullptr, r64, p64, rho,
+                                          c.slot(PI), h->active, rho_new));
+        COLA_HIP(h, launch_ms_advance(state, rho_new, c.slot(PI), st));
+        COLA_HIP(h, launch_ms_update(xs, ps, r64, p64, &state->coef, nshift, rho_new, rho, n, st));
+        std::swap(rho, rho_new);
         ++it;
         if (it % check == 0 || it >= p->max_iter) {
             COLA_HIP(h, hipMemcpyAsync(flags, &state->status, sizeof flags,
@@ -871,15 +870,17 @@ int cg_multishift_impl(cola_handle_t *h, void *x, const void *b, int nshift, con
     iters = finished ? flags[2] : it;
     // true residuals |b - (A + sigma_q) x_q| / |b|, all shifts in one multi-rhs pass
     std::vector<double> tr(nshift, 0.0);
-    COLA_TRY(normal(cn, COLA_FP64, axs, xs));
-    COLA_HIP(h, launch_ms_residual(shn, b64, axs, xs, sigma, reduce_into(h, TRUE_RES), st));
+    void *xr = ps;  // the directions are done with
+    COLA_HIP(h, launch_ms_gather(xr, xs, nshift, n, st));
+    COLA_TRY(normal(cn, COLA_FP64, axs, xr));
+    COLA_HIP(h, launch_ms_residual(shn, b64, axs, xr, sigma, reduce_into(h, TRUE_RES), st));
     COLA_TRY(read_slot(cn, TRUE_RES, tr.data()));
     // the recursive residuals drift from the true ones by rounding: a shift counts as
     // converged within twice the tolerance
     for (int q = 0; q < nshift; ++q)
         if (!(tr[q] <= 4.0 * thr) && status == COLA_OK) status = COLA_NOT_CONVERGED;
     if (!full) COLA_HIP(h, hipMemsetAsync(x, 0, (size_t)h->g.Vh * 2 * 12 * 16 * nshift, st));
-    COLA_HIP(h, launch_unpack_spinor(h->g, SpinorFmt::F64, x, xs, nshift, full ? -1 : 0, st));
+    COLA_HIP(h, launch_unpack_spinor(h->g, SpinorFmt::F64, x, xr, nshift, full ? -1 : 0, st));
     COLA_HIP(h, hipStreamSynchronize(st));
     if (res) {
         res->status = status;
