@@ -139,9 +139,10 @@ int cola_destroy(cola_handle_t *h) {
 
 const char *cola_last_error(const cola_handle_t *h) { return h ? h->err.c_str() : "null handle"; }
 
-// Pack a canonical field into the four link formats of dst (allocated on first use);
-// *dev receives the largest SU(3) deviation of its links.
-int pack_links(cola_handle_t *h, const void *U, void *dst[4], double *dev_out, hipStream_t st) {
+// Pack a canonical (packed: 18-real packed) field into the four link formats of dst
+// (allocated on first use); *dev receives the largest SU(3) deviation of its links.
+int pack_links(cola_handle_t *h, const void *U, bool packed, void *dst[4], double *dev_out,
+               hipStream_t st) {
     const Geom &g = h->g;
     for (int f = 0; f < 4; ++f) {
         const size_t bytes =
@@ -156,7 +157,7 @@ int pack_links(cola_handle_t *h, const void *U, void *dst[4], double *dev_out, h
     COLA_TRY(get_vec(h, "su3_dev", 64, &tmp));
     dev = (unsigned long long *)tmp;
     COLA_HIP(h, hipMemsetAsync(dev, 0, 8, st));
-    COLA_HIP(h, launch_pack_gauge(g, U, dst[0], dst[1], dst[2], dst[3], dev, st));
+    COLA_HIP(h, launch_pack_gauge(g, U, packed, dst[0], dst[1], dst[2], dst[3], dev, st));
     unsigned long long bits = 0;
     COLA_HIP(h, hipMemcpyAsync(&bits, dev, 8, hipMemcpyDeviceToHost, st));
     COLA_HIP(h, hipStreamSynchronize(st));
@@ -189,13 +190,10 @@ int build_clover(cola_handle_t *h, const void *W, hipStream_t st) {
     return COLA_OK;
 }
 
-int cola_set_gauge(cola_handle_t *h, const void *U, void *stream) {
-    if (!h) return COLA_EINVAL;
-    if (!U) return set_error(h, COLA_EINVAL, "null gauge pointer");
-    hipStream_t st = as_stream(stream);
+extern "C++" int cola::set_links(cola_handle_t *h, const void *U, bool packed, hipStream_t st) {
     double d;
     h->flic = false;
-    COLA_TRY(pack_links(h, U, h->gauge, &d, st));
+    COLA_TRY(pack_links(h, U, packed, h->gauge, &d, st));
     h->su3_dev = d;
     h->su3 = d <= 1e-12;
     if (h->csw != 0.0) {
@@ -209,6 +207,12 @@ int cola_set_gauge(cola_handle_t *h, const void *U, void *stream) {
     return COLA_OK;
 }
 
+int cola_set_gauge(cola_handle_t *h, const void *U, void *stream) {
+    if (!h) return COLA_EINVAL;
+    if (!U) return set_error(h, COLA_EINVAL, "null gauge pointer");
+    return set_links(h, U, false, as_stream(stream));
+}
+
 int cola_set_fat_gauge(cola_handle_t *h, const void *F, void *stream) {
     if (!h) return COLA_EINVAL;
     if (!F) return set_error(h, COLA_EINVAL, "null fat-link pointer");
@@ -216,7 +220,7 @@ int cola_set_fat_gauge(cola_handle_t *h, const void *F, void *stream) {
     hipStream_t st = as_stream(stream);
     double d;
     h->flic = false;
-    COLA_TRY(pack_links(h, F, h->fat, &d, st));
+    COLA_TRY(pack_links(h, F, false, h->fat, &d, st));
     if (!(d <= 1e-12))
         return set_error(h, COLA_EINVAL, "smeared links are not SU(3) (deviation " +
                                              std::to_string(d) + ")");

@@ -150,6 +150,9 @@ struct HopCall {
 };
 int hop(cola_handle_t *h, const HopCall &c, int prec, int nrhs, hipStream_t st);
 
+// The handle's links from U, canonical or (packed) in the packed 18-real format.
+int set_links(cola_handle_t *h, const void *U, bool packed, hipStream_t st);
+
 // One CG step on the even-odd normal system S^dag S, with the update fused into the
 // last hop: pi = |S p|^2, then with alpha = rho / pi per active rhs,
 //   x += alpha p,  r -= alpha S^dag S p,  rho_new = |r|^2.

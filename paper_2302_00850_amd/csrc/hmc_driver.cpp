@@ -1,11 +1,11 @@
 // HMC entry points and the leapfrog trajectory driver (hybrid Monte Carlo, the gauge-field
 // generation algorithm in the paper's list, after Duane et al.).  The driver sequences
-// the library's own kernels: gauge force, fermion solve and force (the FP64 CG on
-// M^H M, Y = M X, the link-wise force kernel), momentum and link updates, and the
-// reductions that give H.
+// the library's own kernels: the gauge kick with the link update, the fermion solve and kick
+// (the CG on M^H M, Y = M X, the link-wise force kernel), and the reductions that give H.
 #include <chrono>
 #include <cmath>
 #include <string>
+#include <vector>
 
 #include "cola.h"
 #include "handle.h"
@@ -19,31 +19,36 @@ hipStream_t hstream(void *s) { return (hipStream_t)s; }
 
 size_t nlinks(const cola_handle_t *h) { return (size_t)8 * h->g.Vh; }
 
-// device scratch of the trajectory: forces, fermion vectors, packed M X, scalars
+// device scalars of the trajectory: the parts of H at its start and end (the plaquette sum
+// four times over)
+enum Scalar { KIN0, RETR0, SF0, RETR1, SF1, KIN1, NSCALAR };
+
+// device scratch of the trajectory: packed links (the step reads one and writes the other)
+// and momenta, fermion vectors
 struct HmcWork {
-    void *Fg = nullptr, *Ff = nullptr;  // gauge / fermion force (canonical gauge shape)
-    void *X = nullptr, *Y = nullptr;    // canonical spinors
-    void *Xp = nullptr, *Yp = nullptr;  // packed FP64 full-lattice spinors
-    double *sc = nullptr;               // 4 device scalars
+    void *U[2] = {nullptr, nullptr}, *P = nullptr;
+    void *X = nullptr;                 // canonical spinor: the CG's solution and next guess
+    void *Xp = nullptr, *Yp = nullptr; // packed FP64 full-lattice spinors
+    double *sc = nullptr;              // NSCALAR device scalars
 };
 
 int scalars(cola_handle_t *h, double **sc) {
     void *p;
-    COLA_TRY(get_vec(h, "hmc_sc", 4 * sizeof(double), &p));
+    COLA_TRY(get_vec(h, "hmc_sc", NSCALAR * sizeof(double), &p));
     *sc = (double *)p;
     return COLA_OK;
 }
 
 int work(cola_handle_t *h, bool fermions, HmcWork *w) {
-    const size_t gb = nlinks(h) * 9 * 16;
-    COLA_TRY(get_vec(h, "hmc_Fg", gb, &w->Fg));
+    const size_t gb = (size_t)8 * 9 * 16 * h->g.S;
+    COLA_TRY(get_vec(h, "hmc_U0", gb, &w->U[0]));
+    COLA_TRY(get_vec(h, "hmc_U1", gb, &w->U[1]));
+    COLA_TRY(get_vec(h, "hmc_P", gb, &w->P));
     COLA_TRY(scalars(h, &w->sc));
     if (!fermions) return COLA_OK;
     const size_t sb = (size_t)2 * h->g.Vh * 12 * 16;
     const size_t pb = cola_field_bytes(h, COLA_FP64, 1, -1);
-    COLA_TRY(get_vec(h, "hmc_Ff", gb, &w->Ff));
     COLA_TRY(get_vec(h, "hmc_X", sb, &w->X));
-    COLA_TRY(get_vec(h, "hmc_Y", sb, &w->Y));
     COLA_TRY(get_vec(h, "hmc_Xp", pb, &w->Xp));
     COLA_TRY(get_vec(h, "hmc_Yp", pb, &w->Yp));
     return COLA_OK;
@@ -57,15 +62,21 @@ double read_scalar(cola_handle_t *h, const double *d, hipStream_t st, int *rc) {
     return v;
 }
 
-// Even-odd pseudofermion S_f = phi_e^H (S^H S)^{-1} phi_e (plain Wilson): with
-// X_e = (S^H S)^{-1} phi_e and Y_e = S X_e,
+// The fermion force at the links U (packed) kicks the momenta: P -= eps F_f; sf (device, may
+// be null) receives S_f = Re <phi, X>.  X of the previous call is the CG's starting guess.
+//
+// Full lattice: X = (M^H M)^{-1} phi, Y = M X.  Even-odd pseudofermion
+// S_f = phi_e^H (S^H S)^{-1} phi_e (plain Wilson): with X_e = (S^H S)^{-1} phi_e and
+// Y_e = S X_e,
 //   dS_f = 2 kappa^2 Re[Y_e^H dD_eo X_o + Y_o^H dD_oe X_e],  X_o = D_oe X_e, Y_o = D_eo^H Y_e,
 // which is the full-lattice fermion force of (X_e, X_o) and (Y_e, Y_o) with kappa^2 in
-// place of kappa.  The handle's gauge field is already packed from U.
-int forces_eo(cola_handle_t *h, const void *phi, const cola_hmc_params_t *p, HmcWork &w,
-              bool first, bool energy, double *sf, int *iters, int *status, hipStream_t st) {
+// place of kappa.
+int fermion_kick(cola_handle_t *h, const void *U, const void *phi, const cola_hmc_params_t *p,
+                 HmcWork &w, bool first, double eps, double *sf, int *iters, int *status,
+                 hipStream_t st) {
+    COLA_TRY(set_links(h, U, true, st));
     cola_cg_params_t cp{};
-    cp.system = COLA_SYS_SCHUR;
+    cp.system = p->eo ? COLA_SYS_SCHUR : COLA_SYS_MDAGM;
     cp.scheme = p->cg_scheme;
     cp.tol = p->cg_tol;
     cp.max_iter = p->cg_max_iter;
@@ -74,81 +85,66 @@ int forces_eo(cola_handle_t *h, const void *phi, const cola_hmc_params_t *p, Hmc
     double res = 0.0;
     cola_cg_result_t cr{};
     cr.true_rel_residual = &res;
-    COLA_TRY(cola_cg_solve(h, w.X, phi, 1, &cp, &cr, st));  // odd sites of X set to 0
+    COLA_TRY(cola_cg_solve(h, w.X, phi, 1, &cp, &cr, st));  // even-odd: odd sites of X set to 0
     *iters += cr.iterations;
     if (cr.status != COLA_OK) *status = COLA_NOT_CONVERGED;
-    const size_t blk = cola_field_bytes(h, COLA_FP64, 1, 0);
-    char *xe = (char *)w.Xp, *xo = xe + blk, *ye = (char *)w.Yp, *yo = ye + blk;
     COLA_TRY(cola_pack_spinor(h, w.Xp, w.X, COLA_FP64, 1, -1, st));
-    COLA_TRY(cola_dslash_apply(h, xo, xe, COLA_OP_HOP, 1, COLA_FP64, 1, st));
-    COLA_TRY(cola_dslash_apply(h, ye, xe, COLA_OP_SCHUR, 0, COLA_FP64, 1, st));
-    COLA_TRY(cola_dslash_apply(h, yo, ye, COLA_OP_HOP_DAG, 1, COLA_FP64, 1, st));
-    COLA_TRY(cola_unpack_spinor(h, w.Y, w.Yp, COLA_FP64, 1, -1, st));
-    if (energy) {
-        // X still has zero odd sites here: Re <phi, X> = Re <phi_e, X_e>
-        COLA_HIP(h, launch_redot(phi, w.X, (size_t)2 * h->g.Vh * 12, h->partial, w.sc + 1, st));
-        int rc = COLA_OK;
-        *sf = read_scalar(h, w.sc + 1, st, &rc);
-        COLA_TRY(rc);
+    if (p->eo) {
+        const size_t blk = cola_field_bytes(h, COLA_FP64, 1, 0);
+        char *xe = (char *)w.Xp, *xo = xe + blk, *ye = (char *)w.Yp, *yo = ye + blk;
+        COLA_TRY(cola_dslash_apply(h, xo, xe, COLA_OP_HOP, 1, COLA_FP64, 1, st));
+        COLA_TRY(cola_dslash_apply(h, ye, xe, COLA_OP_SCHUR, 0, COLA_FP64, 1, st));
+        COLA_TRY(cola_dslash_apply(h, yo, ye, COLA_OP_HOP_DAG, 1, COLA_FP64, 1, st));
+    } else {
+        COLA_TRY(cola_dslash_apply(h, w.Yp, w.Xp, COLA_OP_M, -1, COLA_FP64, 1, st));
     }
-    COLA_TRY(cola_unpack_spinor(h, w.X, w.Xp, COLA_FP64, 1, -1, st));
-    COLA_HIP(h, launch_force(h->g, h->gauge[0], w.X, w.Y, w.Ff, h->kappa * h->kappa, h->phase,
-                             COLA_FORCE_LIE, st));
+    if (sf)
+        COLA_HIP(h, launch_redot(phi, w.X, (size_t)2 * h->g.Vh * 12, h->partial, sf, st));
+    COLA_HIP(h, launch_fermion_kick(h->g, U, w.Xp, w.Yp, w.P,
+                                    p->eo ? h->kappa * h->kappa : h->kappa, h->phase, eps, st));
     return COLA_OK;
 }
 
-// Forces at the current U into w.Fg (and w.Ff with fermions); with `energy`, the parts
-// of H that depend on U: *sg = S_g, *sf = S_f = Re <phi, X>.  X of the previous call is
-// the CG's starting guess.
-int forces(cola_handle_t *h, void *U, const void *phi, const cola_hmc_params_t *p, HmcWork &w,
-           bool first, bool energy, double *sg, double *sf, int *iters, int *status,
-           hipStream_t st) {
-    COLA_HIP(h, launch_gauge_force(h->g, U, w.Fg, p->beta, st));
-    if (energy) {
-        COLA_HIP(h, launch_plaquette_sum(h->g, U, h->partial, w.sc, st));
-        int rc = COLA_OK;
-        const double plaq = read_scalar(h, w.sc, st, &rc);
-        COLA_TRY(rc);
-        *sg = p->beta * (6.0 * 2.0 * h->g.Vh - plaq / 3.0);
-    }
-    if (!phi) {
-        if (energy) *sf = 0.0;
-        return COLA_OK;
-    }
-    COLA_TRY(cola_set_gauge(h, U, st));
-    if (p->eo) return forces_eo(h, phi, p, w, first, energy, sf, iters, status, st);
-    cola_cg_params_t cp{};
-    cp.system = COLA_SYS_MDAGM;
-    cp.scheme = p->cg_scheme;
-    cp.tol = p->cg_tol;
-    cp.max_iter = p->cg_max_iter;
-    cp.reliable_interval = 50;
-    cp.use_x0 = first ? 0 : 1;
-    double res = 0.0;
-    cola_cg_result_t cr{};
-    cr.true_rel_residual = &res;
-    COLA_TRY(cola_cg_solve(h, w.X, phi, 1, &cp, &cr, st));
-    *iters += cr.iterations;
-    if (cr.status != COLA_OK) *status = COLA_NOT_CONVERGED;
-    // Y = M X through the packed FP64 field
-    COLA_TRY(cola_pack_spinor(h, w.Xp, w.X, COLA_FP64, 1, -1, st));
-    COLA_TRY(cola_dslash_apply(h, w.Yp, w.Xp, COLA_OP_M, -1, COLA_FP64, 1, st));
-    COLA_TRY(cola_unpack_spinor(h, w.Y, w.Yp, COLA_FP64, 1, -1, st));
-    COLA_TRY(cola_fermion_force(h, w.Ff, w.X, w.Y, COLA_FORCE_LIE, st));
-    if (energy) {
-        COLA_HIP(h, launch_redot(phi, w.X, (size_t)2 * h->g.Vh * 12, h->partial, w.sc + 1, st));
-        int rc = COLA_OK;
-        *sf = read_scalar(h, w.sc + 1, st, &rc);
-        COLA_TRY(rc);
-    }
-    return COLA_OK;
-}
+// One stage of the integrator at the current links: the fermion kick (if any), then the
+// gauge kick and, unless it is the last, the link update.
+struct Stage {
+    bool fermions;
+    double eps_f, eps_g, eps_u;
+};
 
-int kinetic(cola_handle_t *h, const void *P, HmcWork &w, hipStream_t st, double *k) {
-    COLA_HIP(h, launch_sqnorm(P, nlinks(h) * 9, h->partial, w.sc + 2, st));
-    int rc = COLA_OK;
-    *k = 0.5 * read_scalar(h, w.sc + 2, st, &rc);
-    return rc;
+std::vector<Stage> stages(const cola_hmc_params_t *p) {
+    std::vector<Stage> v;
+    const double eps = p->eps;
+    if (p->integrator == 0) {
+        // leapfrog: P eps/2, then per step U eps and P eps (eps/2 after the last)
+        for (int k = 0; k <= p->nsteps; ++k) {
+            const double e = k == 0 || k == p->nsteps ? 0.5 * eps : eps;
+            v.push_back({true, e, e, eps});
+        }
+    } else if (p->integrator == 2) {
+        // two time scales: fermion kicks of eps around n_gauge gauge leapfrog sub-steps of
+        // eps / n_gauge; the half gauge kicks that end one step and start the next are one
+        const int m = p->n_gauge;
+        const double hs = eps / m;
+        for (int k = 0; k <= p->nsteps; ++k) {
+            const bool end = k == 0 || k == p->nsteps;
+            v.push_back({true, end ? 0.5 * eps : eps, end ? 0.5 * hs : hs, hs});
+            for (int j = 1; j < m && k < p->nsteps; ++j) v.push_back({false, 0.0, hs, hs});
+        }
+    } else {
+        // Omelyan: P lambda eps, then per step U eps/2, P (1 - 2 lambda) eps, U eps/2 and
+        // P 2 lambda eps (the next step's first momentum step merged; lambda eps after the
+        // last)
+        const double lam = 0.1931833275037836;
+        v.push_back({true, lam * eps, lam * eps, 0.5 * eps});
+        for (int k = 0; k < p->nsteps; ++k) {
+            const double mid = (1.0 - 2.0 * lam) * eps;
+            const double e = (k == p->nsteps - 1 ? lam : 2.0 * lam) * eps;
+            v.push_back({true, mid, mid, 0.5 * eps});
+            v.push_back({true, e, e, 0.5 * eps});
+        }
+    }
+    return v;
 }
 
 }  // namespace
@@ -255,67 +251,46 @@ int cola_hmc_trajectory(cola_handle_t *h, void *U, void *P, const void *phi,
     COLA_TRY(work(h, phi != nullptr, &w));
     *r = cola_hmc_result_t{};
     r->status = COLA_OK;
-    const size_t nl = nlinks(h);
-    const double eps = p->eps;
     int status = COLA_OK, iters = 0;
 
-    // H0 and the force at the start
-    COLA_TRY(kinetic(h, P, w, st, &r->kinetic0));
-    COLA_TRY(forces(h, U, phi, p, w, true, true, &r->gauge0, &r->fermion0, &iters, &status, st));
-    const void *Ff = phi ? w.Ff : nullptr;
-    if (p->integrator == 0) {
-        // leapfrog: P eps/2, then per step U eps and P eps (eps/2 after the last)
-        COLA_HIP(h, launch_momentum_update(P, w.Fg, Ff, 0.5 * eps, nl, st));
-        for (int k = 0; k < p->nsteps; ++k) {
-            COLA_HIP(h, launch_link_update(U, P, eps, nl, st));
-            const bool last = k == p->nsteps - 1;
-            COLA_TRY(forces(h, U, phi, p, w, false, last, &r->gauge1, &r->fermion1, &iters,
-                            &status, st));
-            COLA_HIP(h, launch_momentum_update(P, w.Fg, Ff, last ? 0.5 * eps : eps, nl, st));
-        }
-    } else if (p->integrator == 2) {
-        // two time scales: fermion kicks of eps around n_gauge gauge leapfrog sub-steps of
-        // eps / n_gauge (w.Fg and w.Ff hold the forces at the current U)
-        const int m = p->n_gauge;
-        const double hs = eps / m;
-        if (Ff) COLA_HIP(h, launch_momentum_update(P, Ff, nullptr, 0.5 * eps, nl, st));
-        for (int k = 0; k < p->nsteps; ++k) {
-            const bool last = k == p->nsteps - 1;
-            COLA_HIP(h, launch_momentum_update(P, w.Fg, nullptr, 0.5 * hs, nl, st));
-            for (int j = 0; j < m; ++j) {
-                COLA_HIP(h, launch_link_update(U, P, hs, nl, st));
-                COLA_HIP(h, launch_gauge_force(h->g, U, w.Fg, p->beta, st));
-                COLA_HIP(h, launch_momentum_update(P, w.Fg, nullptr, j < m - 1 ? hs : 0.5 * hs,
-                                                   nl, st));
-            }
-            // the fermion force (and, after the last step, the energies) at the new U
-            COLA_TRY(forces(h, U, phi, p, w, false, last, &r->gauge1, &r->fermion1, &iters,
-                            &status, st));
-            if (Ff)
-                COLA_HIP(h, launch_momentum_update(P, Ff, nullptr, last ? 0.5 * eps : eps, nl,
-                                                   st));
-        }
-    } else {
-        // Omelyan: P lambda eps, then per step U eps/2, P (1 - 2 lambda) eps, U eps/2 and
-        // P 2 lambda eps (the next step's first momentum step merged; lambda eps after the
-        // last)
-        const double lam = 0.1931833275037836;
-        COLA_HIP(h, launch_momentum_update(P, w.Fg, Ff, lam * eps, nl, st));
-        for (int k = 0; k < p->nsteps; ++k) {
-            const bool last = k == p->nsteps - 1;
-            COLA_HIP(h, launch_link_update(U, P, 0.5 * eps, nl, st));
-            COLA_TRY(forces(h, U, phi, p, w, false, false, nullptr, nullptr, &iters, &status,
-                            st));
-            COLA_HIP(h, launch_momentum_update(P, w.Fg, Ff, (1.0 - 2.0 * lam) * eps, nl, st));
-            COLA_HIP(h, launch_link_update(U, P, 0.5 * eps, nl, st));
-            COLA_TRY(forces(h, U, phi, p, w, false, last, &r->gauge1, &r->fermion1, &iters,
-                            &status, st));
-            COLA_HIP(h, launch_momentum_update(P, w.Fg, Ff, (last ? lam : 2.0 * lam) * eps, nl,
-                                               st));
-        }
+    // The trajectory runs on packed copies; the caller's fields receive its end.  The parts of
+    // H are left on the device and read once, after the last launch.
+    const size_t n = nlinks(h) * 9;
+    COLA_HIP(h, launch_sqnorm(P, n, h->partial, w.sc + KIN0, st));
+    COLA_HIP(h, launch_md_pack(h->g, U, P, w.U[0], w.P, st));
+    const std::vector<Stage> plan = stages(p);
+    int cur = 0;
+    for (size_t k = 0; k < plan.size(); ++k) {
+        const Stage &s = plan[k];
+        const bool first = k == 0, last = k + 1 == plan.size();
+        if (phi && s.fermions)
+            COLA_TRY(fermion_kick(h, w.U[cur], phi, p, w, first, s.eps_f,
+                                  first  ? w.sc + SF0
+                                  : last ? w.sc + SF1
+                                         : nullptr,
+                                  &iters, &status, st));
+        COLA_HIP(h, launch_md_step(h->g, w.U[cur], last ? nullptr : w.U[1 - cur], w.P, p->beta,
+                                   s.eps_g, s.eps_u, h->partial,
+                                   first  ? w.sc + RETR0
+                                   : last ? w.sc + RETR1
+                                          : nullptr,
+                                   st));
+        if (!last) cur = 1 - cur;
     }
-    COLA_TRY(kinetic(h, P, w, st, &r->kinetic1));
+    COLA_HIP(h, launch_md_unpack(h->g, U, P, w.U[cur], w.P, st));
+    COLA_HIP(h, launch_sqnorm(P, n, h->partial, w.sc + KIN1, st));
+    double sc[NSCALAR];
+    COLA_HIP(h, hipMemcpyAsync(sc, w.sc, sizeof sc, hipMemcpyDeviceToHost, st));
     COLA_HIP(h, hipStreamSynchronize(st));
+    const auto gauge = [&](double retr) {
+        return p->beta * (6.0 * 2.0 * h->g.Vh - 0.25 * retr / 3.0);
+    };
+    r->kinetic0 = 0.5 * sc[KIN0];
+    r->kinetic1 = 0.5 * sc[KIN1];
+    r->gauge0 = gauge(sc[RETR0]);
+    r->gauge1 = gauge(sc[RETR1]);
+    r->fermion0 = phi ? sc[SF0] : 0.0;
+    r->fermion1 = phi ? sc[SF1] : 0.0;
     r->H0 = r->kinetic0 + r->gauge0 + r->fermion0;
     r->H1 = r->kinetic1 + r->gauge1 + r->fermion1;
     r->dH = r->H1 - r->H0;

@@ -24,9 +24,10 @@ hipError_t launch_hop(const HopArgs &a, LinkFmt lf, int rpt, int grid, int block
 // --- packing
 // canonical complex128 U -> every non-null packed format; maxdev receives the
 // largest SU(3) deviation (max |U U^H - 1|, |det U - 1|) as the bits of a double.
-hipError_t launch_pack_gauge(const Geom &g, const void *U, void *g64_18, void *g64_12,
-                             void *g32_12, void *g16_12, unsigned long long *maxdev,
-                             hipStream_t st);
+// packed: U itself is a packed 18-real field.
+hipError_t launch_pack_gauge(const Geom &g, const void *U, bool packed, void *g64_18,
+                             void *g64_12, void *g32_12, void *g16_12,
+                             unsigned long long *maxdev, hipStream_t st);
 // canonical complex128 [nrhs][V][4][3] <-> packed; parity -1 = both parity blocks
 hipError_t launch_pack_spinor(const Geom &g, SpinorFmt f, void *dst, const void *src, int nrhs,
                               int parity, hipStream_t st);
@@ -171,6 +172,22 @@ hipError_t launch_momentum_update(void *P, const void *F1, const void *F2, doubl
                                   size_t nlinks, hipStream_t st);
 // U <- exp(i eps P) U over nlinks links, rows re-orthonormalised (row 2 = conj(row0 x row1))
 hipError_t launch_link_update(void *U, const void *P, double eps, size_t nlinks, hipStream_t st);
+
+// --- HMC trajectory on packed 18-real FP64 links U and momenta P
+// canonical U and P -> packed, and back
+hipError_t launch_md_pack(const Geom &g, const void *U, const void *P, void *Up, void *Pp,
+                          hipStream_t st);
+hipError_t launch_md_unpack(const Geom &g, void *U, void *P, const void *Up, const void *Pp,
+                            hipStream_t st);
+// P -= eps_p F_g(U); Unew = exp(i eps_u P) U if Unew is not null (Unew != U); with retr
+// (device), *retr = sum over links of Re Tr (U A) at U, four times the plaquette sum
+hipError_t launch_md_step(const Geom &g, const void *U, void *Unew, void *P, double beta,
+                          double eps_p, double eps_u, double *partial, double *retr,
+                          hipStream_t st);
+// P -= eps F, F the Lie-algebra fermion force of the packed FP64 one-rhs fields X and Y
+hipError_t launch_fermion_kick(const Geom &g, const void *U, const void *X, const void *Y, void *P,
+                               double kappa, const Cplx64 phase[4], double eps, hipStream_t st);
+
 // one APE smearing sweep Out = P_SU3[(1 - alpha) U + alpha/6 staples] (Out != U)
 hipError_t launch_ape_sweep(const Geom &g, const void *U, void *Out, double alpha,
                             hipStream_t st);

@@ -22,6 +22,9 @@ __device__ __forceinline__ T to_real(double v) {
     return (T)v;
 }
 
+// PACKED: U is a packed 18-real field (consecutive lanes then take consecutive sites of one
+// direction), else canonical.
+template <bool PACKED>
 __global__ void pack_gauge_kernel(const Geom g, const cpx<double> *__restrict__ U, void *g64_18,
                                   void *g64_12, void *g32_12, void *g16_12,
                                   unsigned long long *maxdev) {
@@ -29,16 +32,28 @@ __global__ void pack_gauge_kernel(const Geom g, const cpx<double> *__restrict__ 
     double dev = 0.0;
     for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < V * 4u;
          t += gridDim.x * blockDim.x) {
-        const uint32_t s = t >> 2;
-        const int mu = (int)(t & 3u);
-        int x[4];
-        lex_coords(g, s, x);
-        const int p = (x[0] + x[1] + x[2] + x[3]) & 1;
-        const uint32_t i = s >> 1;  // Lx even: checkerboard index
-        const cpx<double> *u = U + (size_t)t * 9;
+        int mu, p;
+        uint32_t i;
         cpx<double> m[9];
+        if constexpr (PACKED) {
+            const uint32_t a = t / (uint32_t)g.Vh;
+            i = t - a * (uint32_t)g.Vh;
+            p = (int)(a >> 2);
+            mu = (int)(a & 3u);
+            const cpx<double> *u = U + (size_t)a * 9 * (size_t)g.S + i;
 #pragma unroll
-        for (int k = 0; k < 9; ++k) m[k] = u[k];
+            for (int k = 0; k < 9; ++k) m[k] = u[(size_t)k * (size_t)g.S];
+        } else {
+            const uint32_t s = t >> 2;
+            mu = (int)(t & 3u);
+            int x[4];
+            lex_coords(g, s, x);
+            p = (x[0] + x[1] + x[2] + x[3]) & 1;
+            i = s >> 1;  // Lx even: checkerboard index
+            const cpx<double> *u = U + (size_t)t * 9;
+#pragma unroll
+            for (int k = 0; k < 9; ++k) m[k] = u[k];
+        }
         // SU(3) deviation: |U U^H - 1| and |det U - 1|
 #pragma unroll
         for (int a = 0; a < 3; ++a)
@@ -180,11 +195,12 @@ size_t spinor_block_bytes(const Geom &g, SpinorFmt f, int nrhs) {
 
 }  // namespace
 
-hipError_t launch_pack_gauge(const Geom &g, const void *U, void *g64_18, void *g64_12,
-                             void *g32_12, void *g16_12, unsigned long long *maxdev,
-                             hipStream_t st) {
+hipError_t launch_pack_gauge(const Geom &g, const void *U, bool packed, void *g64_18,
+                             void *g64_12, void *g32_12, void *g16_12,
+                             unsigned long long *maxdev, hipStream_t st) {
     const size_t work = (size_t)g.Vh * 2 * 4;
-    hipLaunchKernelGGL(pack_gauge_kernel, dim3(grid_for(work, 256)), dim3(256), 0, st, g,
+    const auto kernel = packed ? pack_gauge_kernel<true> : pack_gauge_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3(grid_for(work, 256)), dim3(256), 0, st, g,
                        (const cpx<double> *)U, g64_18, g64_12, g32_12, g16_12, maxdev);
     return hipGetLastError();
 }

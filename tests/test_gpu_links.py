@@ -44,3 +44,51 @@ def test_clover_blocks_match_oracle(dims):
     ref = oracle.apply_schur(U, even, kappa, ANTI, clover=A, clover_inv=oracle.site_inverse(A))
     assert_close(got, ref, 1e-13, dims)
     lat.close()
+
+
+@pytest.mark.parametrize("dims", LATTICES)
+@pytest.mark.parametrize("eps", [0.002, 0.01, 0.03, 0.06, 0.11, 1.5])
+def test_packed_trajectory_matches_canonical_updates(dims, eps):
+    """One leapfrog step (packed fields, kick and link update in one pass) against the updates
+    on canonical fields, for steps that take each order of the exponential's series and, the
+    largest, its squarings.  Rounding of P (force and step) and of the links."""
+    s, beta = Synth(91), 5.5
+    U0, P0 = _cuda(s.gauge(dims, mix=0.5).numpy()), _cuda(s.momenta(dims).numpy())
+    lat = cola.Lattice(dims, 0.12, ANTI)
+    U, P = U0.clone(), P0.clone()
+    info = lat.hmc_trajectory(U, P, beta, eps, 1)
+    Ur, Pr = U0.clone(), P0.clone()
+    lat.momentum_update(Pr, lat.gauge_force(Ur, beta), 0.5 * eps)
+    lat.link_update(Ur, Pr, eps)
+    lat.momentum_update(Pr, lat.gauge_force(Ur, beta), 0.5 * eps)
+    assert (U - Ur).abs().max().item() < 1e-13
+    assert (P - Pr).abs().max().item() < 1e-13 * (1 + eps) * beta
+    assert info["gauge0"] == pytest.approx(lat.gauge_action(U0, beta), rel=1e-12)
+    assert info["gauge1"] == pytest.approx(lat.gauge_action(U, beta), rel=1e-12)
+    assert info["kinetic1"] == pytest.approx(0.5 * P.abs().square().sum().item(), rel=1e-12)
+    lat.close()
+
+
+@pytest.mark.parametrize("dims", LATTICES)
+def test_packed_fermion_kick_matches_canonical_force(dims):
+    """The pseudofermion's kick of a short trajectory against the force on canonical fields;
+    the bound is the solves' tolerance times the size of X, Y and the force."""
+    s, beta, eps, tol = Synth(92), 5.5, 0.02, 1e-12
+    U0, P0 = _cuda(s.gauge(dims, mix=0.5).numpy()), _cuda(s.momenta(dims).numpy())
+    phi = _cuda(s.gaussian_spinor(dims).numpy()[0])
+    lat = cola.Lattice(dims, 0.12, bc_phases((0.3, 0, np.pi, np.pi)))
+    U, P = U0.clone(), P0.clone()
+    lat.hmc_trajectory(U, P, beta, eps, 1, phi=phi, cg_tol=tol)
+    Ur, Pr = U0.clone(), P0.clone()
+    for k in range(2):
+        lat.set_gauge(Ur)
+        X, Y = torch.empty_like(phi), torch.empty_like(phi)
+        cola.cola_fermion_action(lat.h, cola._ptr(phi), cola._ptr(X), cola._ptr(Y), tol,
+                                 cola._stream())
+        Ff = lat.force(X, Y, cola.COLA_FORCE_LIE)
+        lat.momentum_update(Pr, lat.gauge_force(Ur, beta), 0.5 * eps, Ff)
+        if k == 0:
+            lat.link_update(Ur, Pr, eps)
+    assert (U - Ur).abs().max().item() < 1e-10
+    assert (P - Pr).abs().max().item() < 1e-9
+    lat.close()
