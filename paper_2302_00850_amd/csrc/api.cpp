@@ -247,18 +247,15 @@ int cola_ape_smear(cola_handle_t *h, void *F, const void *U, double alpha, int n
         if (F != U) COLA_HIP(h, hipMemcpyAsync(F, U, bytes, hipMemcpyDeviceToDevice, st));
         return COLA_OK;
     }
-    void *tmp;
-    COLA_TRY(get_vec(h, "ape_tmp", bytes, &tmp));
-    // sweeps alternate between F and the work field so that the last lands in F; a sweep
-    // never reads the field it writes
-    const void *src = U;
-    for (int k = 0; k < nsweeps; ++k) {
-        void *dst = ((nsweeps - 1 - k) % 2 == 0) ? F : tmp;
-        if (dst == src) dst = dst == F ? tmp : F;  // F aliasing U on the first sweep
-        COLA_HIP(h, launch_ape_sweep(h->g, src, dst, alpha, st));
-        src = dst;
-    }
-    if (src != F) COLA_HIP(h, hipMemcpyAsync(F, src, bytes, hipMemcpyDeviceToDevice, st));
+    // the sweeps run on packed copies, from one to the other
+    void *w[2];
+    const size_t pb = (size_t)8 * 9 * 16 * h->g.S;
+    COLA_TRY(get_vec(h, "ape_w0", pb, &w[0]));
+    COLA_TRY(get_vec(h, "ape_w1", pb, &w[1]));
+    COLA_HIP(h, launch_md_pack(h->g, U, nullptr, w[0], nullptr, st));
+    for (int k = 0; k < nsweeps; ++k)
+        COLA_HIP(h, launch_ape_sweep(h->g, w[k & 1], w[(k + 1) & 1], alpha, st));
+    COLA_HIP(h, launch_md_unpack(h->g, F, nullptr, w[nsweeps & 1], nullptr, st));
     return COLA_OK;
 }
 

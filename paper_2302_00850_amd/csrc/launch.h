@@ -174,7 +174,7 @@ hipError_t launch_momentum_update(void *P, const void *F1, const void *F2, doubl
 hipError_t launch_link_update(void *U, const void *P, double eps, size_t nlinks, hipStream_t st);
 
 // --- HMC trajectory on packed 18-real FP64 links U and momenta P
-// canonical U and P -> packed, and back
+// canonical U and P (or U alone, P null) -> packed, and back
 hipError_t launch_md_pack(const Geom &g, const void *U, const void *P, void *Up, void *Pp,
                           hipStream_t st);
 hipError_t launch_md_unpack(const Geom &g, void *U, void *P, const void *Up, const void *Pp,
@@ -188,7 +188,8 @@ hipError_t launch_md_step(const Geom &g, const void *U, void *Unew, void *P, dou
 hipError_t launch_fermion_kick(const Geom &g, const void *U, const void *X, const void *Y, void *P,
                                double kappa, const Cplx64 phase[4], double eps, hipStream_t st);
 
-// one APE smearing sweep Out = P_SU3[(1 - alpha) U + alpha/6 staples] (Out != U)
+// one APE smearing sweep Out = P_SU3[(1 - alpha) U + alpha/6 staples] of packed 18-real
+// links (Out != U)
 hipError_t launch_ape_sweep(const Geom &g, const void *U, void *Out, double alpha,
                             hipStream_t st);
 // *result (device) = sum over sites and mu < nu of Re Tr U_plaq

@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import oracle
+import oracle.flic
 from paper_2302_00850_amd.synth import Synth, bc_phases
 from tests._util import assert_close
 
@@ -91,4 +92,15 @@ def test_packed_fermion_kick_matches_canonical_force(dims):
             lat.link_update(Ur, Pr, eps)
     assert (U - Ur).abs().max().item() < 1e-10
     assert (P - Pr).abs().max().item() < 1e-9
+    lat.close()
+
+
+@pytest.mark.parametrize("dims", LATTICES)
+@pytest.mark.parametrize("nsweeps", [1, 2])
+def test_ape_sweeps_match_oracle(dims, nsweeps):
+    """Smeared links; the projection's rounding, as on the other lattices."""
+    U = Synth(93).gauge(dims, mix=0.5).numpy()
+    lat = cola.Lattice(dims, 0.12, ANTI)
+    F = lat.ape_smear(_cuda(U), 0.7, nsweeps).cpu().numpy()
+    assert np.abs(F - oracle.flic.ape_smear(U, 0.7, nsweeps)).max() < 1e-12
     lat.close()
