@@ -51,7 +51,11 @@ struct Ctx {
     int nblk() const { return full ? 2 : 1; }
     size_t bytes(SpinorFmt f) const { return spinor_block_bytes(h->g, f, R) * nblk(); }
     BlasShape shape() const { return blas_shape(h->g, R, nblk()); }
-    double *slot(int s) const { return scal_slot(h, s); }
+    // RHO and RHO_NEW trade places each iteration (rotate_rho)
+    mutable int flip = 0;
+    int place(int s) const { return s <= RHO_NEW ? s ^ flip : s; }
+    double *slot(int s) const { return scal_slot(h, place(s)); }
+    Reduce reduce(int s) const { return reduce_into(h, place(s)); }
 };
 
 // Iterations between host convergence checks when the caller leaves it to the library.
@@ -126,7 +130,7 @@ int cg_step(const Ctx &c, int prec, SpinorFmt fx, void *x, void *r, void *pv, vo
                                     h->active, c.slot(RHO_NEW));
     COLA_TRY(normal(c, prec, ap, pv));
     COLA_HIP(h, launch_cg_xr(c.shape(), fx, fp, fx, fp, x, pv, r, ap, c.slot(RHO), c.slot(PI),
-                             h->active, reduce_into(h, RHO_NEW), c.st));
+                             h->active, c.reduce(RHO_NEW), c.st));
     return COLA_OK;
 }
 
@@ -179,12 +183,9 @@ bool finite_all(const double *v, int n) {
     return true;
 }
 
-// swap the RHO and RHO_NEW slots by copying (keeps slot numbering fixed); a kernel, so
-// that captured iteration blocks hold kernel nodes only
-int rotate_rho(const Ctx &c) {
-    COLA_HIP(c.h, launch_scalar_copy(c.slot(RHO), c.slot(RHO_NEW), c.R, c.st));
-    return COLA_OK;
-}
+// the new |r|^2 becomes the old one: the slots trade places (a copy in a launch of its own
+// took 4.5 us of a 16^3 x 32 iteration's 90)
+void rotate_rho(const Ctx &c) { c.flip ^= 1; }
 
 struct Outcome {
     int status = COLA_OK;
@@ -198,7 +199,7 @@ struct Outcome {
 
 // Small solves are bound by launch latency (a 16^3 x 32 CG iteration runs ~90 us of
 // kernels in ~165 us), so with COLA_GRAPHS=1 the n iterations between two convergence
-// checks -- (step, p update, rho rotation) x (n - 1), step -- are captured once as a HIP
+// checks -- (step, p update) x (n - 1), step -- are captured once as a HIP
 // graph and replayed (large solves check every iteration and launch directly).  Capture
 // needs every launch shape settled (the first block of a solve runs directly, which
 // tunes) and no per-launch timing.  Off by default: measured on 16^3 x 32 and 8^3 x 16,
@@ -220,7 +221,7 @@ int cg_block(const Ctx &c, int prec, SpinorFmt fx, void *x, void *r, void *pv, v
             if (k + 1 < n) {
                 COLA_HIP(h, launch_cg_p(cc.shape(), fx, fp, r, pv, cc.slot(RHO_NEW),
                                         cc.slot(RHO), h->active, cc.st));
-                COLA_TRY(rotate_rho(cc));
+                rotate_rho(cc);
             }
         }
         return COLA_OK;
@@ -233,8 +234,8 @@ int cg_block(const Ctx &c, int prec, SpinorFmt fx, void *x, void *r, void *pv, v
     // everything the captured launches hold: vectors, fields, operator, shape
     char key[512];
     const char *fuse = getenv("COLA_CG_FUSE");
-    snprintf(key, sizeof key, "%d %d %d %d %d %p %p %p %p %p %p %p %p %p %p %p %p %p %p %p %p %d %c",
-             prec, (int)fx, c.R, c.full, n, x, r, pv, ap, h->gauge[0], h->gauge[1], h->gauge[2],
+    snprintf(key, sizeof key, "%d %d %d %d %d %d %p %p %p %p %p %p %p %p %p %p %p %p %p %p %p %p %d %c",
+             prec, (int)fx, c.R, c.full, n, c.flip, x, r, pv, ap, h->gauge[0], h->gauge[1], h->gauge[2],
              h->gauge[3], h->fat[0], h->fat[1], h->fat[2], h->fat[3], h->clov32, h->clov64,
              h->clovinv32, h->clovinv64, h->flic ? 1 : 0, fuse ? fuse[0] : '-');
     hipGraphExec_t exec;
@@ -264,6 +265,7 @@ int cg_block(const Ctx &c, int prec, SpinorFmt fx, void *x, void *r, void *pv, v
     COLA_HIP(h, hipGraphLaunch(exec, h->gstream));
     COLA_HIP(h, hipEventRecord(h->gevent, h->gstream));
     COLA_HIP(h, hipStreamWaitEvent(c.st, h->gevent, 0));
+    c.flip ^= (n - 1) & 1;
     return COLA_OK;
 }
 
@@ -323,11 +325,10 @@ int solve_reliable(const Ctx &c, int sloppy_prec, const cola_cg_params_t &p, voi
         return COLA_OK;
     }
     COLA_TRY(write_active(c, act));
-    const Reduce red_rho = reduce_into(h, RHO);
+    const Reduce red_rho = c.reduce(RHO);
     if (!same) COLA_HIP(h, launch_convert(sh, fs, SpinorFmt::F64, rs, r64, nullptr, 0, &red_rho, c.st));
     else COLA_HIP(h, hipMemcpyAsync(c.slot(RHO), c.slot(TRUE_RES), sizeof(double) * c.R, hipMemcpyDeviceToDevice, c.st));
     COLA_HIP(h, launch_convert(sh, fs, fs, ps, rs, nullptr, 0, nullptr, c.st));
-    const Reduce red_new = reduce_into(h, RHO_NEW);
     int last_rel = 0;
     int it = 0;
     const bool graphs = graphs_wanted(c);
@@ -370,6 +371,7 @@ int solve_reliable(const Ctx &c, int sloppy_prec, const cola_cg_params_t &p, voi
                     stop = true;
                     o->final_tr = tr;  // x64 holds the whole solution (xs was folded in)
                 } else {
+                    const Reduce red_new = c.reduce(RHO_NEW);
                     if (!same)
                         COLA_HIP(h, launch_convert(sh, fs, SpinorFmt::F64, rs, r64, nullptr, 0,
                                                    &red_new, c.st));
@@ -382,7 +384,7 @@ int solve_reliable(const Ctx &c, int sloppy_prec, const cola_cg_params_t &p, voi
                         COLA_TRY(write_active(c, keep));
                         COLA_HIP(h, launch_cg_p(sh, fs, fs, rs, ps, c.slot(RHO_NEW), c.slot(RHO),
                                                 h->active, c.st));
-                        COLA_TRY(rotate_rho(c));
+                        rotate_rho(c);
                         COLA_TRY(write_active(c, act));
                         continue;
                     }
@@ -392,7 +394,7 @@ int solve_reliable(const Ctx &c, int sloppy_prec, const cola_cg_params_t &p, voi
         }
         if (stop) break;
         COLA_HIP(h, launch_cg_p(sh, fs, fs, rs, ps, c.slot(RHO_NEW), c.slot(RHO), h->active, c.st));
-        COLA_TRY(rotate_rho(c));
+        rotate_rho(c);
     }
     if (!same && o->status == COLA_OK) {
         // fold any remaining sloppy solution in (no-op after a final reliable update)
@@ -443,7 +445,7 @@ int inner_cg(const Ctx &c, int prec, SpinorFmt fx, void *x, void *r, void *pv, v
             COLA_TRY(write_active(c, act));
         }
         COLA_HIP(h, launch_cg_p(sh, fx, fp, r, pv, c.slot(RHO_NEW), c.slot(RHO), h->active, c.st));
-        COLA_TRY(rotate_rho(c));
+        rotate_rho(c);
     }
     *iters = it;
     return COLA_OK;
@@ -589,7 +591,7 @@ int solve_defect(const Ctx &c, int inner_prec, const cola_cg_params_t &p, void *
         void *pv, *ap;
         COLA_TRY(vec(c, "dp", fp, &pv));
         COLA_TRY(vec(c, "dap", fp, &ap));
-        const Reduce red_rho = reduce_into(h, RHO);
+        const Reduce red_rho = c.reduce(RHO);
         // Inner vectors: r = R / |R| (rho = |r|^2), p = r, x = 0.  Block CG keeps x and r in
         // FP32; the lockstep solver stores them like p, in the inner precision (FP16 rounds
         // them to about 5e-4 per update, far below the inner solve's 1e-2 reduction, and
