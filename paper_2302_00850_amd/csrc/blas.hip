@@ -115,32 +115,118 @@ struct XrFn {
     }
 };
 
-template <SpinorFmt FR, SpinorFmt FP>
-struct PFn {
+// x += alpha p, then p = r + beta p (either may be left out), FP16 storage
+struct XpFn {
+    void *x;
     const void *r;
     void *p;
-    size_t br, bp;
-    const double *rho_new, *rho;
+    size_t bb;
+    const double *rho_new, *rho, *pi;
     const int *active;
     int S, R;
     __device__ double operator()(const Loc &l) const {
-        using TP = typename SpinorT<FP>::real;
-        const double be = active[l.r] && rho[l.r] != 0.0 ? rho_new[l.r] / rho[l.r] : 0.0;
-        const auto Rv = view<FR>(r, br, l, S, R);
-        const auto P = view<FP>(p, bp, l, S, R);
-        cpx<typename SpinorT<FR>::real> rv[12];
-        cpx<TP> pv[12];
-        Rv.load(l.i, l.r, rv);
+        constexpr SpinorFmt F = SpinorFmt::F16;
+        const bool on = active[l.r];
+        const auto P = view<F>(p, bb, l, S, R);
+        cpx<float> pv[12], v[12];
         P.load(l.i, l.r, pv);
+        if (x) {
+            const double den = pi[l.r];
+            const float al = (float)(on && den != 0.0 ? rho[l.r] / den : 0.0);
+            const auto X = view<F>(x, bb, l, S, R);
+            X.load(l.i, l.r, v);
 #pragma unroll
-        for (int c = 0; c < 12; ++c) {
-            pv[c].x = (TP)rv[c].x + (TP)be * pv[c].x;
-            pv[c].y = (TP)rv[c].y + (TP)be * pv[c].y;
+            for (int c = 0; c < 12; ++c)
+                v[c] = {fma(al, pv[c].x, v[c].x), fma(al, pv[c].y, v[c].y)};
+            X.store(l.i, l.r, v);
         }
-        P.store(l.i, l.r, pv);
+        if (r) {
+            const float be = (float)(on && rho[l.r] != 0.0 ? rho_new[l.r] / rho[l.r] : 0.0);
+            view<F>(r, bb, l, S, R).load(l.i, l.r, v);
+#pragma unroll
+            for (int c = 0; c < 12; ++c) {
+                pv[c].x = v[c].x + be * pv[c].x;
+                pv[c].y = v[c].y + be * pv[c].y;
+            }
+            P.store(l.i, l.r, pv);
+        }
         return 0.0;
     }
 };
+
+// The same in FP64 or FP32 storage, where a field is a plain array of complex values with the
+// rhs innermost: one 16-byte element per lane and pass, four passes' loads in flight, the
+// first of them under way before the coefficients are known.  x, not used again before the
+// next update, passes by the caches.  Bound by memory (five fields, three of them read):
+// 24^3 x 48, 12 rhs in FP32, even sites: 366 us (5.2 TB/s), and the hop left without x and p
+// 716 -> 457 us, against 186 us for the update of p alone (a lane per site and rhs walking
+// twelve arrays at once).  One rhs at 16^3 x 32: 9.3 against
+// 6.0 us, the hop 13.6 -> 11.2 us.
+constexpr size_t kXpBlocks = 8192;
+
+template <typename T>
+__global__ void __launch_bounds__(256)
+    cg_xp_kernel(cpx<T> *x, const cpx<T> *r, cpx<T> *p, size_t n, int R, const double *rho_new,
+                 const double *rho, const double *pi, const int *active) {
+    constexpr int N = 16 / sizeof(cpx<T>);  // complex values per element
+    constexpr int U = 4;
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    struct alignas(16) E {
+        cpx<T> v[N];
+    };
+    __shared__ T al[kRedMaxWidth], be[kRedMaxWidth];
+    f4 *const X = (f4 *)x;
+    E *const P = (E *)p;
+    const E *const Rv = (const E *)r;
+    const size_t ne = n / N, step = (size_t)gridDim.x * 256;
+    size_t e0 = (size_t)blockIdx.x * 256 + threadIdx.x;
+    f4 xv[U];
+    E rv[U], pv[U];
+    auto fetch = [&] {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const size_t e = e0 + u * step;
+            if (e < ne) {
+                pv[u] = P[e];
+                if (x) xv[u] = __builtin_nontemporal_load(X + e);
+                if (r) rv[u] = Rv[e];
+            }
+        }
+    };
+    fetch();
+    if ((int)threadIdx.x < R) {
+        const int q = (int)threadIdx.x;
+        const bool on = active[q];
+        al[q] = (T)(x && on && pi[q] != 0.0 ? rho[q] / pi[q] : 0.0);
+        be[q] = (T)(r && on && rho[q] != 0.0 ? rho_new[q] / rho[q] : 0.0);
+    }
+    __syncthreads();
+    while (e0 < ne) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const size_t e = e0 + u * step;
+            if (e >= ne) break;
+            uint32_t q = R == 1 ? 0u : (uint32_t)(e * N % (size_t)R);
+            E xe;
+            __builtin_memcpy(&xe, &xv[u], 16);
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                cpx<T> &a = xe.v[k], &b = pv[u].v[k];
+                const cpx<T> c = rv[u].v[k];
+                if (x) a = {fma(al[q], b.x, a.x), fma(al[q], b.y, a.y)};
+                if (r) b = {fma(be[q], b.x, c.x), fma(be[q], b.y, c.y)};
+                if (R != 1) q = q + 1 == (uint32_t)R ? 0u : q + 1;
+            }
+            if (x) {
+                __builtin_memcpy(&xv[u], &xe, 16);
+                __builtin_nontemporal_store(xv[u], X + e);
+            }
+            if (r) P[e] = pv[u];
+        }
+        e0 += U * step;
+        fetch();
+    }
+}
 
 template <SpinorFmt F>
 struct NormFn {
@@ -190,6 +276,9 @@ struct AccumFn {
     const double *scale;
     int zero;
     int S, R;
+    const void *p;  // with p: s + alpha p in place of s
+    const double *rho, *pi;
+    const int *active;
     __device__ double operator()(const Loc &l) const {
         using TS = typename SpinorT<FS>::real;
         const auto Sv = view<FS>(s, bs, l, S, R);
@@ -197,6 +286,14 @@ struct AccumFn {
         cpx<TS> a[12];
         cpx<double> o[12];
         Sv.load(l.i, l.r, a);
+        if (p) {
+            const double den = pi[l.r];
+            const TS al = (TS)(active[l.r] && den != 0.0 ? rho[l.r] / den : 0.0);
+            cpx<TS> pv[12];
+            view<FS>(p, bs, l, S, R).load(l.i, l.r, pv);
+#pragma unroll
+            for (int c = 0; c < 12; ++c) a[c] = {fma(al, pv[c].x, a[c].x), fma(al, pv[c].y, a[c].y)};
+        }
         D.load(l.i, l.r, o);
         const double f = scale ? scale[l.r] : 1.0;
 #pragma unroll
@@ -591,22 +688,26 @@ hipError_t launch_cg_xr(const BlasShape &b, SpinorFmt fx, SpinorFmt fp, SpinorFm
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_cg_p(const BlasShape &b, SpinorFmt fr, SpinorFmt fp, const void *r, void *p,
-                       const double *rho_new, const double *rho, const int *active,
-                       hipStream_t st) {
-    if (fr == fp) {
-        DISPATCH_FMT(fr, F,
-                     PFn<F, F> fn{r, p, block_bytes(F, b.S, b.R), block_bytes(F, b.S, b.R),
-                                  rho_new, rho, active, b.S, b.R};
-                     return run(fn, b, nullptr, st));
-    }
-    if (fr == SpinorFmt::F32 && fp == SpinorFmt::F16) {
-        PFn<SpinorFmt::F32, SpinorFmt::F16> fn{r, p, block_bytes(fr, b.S, b.R),
-                                               block_bytes(fp, b.S, b.R), rho_new, rho, active,
-                                               b.S, b.R};
+hipError_t launch_cg_xp(const BlasShape &b, SpinorFmt f, void *x, const void *r, void *p,
+                        const double *rho_new, const double *rho, const double *pi,
+                        const int *active, hipStream_t st) {
+    const size_t bb = block_bytes(f, b.S, b.R);
+    if (f == SpinorFmt::F16) {
+        XpFn fn{x, r, p, bb, rho_new, rho, pi, active, b.S, b.R};
         return run(fn, b, nullptr, st);
     }
-    return hipErrorInvalidValue;
+    // S is a multiple of 64 sites, so a field is whole elements
+    const size_t bytes = bb * b.nblk, blocks = (bytes / 16 + 255) / 256;
+    const dim3 grid((unsigned)(blocks <= kXpBlocks ? blocks : kXpBlocks));
+    if (f == SpinorFmt::F64)
+        hipLaunchKernelGGL(cg_xp_kernel<double>, grid, dim3(256), 0, st, (cpx<double> *)x,
+                           (const cpx<double> *)r, (cpx<double> *)p, bytes / 16, b.R, rho_new, rho,
+                           pi, active);
+    else
+        hipLaunchKernelGGL(cg_xp_kernel<float>, grid, dim3(256), 0, st, (cpx<float> *)x,
+                           (const cpx<float> *)r, (cpx<float> *)p, bytes / 8, b.R, rho_new, rho,
+                           pi, active);
+    return hipGetLastError();
 }
 
 hipError_t launch_norm2(const BlasShape &b, SpinorFmt f, const void *v, const Reduce &red,
@@ -627,10 +728,12 @@ hipError_t launch_convert(const BlasShape &b, SpinorFmt fd, SpinorFmt fs, void *
 }
 
 hipError_t launch_accum(const BlasShape &b, SpinorFmt fs, void *dst, void *src, const double *s,
-                        int zero_src, hipStream_t st) {
+                        int zero_src, hipStream_t st, const void *p, const double *rho,
+                        const double *pi, const int *active) {
     DISPATCH_FMT(fs, FS,
                  AccumFn<FS> fn{dst, src, block_bytes(SpinorFmt::F64, b.S, b.R),
-                                block_bytes(FS, b.S, b.R), s, zero_src, b.S, b.R};
+                                block_bytes(FS, b.S, b.R), s, zero_src, b.S, b.R, p, rho, pi,
+                                active};
                  return run(fn, b, nullptr, st));
     return hipErrorInvalidValue;
 }

@@ -94,8 +94,8 @@ enum Epilogue : int {
     EPI_XPAY_CLOV = 4,   // out = C (x + a D in)
     // CG step fused into the last hop of the normal operator: with o = x + a D in
     // (EPI_XPAY_CG) or C x + a D in (EPI_CLOV_XPAY_CG), and per rhs
-    // alpha = active ? rho / pi : 0:  cg_x += alpha cg_p,  cg_r -= alpha o;
-    // o itself is not stored and the fused norm is |cg_r|^2
+    // alpha = active ? rho / pi : 0:  cg_r -= alpha o; o itself is not stored and the fused
+    // norm is |cg_r|^2
     EPI_XPAY_CG = 5,
     EPI_CLOV_XPAY_CG = 6
 };
@@ -144,10 +144,9 @@ struct HopArgs {
     // host only: when set, the launcher stores the kernel's resident blocks per CU here
     // instead of launching
     int *occupancy;
-    // CG epilogues: the solver's vectors (parity `parity` blocks of the launch format)
-    // and its per-rhs scalars; cg_x null: only r is updated (cg_p is not read)
-    void *cg_x, *cg_r;
-    const void *cg_p;
+    // CG epilogues: the solver's residual (parity `parity` block of the launch format) and
+    // its per-rhs scalars
+    void *cg_r;
     const double *cg_rho, *cg_pi;
     const int *cg_active;
 };

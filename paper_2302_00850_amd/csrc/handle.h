@@ -138,9 +138,8 @@ struct HopCall {
     double a = 0;
     const void *clov = nullptr;
     double *norm_result = nullptr;  // per-rhs |out|^2 (fused)
-    // EPI_XPAY_CG / EPI_CLOV_XPAY_CG: the CG vectors and per-rhs scalars
-    void *cg_x = nullptr, *cg_r = nullptr;
-    const void *cg_p = nullptr;
+    // EPI_XPAY_CG / EPI_CLOV_XPAY_CG: the CG residual and per-rhs scalars
+    void *cg_r = nullptr;
     const double *cg_rho = nullptr, *cg_pi = nullptr;
     const int *cg_active = nullptr;
     // fixed: no launch-shape tuning, no timing events, no occupancy queries (the
@@ -153,11 +152,11 @@ int hop(cola_handle_t *h, const HopCall &c, int prec, int nrhs, hipStream_t st);
 // The handle's links from U, canonical or (packed) in the packed 18-real format.
 int set_links(cola_handle_t *h, const void *U, bool packed, hipStream_t st);
 
-// One CG step on the even-odd normal system S^dag S, with the update fused into the
+// One CG step on the even-odd normal system S^dag S, with the update of r fused into the
 // last hop: pi = |S p|^2, then with alpha = rho / pi per active rhs,
-//   x += alpha p,  r -= alpha S^dag S p,  rho_new = |r|^2.
-// x, r, p: even-parity blocks in the storage of prec (x null: no x update).
-int schur_normal_cg_step(cola_handle_t *h, int prec, int nrhs, hipStream_t st, void *x, void *r,
+//   r -= alpha S^dag S p,  rho_new = |r|^2
+// (x += alpha p is left to the update of p).  r, p: even-parity blocks in the storage of prec.
+int schur_normal_cg_step(cola_handle_t *h, int prec, int nrhs, hipStream_t st, void *r,
                          const void *p, const double *rho, double *pi, const int *active,
                          double *rho_new);
 

@@ -173,15 +173,11 @@ __global__ void __launch_bounds__(8 * kDirsSites) hop_dirs_kernel(const HopArgs 
             v[c] = {e.x, e.y};
         }
     };
-    C xv[3], cx[3], cp[3], cr[3];
+    C xv[3], cr[3];
     T al = (T)0;
     if (d < 4 && valid) {
         if constexpr (XIN) own(a.x, xv);
         if constexpr (CG) {
-            if (a.cg_x) {
-                own(a.cg_x, cx);
-                own(a.cg_p, cp);
-            }
             own(a.cg_r, cr);
             const double den = a.cg_pi[j];
             al = (T)(a.cg_active[j] && den != 0.0 ? a.cg_rho[j] / den : 0.0);
@@ -240,12 +236,6 @@ __global__ void __launch_bounds__(8 * kDirsSites) hop_dirs_kernel(const HopArgs 
             for (int c = 0; c < 3; ++c) bstore<E>(w.next(), off, E{v[c].x, v[c].y});
         };
         if constexpr (CG) {
-            if (a.cg_x) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    cx[c] = {fma(al, cp[c].x, cx[c].x), fma(al, cp[c].y, cx[c].y)};
-                put(a.cg_x, cx);
-            }
 #pragma unroll
             for (int c = 0; c < 3; ++c)
                 o[c] = {fma(-al, o[c].x, cr[c].x), fma(-al, o[c].y, cr[c].y)};

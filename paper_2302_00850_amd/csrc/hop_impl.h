@@ -17,7 +17,7 @@
 //   EPI_CLOV       out = C (D in)
 //   EPI_CLOV_XPAY  out = C x + a D in
 //   EPI_XPAY_CLOV  out = C (x + a D in)
-//   EPI_XPAY_CG, EPI_CLOV_XPAY_CG: the CG update of x and r with o = x + a D in
+//   EPI_XPAY_CG, EPI_CLOV_XPAY_CG: the CG update of r with o = x + a D in
 //                  (or C x + a D in) in place of storing o
 // and |out|^2 per rhs can be accumulated: per-block partials, summed in block
 // order by a reduce_partials launch that follows.
@@ -279,7 +279,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK ? 3
         return SpinorBlock<SF, true>((const char *)(base ? base : a.out) + o, g.S, a.nrhs);
     };
     const auto in = view(a.in, no), out = view(a.out, po), xin = view(a.x, po);
-    const auto cgx = view(a.cg_x, po), cgr = view(a.cg_r, po), cgp = view(a.cg_p, po);
+    const auto cgr = view(a.cg_r, po);
     // WALK: the input sites of the lane's index at t - 1, t, t + 1
     Fetched<SF, 1> rp, rc, rn;
     for (int tt = 0; tt < a.tchunk; ++tt) {
@@ -452,18 +452,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK ? 3
                     clover_apply<CR, T>(a.clov, g.S, p, i, xv, o);
             }
             if constexpr (CG) {
-                // x += alpha p, r -= alpha o; o becomes the stored r (for the norm)
+                // r -= alpha o; o becomes the stored r (for the norm)
                 const double den = a.cg_pi[rr];
                 const T al = (T)(a.cg_active[rr] && den != 0.0 ? a.cg_rho[rr] / den : 0.0);
-                if (a.cg_x) {
-                    C xv[12], pv[12];
-                    cgx.load(i, rr, xv);
-                    cgp.load(i, rr, pv);
-#pragma unroll
-                    for (int c = 0; c < 12; ++c)
-                        xv[c] = {fma(al, pv[c].x, xv[c].x), fma(al, pv[c].y, xv[c].y)};
-                    cgx.store(i, rr, xv);
-                }
                 C rv[12];
                 cgr.load(i, rr, rv);
 #pragma unroll

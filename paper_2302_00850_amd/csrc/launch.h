@@ -86,10 +86,12 @@ hipError_t launch_scalar_add(double *a, const double *b, int n, hipStream_t st);
 hipError_t launch_cg_xr(const BlasShape &b, SpinorFmt fx, SpinorFmt fp, SpinorFmt fr,
                         SpinorFmt fap, void *x, const void *p, void *r, const void *ap,
                         const double *rho, const double *pi, const int *active, const Reduce &red, hipStream_t st);
-// p = r + beta p ; beta_q = active_q ? rho_new_q / rho_q : 0
-hipError_t launch_cg_p(const BlasShape &b, SpinorFmt fr, SpinorFmt fp, const void *r, void *p,
-                       const double *rho_new, const double *rho, const int *active,
-                       hipStream_t st);
+// The vector updates that follow a CG step with r updated in the last hop, all fields in
+// format f: x += alpha p (x null: not done; alpha_q = active_q ? rho_q / pi_q : 0), then
+// p = r + beta p (r null: not done; beta_q = active_q ? rho_new_q / rho_q : 0)
+hipError_t launch_cg_xp(const BlasShape &b, SpinorFmt f, void *x, const void *r, void *p,
+                        const double *rho_new, const double *rho, const double *pi,
+                        const int *active, hipStream_t st);
 // result = |v|^2 per rhs
 hipError_t launch_norm2(const BlasShape &b, SpinorFmt f, const void *v, const Reduce &red,
                         hipStream_t st);
@@ -97,9 +99,12 @@ hipError_t launch_norm2(const BlasShape &b, SpinorFmt f, const void *v, const Re
 hipError_t launch_convert(const BlasShape &b, SpinorFmt fd, SpinorFmt fs, void *dst,
                           const void *src, const double *s, int inv_scale, const Reduce *red,
                           hipStream_t st);
-// dst(FP64) += s_q * src; zero_src: src = 0 afterwards
+// dst(FP64) += s_q * src; zero_src: src = 0 afterwards.  With p, src + alpha p (alpha as in
+// launch_cg_xp) takes src's place
 hipError_t launch_accum(const BlasShape &b, SpinorFmt fs, void *dst, void *src, const double *s,
-                        int zero_src, hipStream_t st);
+                        int zero_src, hipStream_t st, const void *p = nullptr,
+                        const double *rho = nullptr, const double *pi = nullptr,
+                        const int *active = nullptr);
 // r = b - ax (all FP64), result = |r|^2
 hipError_t launch_residual(const BlasShape &b, void *r, const void *bb, const void *ax,
                            const Reduce &red, hipStream_t st);

@@ -114,9 +114,9 @@ void hop_work(const cola_handle_t *h, int prec, int nrhs, int epi, double *bytes
         f += 48.0 * nrhs;
     }
     if (cg) {
-        // reads x, p, r and writes x, r in place of writing the result
-        b += 4.0 * nrhs * spinor_site_bytes(sf);
-        f += 96.0 * nrhs;
+        // reads and writes r in place of writing the result
+        b += 1.0 * nrhs * spinor_site_bytes(sf);
+        f += 48.0 * nrhs;
     }
     if (epi == EPI_CLOV || epi == EPI_CLOV_XPAY || epi == EPI_XPAY_CLOV ||
         epi == EPI_CLOV_XPAY_CG) {
@@ -382,9 +382,7 @@ int fill_and_launch(cola_handle_t *h, const HopCall &c, int prec, int nrhs, cons
     a.in = c.in;
     a.out = c.out;
     a.x = c.x;
-    a.cg_x = c.cg_x;
     a.cg_r = c.cg_r;
-    a.cg_p = c.cg_p;
     a.cg_rho = c.cg_rho;
     a.cg_pi = c.cg_pi;
     a.cg_active = c.cg_active;
@@ -763,7 +761,7 @@ int apply_op(cola_handle_t *h, void *out, const void *in, int op, int parity, in
     }
 }
 
-int schur_normal_cg_step(cola_handle_t *h, int prec, int nrhs, hipStream_t st, void *x, void *r,
+int schur_normal_cg_step(cola_handle_t *h, int prec, int nrhs, hipStream_t st, void *r,
                          const void *p, const double *rho, double *pi, const int *active,
                          double *rho_new) {
     const SpinorFmt sf = spinor_fmt(prec);
@@ -790,9 +788,7 @@ int schur_normal_cg_step(cola_handle_t *h, int prec, int nrhs, hipStream_t st, v
     c2.a = -h->kappa * h->kappa;
     c2.clov = f64 ? h->clov64 : h->clov32;
     c2.norm_result = rho_new;
-    c2.cg_x = x;
     c2.cg_r = r;
-    c2.cg_p = p;
     c2.cg_rho = rho;
     c2.cg_pi = pi;
     c2.cg_active = active;

@@ -53,6 +53,8 @@ struct Ctx {
     BlasShape shape() const { return blas_shape(h->g, R, nblk()); }
     // RHO and RHO_NEW trade places each iteration (rotate_rho)
     mutable int flip = 0;
+    // x += alpha p of the last step is still to be done (with the update of p, or finish_x)
+    mutable bool x_due = false;
     int place(int s) const { return s <= RHO_NEW ? s ^ flip : s; }
     double *slot(int s) const { return scal_slot(h, place(s)); }
     Reduce reduce(int s) const { return reduce_into(h, place(s)); }
@@ -88,12 +90,12 @@ int normal(const Ctx &c, int prec, void *out, const void *in) {
     return apply_op(h, out, t, COLA_OP_MDAG, -1, prec, c.R, c.st);
 }
 
-// One CG step: Ap = A p, pi = <p, Ap>, then x += alpha p, r -= alpha Ap and
-// rho_new = |r|^2.  With x, r and p in the operator's storage the update runs inside the
-// last hop (Ap is never stored): the last hop of S^dag S on the even-odd system, the hop of
-// M^dag on the full lattice; COLA_CG_FUSE=0 selects the separate update
-// kernel.
-int full_normal_cg_step(const Ctx &c, int prec, void *x, void *r, void *pv, const double *rho,
+// One CG step: Ap = A p, pi = <p, Ap>, then r -= alpha Ap and rho_new = |r|^2, and
+// x += alpha p.  With x, r and p in the operator's storage r is updated inside the last hop
+// (Ap is never stored; the last hop of S^dag S on the even-odd system, the hop of M^dag on
+// the full lattice) and x together with p, which is then read once for both;
+// COLA_CG_FUSE=0 selects a separate update kernel of x and r.
+int full_normal_cg_step(const Ctx &c, int prec, void *r, void *pv, const double *rho,
                         double *rho_new) {
     cola_handle_t *h = c.h;
     const SpinorFmt sf = spinor_fmt(prec);
@@ -110,9 +112,7 @@ int full_normal_cg_step(const Ctx &c, int prec, void *x, void *r, void *pv, cons
     hc.a = -h->kappa;
     hc.clov = sf == SpinorFmt::F64 ? h->clov64 : h->clov32;
     hc.norm_result = rho_new;
-    hc.cg_x = x;
     hc.cg_r = r;
-    hc.cg_p = pv;
     hc.cg_rho = rho;
     hc.cg_pi = c.slot(PI);
     hc.cg_active = h->active;
@@ -124,10 +124,11 @@ int cg_step(const Ctx &c, int prec, SpinorFmt fx, void *x, void *r, void *pv, vo
     const SpinorFmt fp = spinor_fmt(prec);
     const char *env = getenv("COLA_CG_FUSE");
     const bool fuse = fx == fp && !(env && env[0] == '0');
-    if (fuse && c.full) return full_normal_cg_step(c, prec, x, r, pv, c.slot(RHO), c.slot(RHO_NEW));
+    c.x_due = fuse;
+    if (fuse && c.full) return full_normal_cg_step(c, prec, r, pv, c.slot(RHO), c.slot(RHO_NEW));
     if (fuse)
-        return schur_normal_cg_step(h, prec, c.R, c.st, x, r, pv, c.slot(RHO), c.slot(PI),
-                                    h->active, c.slot(RHO_NEW));
+        return schur_normal_cg_step(h, prec, c.R, c.st, r, pv, c.slot(RHO), c.slot(PI), h->active,
+                                    c.slot(RHO_NEW));
     COLA_TRY(normal(c, prec, ap, pv));
     COLA_HIP(h, launch_cg_xr(c.shape(), fx, fp, fx, fp, x, pv, r, ap, c.slot(RHO), c.slot(PI),
                              h->active, c.reduce(RHO_NEW), c.st));
@@ -187,6 +188,32 @@ bool finite_all(const double *v, int n) {
 // took 4.5 us of a 16^3 x 32 iteration's 90)
 void rotate_rho(const Ctx &c) { c.flip ^= 1; }
 
+// p = r + beta p, with the x update that is due; the new |r|^2 becomes the old one
+int update_p(const Ctx &c, SpinorFmt f, void *x, const void *r, void *p) {
+    COLA_HIP(c.h, launch_cg_xp(c.shape(), f, c.x_due ? x : nullptr, r, p, c.slot(RHO_NEW),
+                               c.slot(RHO), c.slot(PI), c.h->active, c.st));
+    c.x_due = false;
+    rotate_rho(c);
+    return COLA_OK;
+}
+
+// The x update that is due, without p: before x is read and before the active columns change.
+int finish_x(const Ctx &c, SpinorFmt f, void *x, void *p) {
+    if (c.x_due)
+        COLA_HIP(c.h, launch_cg_xp(c.shape(), f, x, nullptr, p, c.slot(RHO_NEW), c.slot(RHO),
+                                   c.slot(PI), c.h->active, c.st));
+    c.x_due = false;
+    return COLA_OK;
+}
+
+// x64 += x (the sloppy solution, with the x update that is due), x = 0
+int fold_x(const Ctx &c, SpinorFmt f, void *x64, void *x, const void *p) {
+    COLA_HIP(c.h, launch_accum(c.shape(), f, x64, x, nullptr, 1, c.st, c.x_due ? p : nullptr,
+                               c.slot(RHO), c.slot(PI), c.h->active));
+    c.x_due = false;
+    return COLA_OK;
+}
+
 struct Outcome {
     int status = COLA_OK;
     int iterations = 0;
@@ -214,15 +241,10 @@ bool graphs_wanted(const Ctx &c) {
 int cg_block(const Ctx &c, int prec, SpinorFmt fx, void *x, void *r, void *pv, void *ap, int n,
              bool graph) {
     cola_handle_t *h = c.h;
-    const SpinorFmt fp = spinor_fmt(prec);
     auto body = [&](const Ctx &cc) -> int {
         for (int k = 0; k < n; ++k) {
             COLA_TRY(cg_step(cc, prec, fx, x, r, pv, ap));
-            if (k + 1 < n) {
-                COLA_HIP(h, launch_cg_p(cc.shape(), fx, fp, r, pv, cc.slot(RHO_NEW),
-                                        cc.slot(RHO), h->active, cc.st));
-                rotate_rho(cc);
-            }
+            if (k + 1 < n) COLA_TRY(update_p(cc, fx, x, r, pv));
         }
         return COLA_OK;
     };
@@ -266,6 +288,7 @@ int cg_block(const Ctx &c, int prec, SpinorFmt fx, void *x, void *r, void *pv, v
     COLA_HIP(h, hipEventRecord(h->gevent, h->gstream));
     COLA_HIP(h, hipStreamWaitEvent(c.st, h->gevent, 0));
     c.flip ^= (n - 1) & 1;
+    c.x_due = !(fuse && fuse[0] == '0');
     return COLA_OK;
 }
 
@@ -350,9 +373,10 @@ int solve_reliable(const Ctx &c, int sloppy_prec, const cola_cg_params_t &p, voi
                 dropped |= act[q] && rho[q] < delta2 * ref[q];
             }
             if (iter_conv || dropped || it - last_rel >= interval || it == p.max_iter) {
-                if (!same) {
-                    COLA_HIP(h, launch_accum(sh, fs, x64, xs, nullptr, 1, c.st));
-                }
+                if (same)
+                    COLA_TRY(finish_x(c, fs, xs, ps));
+                else
+                    COLA_TRY(fold_x(c, fs, x64, xs, ps));
                 COLA_TRY(true_residual(c, r64, b64, x64, TRUE_RES));
                 COLA_TRY(read_slot(c, TRUE_RES, tr.data()));
                 ++o->reliable;
@@ -382,9 +406,7 @@ int solve_reliable(const Ctx &c, int sloppy_prec, const cola_cg_params_t &p, voi
                     if (restart) {
                         // beta = 0 for the restarted columns: p = r
                         COLA_TRY(write_active(c, keep));
-                        COLA_HIP(h, launch_cg_p(sh, fs, fs, rs, ps, c.slot(RHO_NEW), c.slot(RHO),
-                                                h->active, c.st));
-                        rotate_rho(c);
+                        COLA_TRY(update_p(c, fs, xs, rs, ps));
                         COLA_TRY(write_active(c, act));
                         continue;
                     }
@@ -393,13 +415,15 @@ int solve_reliable(const Ctx &c, int sloppy_prec, const cola_cg_params_t &p, voi
             }
         }
         if (stop) break;
-        COLA_HIP(h, launch_cg_p(sh, fs, fs, rs, ps, c.slot(RHO_NEW), c.slot(RHO), h->active, c.st));
-        rotate_rho(c);
+        COLA_TRY(update_p(c, fs, xs, rs, ps));
     }
-    if (!same && o->status == COLA_OK) {
+    if (same) {
+        COLA_TRY(finish_x(c, fs, xs, ps));
+    } else if (o->status == COLA_OK) {
         // fold any remaining sloppy solution in (no-op after a final reliable update)
-        COLA_HIP(h, launch_accum(sh, fs, x64, xs, nullptr, 1, c.st));
+        COLA_TRY(fold_x(c, fs, x64, xs, ps));
     }
+    c.x_due = false;
     o->iterations += it;
     if (o->status == COLA_OK && it >= p.max_iter) {
         COLA_TRY(true_residual(c, r64, b64, x64, TRUE_RES));
@@ -413,14 +437,12 @@ int solve_reliable(const Ctx &c, int sloppy_prec, const cola_cg_params_t &p, voi
 
 // ---------------------------------------------------------------- defect correction
 
-// CG iterations on the normal system in precision prec (p, Ap in that storage; x and r
-// in storage fx, FP32 arithmetic throughout).
-int inner_cg(const Ctx &c, int prec, SpinorFmt fx, void *x, void *r, void *pv, void *ap,
+// CG iterations on the normal system in precision prec (all vectors in that storage, FP32
+// arithmetic throughout).
+int inner_cg(const Ctx &c, int prec, void *x, void *r, void *pv, void *ap,
              const std::vector<double> &inner_tol2, int max_it, std::vector<int> act, int check,
              int *iters, int *status) {
-    cola_handle_t *h = c.h;
-    const BlasShape sh = c.shape();
-    const SpinorFmt fp = spinor_fmt(prec);
+    const SpinorFmt f = spinor_fmt(prec);
     COLA_TRY(write_active(c, act));
     std::vector<double> rho(c.R);
     int it = 0;
@@ -428,7 +450,7 @@ int inner_cg(const Ctx &c, int prec, SpinorFmt fx, void *x, void *r, void *pv, v
     while (it < max_it) {
         // the iterations up to the next check
         const int n = std::min(check - it % check, max_it - it);
-        COLA_TRY(cg_block(c, prec, fx, x, r, pv, ap, n, graphs && it > 0));
+        COLA_TRY(cg_block(c, prec, f, x, r, pv, ap, n, graphs && it > 0));
         it += n;
         if (it % check == 0) {
             COLA_TRY(read_slot(c, RHO_NEW, rho.data()));
@@ -436,17 +458,23 @@ int inner_cg(const Ctx &c, int prec, SpinorFmt fx, void *x, void *r, void *pv, v
                 *status = COLA_BREAKDOWN;
                 break;
             }
-            bool any = false;
+            bool any = false, change = false;
             for (int q = 0; q < c.R; ++q) {
-                if (act[q] && rho[q] <= inner_tol2[q]) act[q] = 0;
+                if (act[q] && rho[q] <= inner_tol2[q]) {
+                    act[q] = 0;
+                    change = true;
+                }
                 any |= act[q] != 0;
             }
             if (!any) break;
-            COLA_TRY(write_active(c, act));
+            if (change) {
+                COLA_TRY(finish_x(c, f, x, pv));
+                COLA_TRY(write_active(c, act));
+            }
         }
-        COLA_HIP(h, launch_cg_p(sh, fx, fp, r, pv, c.slot(RHO_NEW), c.slot(RHO), h->active, c.st));
-        rotate_rho(c);
+        COLA_TRY(update_p(c, f, x, r, pv));
     }
+    COLA_TRY(finish_x(c, f, x, pv));
     *iters = it;
     return COLA_OK;
 }
@@ -611,8 +639,8 @@ int solve_defect(const Ctx &c, int inner_prec, const cola_cg_params_t &p, void *
             COLA_TRY(inner_block_cg(c, prec, x32, r32, itol2, p.max_iter - o->iterations, act,
                                     check, &its, &st));
         else
-            COLA_TRY(inner_cg(c, prec, fxr, xs, rs, pv, ap, itol2, p.max_iter - o->iterations,
-                              act, check, &its, &st));
+            COLA_TRY(inner_cg(c, prec, xs, rs, pv, ap, itol2, p.max_iter - o->iterations, act,
+                              check, &its, &st));
         o->iterations += its;
         ++o->outer;
         if (st != COLA_OK) {
@@ -795,7 +823,7 @@ int cg_solve_impl(cola_handle_t *h, void *x, const void *b, int nrhs, const cola
 //   x_q += alpha zeta_q'/zeta_q p_q ;  p_q = zeta_q' r' + beta (zeta_q'/zeta_q)^2 p_q
 // (zeta = zeta^old = 1, alpha^old = 1, beta^old = 0, p_q = b at the start).  Each shift's x
 // and p are one-rhs fields; the scalar recursion runs on the device.  The base CG's own x is
-// not needed, so its last hop updates r only.  A shift stops once zeta_q^2 |r|^2 <= tol^2
+// not needed and not formed.  A shift stops once zeta_q^2 |r|^2 <= tol^2
 // |b|^2; its true residual is then checked against twice that.
 int cg_multishift_impl(cola_handle_t *h, void *x, const void *b, int nshift, const double *sigma,
                        const cola_cg_params_t *p, cola_cg_result_t *res, hipStream_t st) {
@@ -849,10 +877,10 @@ int cg_multishift_impl(cola_handle_t *h, void *x, const void *b, int nshift, con
             break;
         }
         if (full)
-            COLA_TRY(full_normal_cg_step(c, COLA_FP64, nullptr, r64, p64, rho, rho_new));
+            COLA_TRY(full_normal_cg_step(c, COLA_FP64, r64, p64, rho, rho_new));
         else
-            COLA_TRY(schur_normal_cg_step(h, COLA_FP64, 1, st, nullptr, r64, p64, rho,
-                                          c.slot(PI), h->active, rho_new));
+            COLA_TRY(schur_normal_cg_step(h, COLA_FP64, 1, st, r64, p64, rho, c.slot(PI),
+                                          h->active, rho_new));
         COLA_HIP(h, launch_ms_advance(state, rho_new, c.slot(PI), st));
         COLA_HIP(h, launch_ms_update(xs, ps, r64, p64, &state->coef, nshift, rho_new, rho, n, st));
         std::swap(rho, rho_new);
