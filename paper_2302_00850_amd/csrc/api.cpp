@@ -276,8 +276,6 @@ int cola_pack_spinor(cola_handle_t *h, void *dst, const void *src, int prec, int
     if (parity < -1 || parity > 1) return set_error(h, COLA_EINVAL, "parity must be -1, 0 or 1");
     COLA_TRY(check_rhs(h, nrhs));
     hipStream_t st = as_stream(stream);
-    // clear the whole destination so padding sites are zero
-    COLA_HIP(h, hipMemsetAsync(dst, 0, cola_field_bytes(h, prec, nrhs, parity), st));
     COLA_HIP(h, launch_pack_spinor(h->g, spinor_fmt(prec), dst, src, nrhs, parity, st));
     return COLA_OK;
 }

@@ -158,7 +158,7 @@ struct XpFn {
 // rhs innermost: one 16-byte element per lane and pass, four passes' loads in flight, the
 // first of them under way before the coefficients are known.  x, not used again before the
 // next update, passes by the caches.  Bound by memory (five fields, three of them read):
-// 24^3 x 48, 12 rhs in FP32, even sites: 366 us (5.2 TB/s), and the hop left without x and p
+// 24^3 x 48, 12 rhs in FP32, even sites: 306 us (6.2 TB/s), and the hop left without x and p
 // 716 -> 457 us, against 186 us for the update of p alone (a lane per site and rhs walking
 // twelve arrays at once).  One rhs at 16^3 x 32: 9.3 against
 // 6.0 us, the hop 13.6 -> 11.2 us.
