@@ -164,10 +164,10 @@ struct XpFn {
 // 6.0 us, the hop 13.6 -> 11.2 us.
 constexpr size_t kXpBlocks = 8192;
 
-template <typename T>
+template <typename T, bool PARTS>
 __global__ void __launch_bounds__(256)
-    cg_xp_kernel(cpx<T> *x, const cpx<T> *r, cpx<T> *p, size_t n, int R, const double *rho_new,
-                 const double *rho, const double *pi, const int *active) {
+    cg_xp_kernel(cpx<T> *x, const cpx<T> *r, cpx<T> *p, size_t n, int R, const Sum rho_new,
+                 const double *rho, const Sum pi, const int *active, double *rho_out) {
     constexpr int N = 16 / sizeof(cpx<T>);  // complex values per element
     constexpr int U = 4;
     typedef float f4 __attribute__((ext_vector_type(4)));
@@ -194,11 +194,32 @@ __global__ void __launch_bounds__(256)
         }
     };
     fetch();
+    __shared__ double sums[2][4];
+    const Sum in[2] = {rho_new, pi};
+    if constexpr (PARTS) {
+        double terms[2][8];
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (in[k].n) partial_terms(in[k].v, in[k].n, (int)threadIdx.x, terms[k]);
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (in[k].n) {
+                const double s = partial_wave(terms[k]);
+                if ((threadIdx.x & 63u) == 0) sums[k][threadIdx.x >> 6] = s;
+            }
+        __syncthreads();
+    }
     if ((int)threadIdx.x < R) {
         const int q = (int)threadIdx.x;
         const bool on = active[q];
-        al[q] = (T)(x && on && pi[q] != 0.0 ? rho[q] / pi[q] : 0.0);
-        be[q] = (T)(r && on && rho[q] != 0.0 ? rho_new[q] / rho[q] : 0.0);
+        double v[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            v[k] = PARTS && in[k].n ? ((sums[k][0] + sums[k][1]) + sums[k][2]) + sums[k][3]
+                                    : in[k].v[q];
+        al[q] = (T)(x && on && v[1] != 0.0 ? rho[q] / v[1] : 0.0);
+        be[q] = (T)(r && on && rho[q] != 0.0 ? v[0] / rho[q] : 0.0);
+        if (PARTS && blockIdx.x == 0 && in[0].n) *rho_out = v[0];
     }
     __syncthreads();
     while (e0 < ne) {
@@ -371,9 +392,7 @@ __global__ void __launch_bounds__(N) reduce_partials_kernel(const double *partia
         for (int k = 0; k < 8; ++k)
             if (b + k * N < nblocks) a[k] += col[b + k * N];
     }
-    double s = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-#pragma unroll
-    for (int w = 32; w > 0; w >>= 1) s += __shfl_down(s, w);
+    const double s = partial_wave(a);
     if ((t & 63) == 0) red[t >> 6] = s;
     __syncthreads();
     if (t == 0) {
@@ -689,24 +708,37 @@ hipError_t launch_cg_xr(const BlasShape &b, SpinorFmt fx, SpinorFmt fp, SpinorFm
 }
 
 hipError_t launch_cg_xp(const BlasShape &b, SpinorFmt f, void *x, const void *r, void *p,
-                        const double *rho_new, const double *rho, const double *pi,
-                        const int *active, hipStream_t st) {
+                        const Sum &rho_new, const double *rho, const Sum &pi, const int *active,
+                        double *rho_out, hipStream_t st) {
     const size_t bb = block_bytes(f, b.S, b.R);
+    const bool parts = rho_new.n > 0 || pi.n > 0;
+    if (parts && (b.R != 1 || f == SpinorFmt::F16 || rho_new.n > kSumMax || pi.n > kSumMax))
+        return hipErrorInvalidValue;
     if (f == SpinorFmt::F16) {
-        XpFn fn{x, r, p, bb, rho_new, rho, pi, active, b.S, b.R};
+        XpFn fn{x, r, p, bb, rho_new.v, rho, pi.v, active, b.S, b.R};
         return run(fn, b, nullptr, st);
     }
     // S is a multiple of 64 sites, so a field is whole elements
     const size_t bytes = bb * b.nblk, blocks = (bytes / 16 + 255) / 256;
-    const dim3 grid((unsigned)(blocks <= kXpBlocks ? blocks : kXpBlocks));
-    if (f == SpinorFmt::F64)
-        hipLaunchKernelGGL(cg_xp_kernel<double>, grid, dim3(256), 0, st, (cpx<double> *)x,
-                           (const cpx<double> *)r, (cpx<double> *)p, bytes / 16, b.R, rho_new, rho,
-                           pi, active);
-    else
-        hipLaunchKernelGGL(cg_xp_kernel<float>, grid, dim3(256), 0, st, (cpx<float> *)x,
-                           (const cpx<float> *)r, (cpx<float> *)p, bytes / 8, b.R, rho_new, rho,
-                           pi, active);
+    // blocks that add partial sums first: four elements per lane, to add them less often
+    const size_t want = parts ? (blocks + 3) / 4 : blocks;
+    const dim3 grid((unsigned)(want <= kXpBlocks ? want : kXpBlocks));
+#define COLA_XP(T, PARTS)                                                                     \
+    hipLaunchKernelGGL((cg_xp_kernel<T, PARTS>), grid, dim3(256), 0, st, (cpx<T> *)x,         \
+                       (const cpx<T> *)r, (cpx<T> *)p, bytes / sizeof(cpx<T>), b.R, rho_new,  \
+                       rho, pi, active, rho_out)
+    if (f == SpinorFmt::F64) {
+        if (parts)
+            COLA_XP(double, true);
+        else
+            COLA_XP(double, false);
+    } else {
+        if (parts)
+            COLA_XP(float, true);
+        else
+            COLA_XP(float, false);
+    }
+#undef COLA_XP
     return hipGetLastError();
 }
 

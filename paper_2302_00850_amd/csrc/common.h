@@ -148,6 +148,7 @@ struct HopArgs {
     // its per-rhs scalars
     void *cg_r;
     const double *cg_rho, *cg_pi;
+    int cg_pi_n;  // > 0 (one rhs): cg_pi is this many partial sums, not yet added
     const int *cg_active;
 };
 
@@ -159,6 +160,7 @@ struct HopArgs {
 // one ticket per group and one for the groups.
 constexpr int kRedGroup = 256;
 constexpr int kRedMaxBlocks = 65536;
+constexpr int kSumMax = 8 * 256;  // most partial sums that a consumer adds itself
 constexpr int kRedMaxWidth = 16;
 constexpr int kRedGroups = kRedMaxBlocks / kRedGroup;
 constexpr size_t kRedPartialDoubles = (size_t)(kRedMaxBlocks + kRedGroups) * kRedMaxWidth;
@@ -182,5 +184,11 @@ constexpr int link_real_bytes(LinkFmt f) {
 constexpr int spinor_real_bytes(SpinorFmt f) {
     return f == SpinorFmt::F64 ? 8 : f == SpinorFmt::F32 ? 4 : 2;
 }
+
+// A per-rhs scalar of the CG (n = 0), or for one rhs n partial sums of it.
+struct Sum {
+    const double *v;
+    int n;
+};
 
 }  // namespace cola

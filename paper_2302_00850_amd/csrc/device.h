@@ -68,6 +68,20 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t n, FastDiv f) {
     return (__umulhi(n, f.m) + n) >> f.s;
 }
 
+// The sum of n <= kSumMax partial sums by the first 256 threads of a block: each loads its
+// terms (partial_terms), each wavefront adds its own (partial_wave, in lane 0), and the four
+// wavefronts' sums are added in order.  The order is that of reduce_partials_kernel<256>.
+__device__ __forceinline__ void partial_terms(const double *v, int n, int t, double a[8]) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) a[k] = t + k * 256 < n ? v[t + k * 256] : 0.0;
+}
+__device__ __forceinline__ double partial_wave(const double a[8]) {
+    double s = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) s += __shfl_down(s, w);
+    return s;
+}
+
 // XCD-aware work split.  Workgroups are dispatched to the 8 XCDs of the chip
 // round-robin (block b runs on XCD b mod 8), each with its own L2.  The nchunks chunks of
 // work are cut into one contiguous range per XCD, in proportion to its blocks, so the

@@ -141,6 +141,11 @@ struct HopCall {
     // EPI_XPAY_CG / EPI_CLOV_XPAY_CG: the CG residual and per-rhs scalars
     void *cg_r = nullptr;
     const double *cg_rho = nullptr, *cg_pi = nullptr;
+    int cg_pi_n = 0;  // as in HopArgs
+    // if set, a launch that can leaves its *norm_n partial sums in norm_partial (kSumMax
+    // doubles) for the consumer to add, instead of norm_result; *norm_n = 0 otherwise
+    double *norm_partial = nullptr;
+    int *norm_n = nullptr;
     const int *cg_active = nullptr;
     // fixed: no launch-shape tuning, no timing events, no occupancy queries (the
     // non-allocating entry point); the shape is the cached or the default one
@@ -152,20 +157,29 @@ int hop(cola_handle_t *h, const HopCall &c, int prec, int nrhs, hipStream_t st);
 // The handle's links from U, canonical or (packed) in the packed 18-real format.
 int set_links(cola_handle_t *h, const void *U, bool packed, hipStream_t st);
 
+// Where a step leaves a norm: the scalars, or the partial sums (may be null) and their count.
+struct NormTo {
+    double *result;
+    double *partial;
+    int *n;
+};
+
 // One CG step on the even-odd normal system S^dag S, with the update of r fused into the
 // last hop: pi = |S p|^2, then with alpha = rho / pi per active rhs,
 //   r -= alpha S^dag S p,  rho_new = |r|^2
 // (x += alpha p is left to the update of p).  r, p: even-parity blocks in the storage of prec.
 int schur_normal_cg_step(cola_handle_t *h, int prec, int nrhs, hipStream_t st, void *r,
-                         const void *p, const double *rho, double *pi, const int *active,
-                         double *rho_new);
+                         const void *p, const double *rho, const NormTo &pi, const int *active,
+                         const NormTo &rho_new);
 
 // composite operators on packed fields (see COLA_OP_*); norm_result (optional)
 // receives |out|^2 per rhs where the composition allows it to be fused.  ws: a
 // caller-provided workspace of op_workspace_bytes() for the intermediate vectors
 // (the hops then run in their fixed shapes, untimed); nullptr: the handle's cache.
+// norm (COLA_OP_M, COLA_OP_SCHUR): in place of norm_result, may leave partial sums.
 int apply_op(cola_handle_t *h, void *out, const void *in, int op, int parity, int prec, int nrhs,
-             hipStream_t st, double *norm_result = nullptr, char *ws = nullptr);
+             hipStream_t st, double *norm_result = nullptr, char *ws = nullptr,
+             const NormTo *norm = nullptr);
 size_t op_workspace_bytes(const cola_handle_t *h, int op, int prec, int nrhs);
 
 // low-eigenmode solver and deflated CG (eigen.cpp)

@@ -174,14 +174,15 @@ __global__ void __launch_bounds__(8 * kDirsSites) hop_dirs_kernel(const HopArgs 
         }
     };
     C xv[3], cr[3];
-    T al = (T)0;
     if (d < 4 && valid) {
         if constexpr (XIN) own(a.x, xv);
-        if constexpr (CG) {
-            own(a.cg_r, cr);
-            const double den = a.cg_pi[j];
-            al = (T)(a.cg_active[j] && den != 0.0 ? a.cg_rho[j] / den : 0.0);
-        }
+        if constexpr (CG) own(a.cg_r, cr);
+    }
+    // pi may be (one rhs) partial sums: loaded here, added once the neighbours are in
+    __shared__ double sums[4];
+    double tp[8];
+    if constexpr (CG) {
+        if (d < 4 && a.cg_pi_n) partial_terms(a.cg_pi, a.cg_pi_n, (int)threadIdx.x, tp);
     }
     if (valid) {
         const SpinorBlock<SF, true> in((const char *)a.in + no, g.S, a.nrhs);
@@ -196,6 +197,12 @@ __global__ void __launch_bounds__(8 * kDirsSites) hop_dirs_kernel(const HopArgs 
             case 5: half_spinor<2, 1, SF, LF, RPH>(a, in, p, i, x, j, sg_f, W[5], l); break;
             case 6: half_spinor<3, 0, SF, LF, RPH>(a, in, p, i, x, j, sg_f, W[6], l); break;
             default: half_spinor<3, 1, SF, LF, RPH>(a, in, p, i, x, j, sg_f, W[7], l); break;
+        }
+    }
+    if constexpr (CG) {
+        if (d < 4 && a.cg_pi_n) {
+            const double s = partial_wave(tp);
+            if (l == 0) sums[d] = s;
         }
     }
     __syncthreads();
@@ -236,6 +243,8 @@ __global__ void __launch_bounds__(8 * kDirsSites) hop_dirs_kernel(const HopArgs 
             for (int c = 0; c < 3; ++c) bstore<E>(w.next(), off, E{v[c].x, v[c].y});
         };
         if constexpr (CG) {
+            const double den = a.cg_pi_n ? ((sums[0] + sums[1]) + sums[2]) + sums[3] : a.cg_pi[j];
+            const T al = (T)(a.cg_active[j] && den != 0.0 ? a.cg_rho[j] / den : 0.0);
 #pragma unroll
             for (int c = 0; c < 3; ++c)
                 o[c] = {fma(-al, o[c].x, cr[c].x), fma(-al, o[c].y, cr[c].y)};

@@ -89,9 +89,11 @@ hipError_t launch_cg_xr(const BlasShape &b, SpinorFmt fx, SpinorFmt fp, SpinorFm
 // The vector updates that follow a CG step with r updated in the last hop, all fields in
 // format f: x += alpha p (x null: not done; alpha_q = active_q ? rho_q / pi_q : 0), then
 // p = r + beta p (r null: not done; beta_q = active_q ? rho_new_q / rho_q : 0)
+// (Sum: the scalars, or for one rhs in FP64 or FP32 at most kSumMax partial sums of them;
+// rho_out receives rho_new where that is partial sums)
 hipError_t launch_cg_xp(const BlasShape &b, SpinorFmt f, void *x, const void *r, void *p,
-                        const double *rho_new, const double *rho, const double *pi,
-                        const int *active, hipStream_t st);
+                        const Sum &rho_new, const double *rho, const Sum &pi, const int *active,
+                        double *rho_out, hipStream_t st);
 // result = |v|^2 per rhs
 hipError_t launch_norm2(const BlasShape &b, SpinorFmt f, const void *v, const Reduce &red,
                         hipStream_t st);

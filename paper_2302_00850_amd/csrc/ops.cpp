@@ -385,11 +385,18 @@ int fill_and_launch(cola_handle_t *h, const HopCall &c, int prec, int nrhs, cons
     a.cg_r = c.cg_r;
     a.cg_rho = c.cg_rho;
     a.cg_pi = c.cg_pi;
+    a.cg_pi_n = c.cg_pi_n;
     a.cg_active = c.cg_active;
     a.gauge = h->gauge[(int)link_fmt(prec)];
     a.gauge_fat = h->flic ? h->fat[(int)link_fmt(prec)] : nullptr;
     a.clov = c.clov;
-    a.partial = h->partial;
+    // Few one-rhs partial sums stay as they are for the kernels that use the norm: at 16^3 x 32 a
+    // launch that adds 1024 of them takes 3.7 us and a gap of 2, adding them beside the
+    // consumer's own loads under 1 us (FP32 solve 6.58 -> 6.25 ms; FP64 M^dag M, 2048 of
+    // them, 29.4 -> 27.9).  Beyond kSumMax a block would need a second round of loads.
+    const bool keep = c.norm_partial && nrhs == 1 && te.stage == 2 && grid <= kSumMax;
+    if (c.norm_n) *c.norm_n = keep ? grid : 0;
+    a.partial = keep ? c.norm_partial : h->partial;
     a.total = (uint32_t)(h->g.Vh / te.tchunk) * (uint32_t)groups;
     a.sites_per_block = T;
     a.tchunk = te.tchunk;
@@ -432,7 +439,7 @@ int fill_and_launch(cola_handle_t *h, const HopCall &c, int prec, int nrhs, cons
     }
     COLA_HIP(h, launch_hop(a, link_fmt(prec), te.rpt, grid, block, st));
     if (grid_out) *grid_out = grid;
-    if (c.norm_result && reduce)
+    if (c.norm_result && reduce && !keep)
         COLA_HIP(h, launch_reduce_partials(h->partial, grid, nrhs, c.norm_result, st));
     return COLA_OK;
 }
@@ -578,7 +585,8 @@ int flush_timing(cola_handle_t *h, bool wait_all) {
     return COLA_OK;
 }
 
-int hop(cola_handle_t *h, const HopCall &c, int prec, int nrhs, hipStream_t st) {
+int hop(cola_handle_t *h, const HopCall &call, int prec, int nrhs, hipStream_t st) {
+    HopCall c = call;
     if (!h->gauge_set) return set_error(h, COLA_ESTATE, "no gauge field set");
     if (prec != COLA_FP64 && !h->su3)
         return set_error(h, COLA_EINVAL,
@@ -621,6 +629,14 @@ int hop(cola_handle_t *h, const HopCall &c, int prec, int nrhs, hipStream_t st) 
         te.rpt = 1;
         te.stage = 0;
     }
+    // the other kernels take ready scalars
+    if (te.stage != 2 && c.cg_pi_n > 0) {
+        void *s;
+        COLA_TRY(get_vec(h, "hop_sum", sizeof(double), &s));
+        COLA_HIP(h, launch_reduce_partials(c.cg_pi, c.cg_pi_n, 1, (double *)s, st));
+        c.cg_pi = (const double *)s;
+        c.cg_pi_n = 0;
+    }
     const bool timed = (h->flags & COLA_FLAG_TIMING) != 0 && !c.fixed;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (timed) {
@@ -634,7 +650,7 @@ int hop(cola_handle_t *h, const HopCall &c, int prec, int nrhs, hipStream_t st) 
     int grid = 0;
     COLA_TRY(fill_and_launch(h, c, prec, nrhs, te, st, false, &grid));
     if (timed) COLA_HIP(h, hipEventRecord(e1, st));
-    if (c.norm_result)
+    if (c.norm_result && !(c.norm_n && *c.norm_n > 0))
         COLA_HIP(h, launch_reduce_partials(h->partial, grid, nrhs, c.norm_result, st));
     if (timed) {
         double b, f;
@@ -684,7 +700,14 @@ size_t op_workspace_bytes(const cola_handle_t *h, int op, int prec, int nrhs) {
 }
 
 int apply_op(cola_handle_t *h, void *out, const void *in, int op, int parity, int prec, int nrhs,
-             hipStream_t st, double *norm_result, char *ws) {
+             hipStream_t st, double *norm_result, char *ws, const NormTo *norm) {
+    auto set_norm = [&](HopCall &c) {
+        c.norm_result = norm ? norm->result : norm_result;
+        if (norm) {
+            c.norm_partial = norm->partial;
+            c.norm_n = norm->n;
+        }
+    };
     const SpinorFmt sf = spinor_fmt(prec);
     const size_t bb = spinor_block_bytes(h->g, sf, nrhs);
     const bool fixed = ws != nullptr;
@@ -711,7 +734,7 @@ int apply_op(cola_handle_t *h, void *out, const void *in, int op, int parity, in
             c.x = in;
             c.a = -k;
             c.clov = A;
-            c.norm_result = norm_result;
+            set_norm(c);
             c.fixed = fixed;
             return hop(h, c, prec, nrhs, st);
         }
@@ -743,7 +766,7 @@ int apply_op(cola_handle_t *h, void *out, const void *in, int op, int parity, in
             c2.x = in;
             c2.a = -k * k;
             c2.clov = A;
-            c2.norm_result = norm_result;
+            set_norm(c2);
             c2.fixed = fixed;
             return hop(h, c2, prec, nrhs, st);
         }
@@ -762,8 +785,8 @@ int apply_op(cola_handle_t *h, void *out, const void *in, int op, int parity, in
 }
 
 int schur_normal_cg_step(cola_handle_t *h, int prec, int nrhs, hipStream_t st, void *r,
-                         const void *p, const double *rho, double *pi, const int *active,
-                         double *rho_new) {
+                         const void *p, const double *rho, const NormTo &pi, const int *active,
+                         const NormTo &rho_new) {
     const SpinorFmt sf = spinor_fmt(prec);
     const size_t bb = spinor_block_bytes(h->g, sf, nrhs);
     const bool clover = h->csw != 0.0;
@@ -774,7 +797,7 @@ int schur_normal_cg_step(cola_handle_t *h, int prec, int nrhs, hipStream_t st, v
                      &te));
     COLA_TRY(get_vec(h, "op_odd_" + std::to_string((int)sf) + "_" + std::to_string(nrhs), bb,
                      &to));
-    COLA_TRY(apply_op(h, te, p, COLA_OP_SCHUR, 0, prec, nrhs, st, pi));
+    COLA_TRY(apply_op(h, te, p, COLA_OP_SCHUR, 0, prec, nrhs, st, nullptr, nullptr, &pi));
     // S^dag te: t_o = A_oo^-1 D_oe^dag te, then the CG update with A_ee te - kappa^2 D_eo^dag t_o
     HopCall c1{to, te, 1, 1};
     if (clover) {
@@ -787,10 +810,14 @@ int schur_normal_cg_step(cola_handle_t *h, int prec, int nrhs, hipStream_t st, v
     c2.x = te;
     c2.a = -h->kappa * h->kappa;
     c2.clov = f64 ? h->clov64 : h->clov32;
-    c2.norm_result = rho_new;
+    c2.norm_result = rho_new.result;
+    c2.norm_partial = rho_new.partial;
+    c2.norm_n = rho_new.n;
     c2.cg_r = r;
     c2.cg_rho = rho;
-    c2.cg_pi = pi;
+    const bool kept = pi.n && *pi.n > 0;
+    c2.cg_pi = kept ? pi.partial : pi.result;
+    c2.cg_pi_n = kept ? *pi.n : 0;
     c2.cg_active = active;
     return hop(h, c2, prec, nrhs, st);
 }

@@ -57,7 +57,27 @@ struct Ctx {
     mutable bool x_due = false;
     int place(int s) const { return s <= RHO_NEW ? s ^ flip : s; }
     double *slot(int s) const { return scal_slot(h, place(s)); }
-    Reduce reduce(int s) const { return reduce_into(h, place(s)); }
+    // RHO_NEW and PI of one rhs may still be partial sums (count > 0), which the kernels that
+    // follow add; keep: steps may leave them so.  slot() and reduce() are for whole
+    // scalars: after settle(), or to write one (fresh()).
+    mutable int parts[3] = {0, 0, 0};
+    mutable double *part_buf = nullptr;  // 3 x kSumMax
+    mutable bool keep = false;
+    Sum sum(int s) const {
+        const int n = parts[place(s)];
+        return n > 0 ? Sum{part_buf + place(s) * kSumMax, n} : Sum{slot(s), 0};
+    }
+    NormTo norm_to(int s) const {
+        return {slot(s), keep ? part_buf + place(s) * kSumMax : nullptr, &parts[place(s)]};
+    }
+    double *fresh(int s) const {
+        if (s <= PI) parts[place(s)] = 0;
+        return slot(s);
+    }
+    Reduce reduce(int s) const {
+        fresh(s);
+        return reduce_into(h, place(s));
+    }
 };
 
 // Iterations between host convergence checks when the caller leaves it to the library.
@@ -77,16 +97,33 @@ int vec(const Ctx &c, const char *tag, SpinorFmt f, void **out) {
     return get_vec(c.h, t, c.bytes(f), out);
 }
 
+// add the partial sums that RHO, RHO_NEW or PI still is
+int settle(const Ctx &c, int s) {
+    const Sum v = c.sum(s);
+    if (v.n > 0) COLA_HIP(c.h, launch_reduce_partials(v.v, v.n, 1, c.fresh(s), c.st));
+    return COLA_OK;
+}
+
+// steps of this solve may leave partial sums (one rhs)
+int keep_sums(const Ctx &c, bool on) {
+    c.keep = on && c.R == 1;
+    if (!c.keep) return COLA_OK;
+    void *v;
+    COLA_TRY(get_vec(c.h, "cg_parts", 3 * kSumMax * sizeof(double), &v));
+    c.part_buf = (double *)v;
+    return COLA_OK;
+}
+
 // out = A in, |first factor output|^2 -> PI
 int normal(const Ctx &c, int prec, void *out, const void *in) {
     if (!c.full)
-        return apply_op(c.h, out, in, COLA_OP_SCHUR_DAGSCHUR, 0, prec, c.R, c.st, c.slot(PI));
+        return apply_op(c.h, out, in, COLA_OP_SCHUR_DAGSCHUR, 0, prec, c.R, c.st, c.fresh(PI));
     cola_handle_t *h = c.h;
     const SpinorFmt sf = spinor_fmt(prec);
     void *t;
     COLA_TRY(get_vec(h, "cg_full_t_" + std::to_string((int)sf) + "_" + std::to_string(c.R),
                      c.bytes(sf), &t));
-    COLA_TRY(apply_op(h, t, in, COLA_OP_M, -1, prec, c.R, c.st, c.slot(PI)));
+    COLA_TRY(apply_op(h, t, in, COLA_OP_M, -1, prec, c.R, c.st, c.fresh(PI)));
     return apply_op(h, out, t, COLA_OP_MDAG, -1, prec, c.R, c.st);
 }
 
@@ -96,25 +133,30 @@ int normal(const Ctx &c, int prec, void *out, const void *in) {
 // the full lattice) and x together with p, which is then read once for both;
 // COLA_CG_FUSE=0 selects a separate update kernel of x and r.
 int full_normal_cg_step(const Ctx &c, int prec, void *r, void *pv, const double *rho,
-                        double *rho_new) {
+                        const NormTo &rho_new) {
     cola_handle_t *h = c.h;
     const SpinorFmt sf = spinor_fmt(prec);
     void *t;
     COLA_TRY(get_vec(h, "cg_full_t_" + std::to_string((int)sf) + "_" + std::to_string(c.R),
                      c.bytes(sf), &t));
     const bool clover = h->csw != 0.0;
-    COLA_TRY(apply_op(h, t, pv, COLA_OP_M, -1, prec, c.R, c.st, c.slot(PI)));
-    // M^dag t with the update of x and r, both parities in one launch
+    const NormTo pi = c.norm_to(PI);
+    COLA_TRY(apply_op(h, t, pv, COLA_OP_M, -1, prec, c.R, c.st, nullptr, nullptr, &pi));
+    // M^dag t with the update of r, both parities in one launch
     HopCall hc{r, t, 0, 1};
     hc.both = true;
     hc.epi = clover ? EPI_CLOV_XPAY_CG : EPI_XPAY_CG;
     hc.x = t;
     hc.a = -h->kappa;
     hc.clov = sf == SpinorFmt::F64 ? h->clov64 : h->clov32;
-    hc.norm_result = rho_new;
+    hc.norm_result = rho_new.result;
+    hc.norm_partial = rho_new.partial;
+    hc.norm_n = rho_new.n;
     hc.cg_r = r;
     hc.cg_rho = rho;
-    hc.cg_pi = c.slot(PI);
+    const Sum ps = c.sum(PI);
+    hc.cg_pi = ps.v;
+    hc.cg_pi_n = ps.n;
     hc.cg_active = h->active;
     return hop(h, hc, prec, c.R, c.st);
 }
@@ -125,10 +167,11 @@ int cg_step(const Ctx &c, int prec, SpinorFmt fx, void *x, void *r, void *pv, vo
     const char *env = getenv("COLA_CG_FUSE");
     const bool fuse = fx == fp && !(env && env[0] == '0');
     c.x_due = fuse;
-    if (fuse && c.full) return full_normal_cg_step(c, prec, r, pv, c.slot(RHO), c.slot(RHO_NEW));
+    if (fuse && c.full)
+        return full_normal_cg_step(c, prec, r, pv, c.slot(RHO), c.norm_to(RHO_NEW));
     if (fuse)
-        return schur_normal_cg_step(h, prec, c.R, c.st, r, pv, c.slot(RHO), c.slot(PI), h->active,
-                                    c.slot(RHO_NEW));
+        return schur_normal_cg_step(h, prec, c.R, c.st, r, pv, c.slot(RHO), c.norm_to(PI),
+                                    h->active, c.norm_to(RHO_NEW));
     COLA_TRY(normal(c, prec, ap, pv));
     COLA_HIP(h, launch_cg_xr(c.shape(), fx, fp, fx, fp, x, pv, r, ap, c.slot(RHO), c.slot(PI),
                              h->active, c.reduce(RHO_NEW), c.st));
@@ -156,6 +199,7 @@ int initial_residual(const Ctx &c, void *r, const void *b, const void *x, bool x
 }
 
 int read_slot(const Ctx &c, int slot, double *out) {
+    if (slot <= PI) COLA_TRY(settle(c, slot));
     COLA_HIP(c.h, hipMemcpyAsync(out, c.slot(slot), sizeof(double) * c.R, hipMemcpyDeviceToHost,
                                  c.st));
     COLA_HIP(c.h, hipStreamSynchronize(c.st));
@@ -190,8 +234,10 @@ void rotate_rho(const Ctx &c) { c.flip ^= 1; }
 
 // p = r + beta p, with the x update that is due; the new |r|^2 becomes the old one
 int update_p(const Ctx &c, SpinorFmt f, void *x, const void *r, void *p) {
-    COLA_HIP(c.h, launch_cg_xp(c.shape(), f, c.x_due ? x : nullptr, r, p, c.slot(RHO_NEW),
-                               c.slot(RHO), c.slot(PI), c.h->active, c.st));
+    COLA_HIP(c.h, launch_cg_xp(c.shape(), f, c.x_due ? x : nullptr, r, p, c.sum(RHO_NEW),
+                               c.slot(RHO), c.x_due ? c.sum(PI) : Sum{c.slot(PI), 0},
+                               c.h->active, c.slot(RHO_NEW), c.st));
+    c.fresh(RHO_NEW);  // whole now
     c.x_due = false;
     rotate_rho(c);
     return COLA_OK;
@@ -200,14 +246,15 @@ int update_p(const Ctx &c, SpinorFmt f, void *x, const void *r, void *p) {
 // The x update that is due, without p: before x is read and before the active columns change.
 int finish_x(const Ctx &c, SpinorFmt f, void *x, void *p) {
     if (c.x_due)
-        COLA_HIP(c.h, launch_cg_xp(c.shape(), f, x, nullptr, p, c.slot(RHO_NEW), c.slot(RHO),
-                                   c.slot(PI), c.h->active, c.st));
+        COLA_HIP(c.h, launch_cg_xp(c.shape(), f, x, nullptr, p, Sum{c.slot(RHO_NEW), 0},
+                                   c.slot(RHO), c.sum(PI), c.h->active, nullptr, c.st));
     c.x_due = false;
     return COLA_OK;
 }
 
 // x64 += x (the sloppy solution, with the x update that is due), x = 0
 int fold_x(const Ctx &c, SpinorFmt f, void *x64, void *x, const void *p) {
+    if (c.x_due) COLA_TRY(settle(c, PI));
     COLA_HIP(c.h, launch_accum(c.shape(), f, x64, x, nullptr, 1, c.st, c.x_due ? p : nullptr,
                                c.slot(RHO), c.slot(PI), c.h->active));
     c.x_due = false;
@@ -350,11 +397,12 @@ int solve_reliable(const Ctx &c, int sloppy_prec, const cola_cg_params_t &p, voi
     COLA_TRY(write_active(c, act));
     const Reduce red_rho = c.reduce(RHO);
     if (!same) COLA_HIP(h, launch_convert(sh, fs, SpinorFmt::F64, rs, r64, nullptr, 0, &red_rho, c.st));
-    else COLA_HIP(h, hipMemcpyAsync(c.slot(RHO), c.slot(TRUE_RES), sizeof(double) * c.R, hipMemcpyDeviceToDevice, c.st));
+    else COLA_HIP(h, hipMemcpyAsync(c.fresh(RHO), c.slot(TRUE_RES), sizeof(double) * c.R, hipMemcpyDeviceToDevice, c.st));
     COLA_HIP(h, launch_convert(sh, fs, fs, ps, rs, nullptr, 0, nullptr, c.st));
     int last_rel = 0;
     int it = 0;
     const bool graphs = graphs_wanted(c);
+    COLA_TRY(keep_sums(c, !graphs));  // replays would need the counts
     while (it < p.max_iter) {
         // the iterations up to the next check (it % check == 0 or the cap)
         const int n = std::min(check - it % check, p.max_iter - it);
@@ -400,7 +448,7 @@ int solve_reliable(const Ctx &c, int sloppy_prec, const cola_cg_params_t &p, voi
                         COLA_HIP(h, launch_convert(sh, fs, SpinorFmt::F64, rs, r64, nullptr, 0,
                                                    &red_new, c.st));
                     else
-                        COLA_HIP(h, hipMemcpyAsync(c.slot(RHO_NEW), c.slot(TRUE_RES),
+                        COLA_HIP(h, hipMemcpyAsync(c.fresh(RHO_NEW), c.slot(TRUE_RES),
                                                    sizeof(double) * c.R, hipMemcpyDeviceToDevice,
                                                    c.st));
                     if (restart) {
@@ -447,6 +495,7 @@ int inner_cg(const Ctx &c, int prec, void *x, void *r, void *pv, void *ap,
     std::vector<double> rho(c.R);
     int it = 0;
     const bool graphs = graphs_wanted(c);
+    COLA_TRY(keep_sums(c, !graphs));  // replays would need the counts
     while (it < max_it) {
         // the iterations up to the next check
         const int n = std::min(check - it % check, max_it - it);
@@ -877,10 +926,12 @@ int cg_multishift_impl(cola_handle_t *h, void *x, const void *b, int nshift, con
             break;
         }
         if (full)
-            COLA_TRY(full_normal_cg_step(c, COLA_FP64, r64, p64, rho, rho_new));
+            COLA_TRY(full_normal_cg_step(c, COLA_FP64, r64, p64, rho,
+                                         NormTo{rho_new, nullptr, nullptr}));
         else
-            COLA_TRY(schur_normal_cg_step(h, COLA_FP64, 1, st, r64, p64, rho, c.slot(PI),
-                                          h->active, rho_new));
+            COLA_TRY(schur_normal_cg_step(h, COLA_FP64, 1, st, r64, p64, rho,
+                                          NormTo{c.slot(PI), nullptr, nullptr}, h->active,
+                                          NormTo{rho_new, nullptr, nullptr}));
         COLA_HIP(h, launch_ms_advance(state, rho_new, c.slot(PI), st));
         COLA_HIP(h, launch_ms_update(xs, ps, r64, p64, &state->coef, nshift, rho_new, rho, n, st));
         std::swap(rho, rho_new);
