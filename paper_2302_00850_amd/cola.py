@@ -324,7 +324,11 @@ def cola_tune_dump(h) -> str:
 # ------------------------------------------------------------- convenience
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    # the raw handle of the current device's current stream: building a Stream object for it
+    # takes 2.7 of the 8.6 us that M on 4^4 spends on the host, the handle alone 0.3
+    if not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t: torch.Tensor) -> int:
