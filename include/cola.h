@@ -168,8 +168,8 @@ enum {
     COLA_HOP_CLOV = 2,         /* out = C D in                                           */
     COLA_HOP_CLOV_XPAY = 3,    /* out = C x + a D in                                     */
     COLA_HOP_XPAY_CLOV = 4,    /* out = C (x + a D in)                                   */
-    COLA_HOP_XPAY_CG = 5,      /* CG update of x and r with x + a D in (nothing stored)  */
-    COLA_HOP_CLOV_XPAY_CG = 6, /* CG update of x and r with C x + a D in                 */
+    COLA_HOP_XPAY_CG = 5,      /* CG update of r with x + a D in (nothing else stored)  */
+    COLA_HOP_CLOV_XPAY_CG = 6, /* CG update of r with C x + a D in                       */
     COLA_HOP_KINDS = 8
 };
 

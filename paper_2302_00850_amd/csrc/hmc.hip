@@ -10,7 +10,8 @@
 //   reductions    sum of Re Tr U_plaq, sum of Tr P^2, Re <a, b>: per-block partials
 //                 in a fixed-shape LDS tree, then the block-order reduce launch.
 //
-// One lane per link (or per site for the plaquette sum), grid-stride loops.
+// One lane per link (or per site for the plaquette sum), grid-stride loops.  These serve the
+// single-step entry points; a trajectory runs on packed fields.
 #include "device.h"
 #include "launch.h"
 
