@@ -77,17 +77,7 @@ int cola_create(cola_handle_t **hp, const int dims[4], double kappa, const doubl
     cola_handle_t *h = new (std::nothrow) cola_handle_t;
     if (!h) return COLA_ENOMEM;
     for (int mu = 0; mu < 4; ++mu) h->dims[mu] = dims[mu];
-    Geom &g = h->g;
-    for (int mu = 0; mu < 4; ++mu) g.L[mu] = dims[mu];
-    g.Lxh = dims[0] / 2;
-    g.Vh = (int)(V / 2);
-    g.S = packed_stride(g.Vh);
-    g.s1 = g.Lxh;
-    g.s2 = g.Lxh * dims[1];
-    g.s3 = g.Lxh * dims[1] * dims[2];
-    g.div_xh = make_fastdiv((uint32_t)g.Lxh);
-    g.div_y = make_fastdiv((uint32_t)dims[1]);
-    g.div_z = make_fastdiv((uint32_t)dims[2]);
+    h->g = make_geom(dims);
     h->kappa = kappa;
     h->csw = csw;
     h->flags = flags;

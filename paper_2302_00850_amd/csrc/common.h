@@ -57,6 +57,21 @@ struct Geom {
     FastDiv div_xh, div_y, div_z;
 };
 
+inline Geom make_geom(const int dims[4]) {
+    Geom g{};
+    for (int mu = 0; mu < 4; ++mu) g.L[mu] = dims[mu];
+    g.Lxh = dims[0] / 2;
+    g.s1 = g.Lxh;
+    g.s2 = g.s1 * dims[1];
+    g.s3 = g.s2 * dims[2];
+    g.Vh = g.s3 * dims[3];
+    g.S = packed_stride(g.Vh);
+    g.div_xh = make_fastdiv((uint32_t)g.Lxh);
+    g.div_y = make_fastdiv((uint32_t)dims[1]);
+    g.div_z = make_fastdiv((uint32_t)dims[2]);
+    return g;
+}
+
 // An order of the checkerboard sites of one parity in which neighbours in t stay close: a
 // tile of all x, ty x tz, walked through t, then the next tile (the extents are even, so
 // 2 x 2 always divides).  For the kernels on 18-real FP64 links, whose timeslices (576 bytes

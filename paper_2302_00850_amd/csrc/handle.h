@@ -11,27 +11,14 @@
 #include "../../include/cola.h"
 #include "common.h"
 #include "launch.h"
+#include "shapes.h"
 
 namespace cola {
 
 constexpr int kMaxRhs = kRedMaxWidth;
-constexpr int kMaxGrid = kRedMaxBlocks;
 constexpr int kEigMax = 32;  // eigenpairs of one cola_eigensolve call
 // size of the fixed device workspace of cola_dslash_apply_noalloc (per device)
 constexpr size_t kScratchBytes = (size_t)128 << 20;
-
-struct TuneEntry {
-    int rpt = 1;
-    int sites_per_block = 64;
-    int grid = 0;    // 0: one block per sites_per_block site columns; -1: the blocks
-                     // resident at once (grid-stride loop, no tail of late blocks)
-    int tchunk = 1;  // timeslices walked by one lane
-    int tile_y = 0;  // spatial tile (all x-rows x tile_y x tile_z); 0 = lexicographic
-    int tile_z = 0;
-    int stage = 0;   // 1: links staged in LDS by the lanes of a site (see stage_ok); 2: a
-                     // wavefront per direction (see dirs_ok)
-    double ms = 0;
-};
 
 // A pool of device vectors keyed by a small integer tag (kept until destroy).
 struct VecCache {

@@ -11,6 +11,7 @@
 #include <unistd.h>
 
 #include "handle.h"
+#include "shapes.h"
 
 namespace cola {
 
@@ -151,40 +152,6 @@ void shape_for(const TuneEntry &t, int Vh, int nrhs, bool both, int *groups, int
     *grid = (int)std::max(1L, g);
 }
 
-// A spatial tile must divide the y and z extents (tile_y = 0: no tiling).
-bool tile_ok(const Geom &g, int ty, int tz) {
-    if (ty == 0 && tz == 0) return true;
-    return ty > 0 && tz > 0 && g.L[1] % ty == 0 && g.L[2] % tz == 0;
-}
-
-// Link staging: one or two rhs per lane, at least three lanes per site to share the
-// eight links, whole sites of at most kStageSites per block, a 12-real FP16 or FP32 field
-// and a packed field addressable with 32-bit byte offsets.
-bool stage_ok(const Geom &g, int prec, int nrhs, const TuneEntry &t) {
-    if (prec != COLA_FP16 && prec != COLA_FP32) return false;
-    const double bytes = 8.0 * 3 * g.S * (prec == COLA_FP16 ? 8 : 16);
-    return (t.rpt == 1 || t.rpt == 2) && nrhs / t.rpt >= 3 && t.sites_per_block <= kStageSites &&
-           bytes < 2147483648.0;
-}
-
-// The hop with a wavefront per direction (stage = 2): FP64 and FP32, one rhs per lane, whole
-// sites of at most kDirsSites lanes per block, one block per sites_per_block sites.
-bool dirs_ok(const Geom &g, int prec, int nrhs, const TuneEntry &e) {
-    return prec != COLA_FP16 && e.rpt == 1 && e.grid == 0 && e.tchunk == 1 && e.tile_y == 0 &&
-           e.tile_z == 0 && e.sites_per_block >= 1 && e.sites_per_block * nrhs <= kDirsSites &&
-           2.0 * ((double)g.Vh / e.sites_per_block + 1) <= kMaxGrid;
-}
-
-// A launch shape the hop kernels accept for this lattice, precision and rhs count.
-bool shape_valid(const Geom &g, int prec, int nrhs, const TuneEntry &e) {
-    if (e.stage == 2) return dirs_ok(g, prec, nrhs, e);
-    const bool f64 = prec == COLA_FP64 || prec == COLA_FP64_12;
-    return (e.rpt >= 1 && e.rpt <= 4) && nrhs % e.rpt == 0 && (e.rpt == 1 || !f64) &&
-           e.sites_per_block >= 1 && (e.sites_per_block & (e.sites_per_block - 1)) == 0 &&
-           e.sites_per_block * (nrhs / e.rpt) <= 256 && e.grid >= -1 && e.tchunk >= 1 &&
-           g.L[3] % e.tchunk == 0 && tile_ok(g, e.tile_y, e.tile_z);
-}
-
 // ---- the persistent table of tuned shapes
 // Shared by every handle of the process and kept in a text file (one entry per line:
 // device tag, key, rpt, sites per block, grid, time chunk, tile y, tile z, staging, ms),
@@ -200,10 +167,6 @@ struct TuneStore {
 TuneStore &tune_store() {
     static TuneStore s;
     return s;
-}
-
-std::string store_key(const cola_handle_t *h, const std::string &key) {
-    return h->arch + ":" + std::to_string(h->num_cu) + " " + key;
 }
 
 int read_table(const std::string &path, std::map<std::string, TuneEntry> &out) {
@@ -238,105 +201,6 @@ int write_table(const std::string &path, const std::map<std::string, TuneEntry> 
     }
     if (fclose(f) != 0) return -1;
     return rename(tmp.c_str(), path.c_str()) == 0 ? (int)t.size() : -1;
-}
-
-// The largest spatial tile (ty x tz columns of all x, dividing the lattice, tz >= 2) whose
-// timeslice holds at most `most` checkerboard sites; the squarer one of equals.  0 x 0 when
-// there is none.
-void best_tile(const Geom &g, int most, int *ty, int *tz) {
-    *ty = *tz = 0;
-    for (int y = 2; y <= g.L[1]; ++y)
-        for (int z = 2; z <= g.L[2]; ++z) {
-            if (g.L[1] % y || g.L[2] % z || g.Lxh * y * z > most) continue;
-            const int now = y * z, had = *ty * *tz;
-            if (now > had || (now == had && abs(y - z) < abs(*ty - *tz))) {
-                *ty = y;
-                *tz = z;
-            }
-        }
-}
-
-// Launch shapes.  Tiles are walked through t, so that the timeslices in flight of a tile and
-// their links stay in one XCD's L2; the tile sizes below are where the times measured over
-// all divisors of 24^3 x 48, 32^3 x 64 and 48^3 x 96 are flat or lowest.
-TuneEntry plain_entry(const Geom &g, int prec, int nrhs, bool both) {
-    TuneEntry t;
-    t.rpt = 1;
-    const int G = nrhs;
-    int T = 1;
-    while (T * 2 * G <= 256) T *= 2;
-    t.sites_per_block = T;
-    t.grid = 0;
-    if (nrhs == 1) {
-        // 8192 sites, or 4096 where both parities run side by side.  M^dag M (both): FP64
-        // 48^3 x 96 7.12 ms with 16x16 tiles of 64-site blocks, 5.06 with 24x6 (256); 32^3 x
-        // 64 1.14 and 1.04 ms with 16x16 (256); 24^3 x 48 410 us untiled, 353 with 24x12;
-        // FP32 48^3 x 96 3.05 ms untiled, 2.36; FP16 1.60 ms with 16x8, 1.35.  S^dag S (one
-        // parity): FP64 48^3 x 96 7.30 -> 6.81 ms, 32^3 x 64 1.27 -> 1.23; FP32 2.94 -> 2.78
-        // ms and 528 -> 515 us.  Blocks of 256 sites where that leaves each CU several of
-        // them, else 64.
-        best_tile(g, both ? 4096 : 8192, &t.tile_y, &t.tile_z);
-        t.sites_per_block = (double)g.Vh * (both ? 2 : 1) >= 524288.0 ? 256 : 64;
-        return t;
-    }
-    if (prec == COLA_FP64 || prec == COLA_FP64_12) {
-        // FP64 (2304 bytes a site with 12 rhs).  12 rhs, S^dag S: 24^3 x 48 2.76 ms with
-        // 12x6, 2.82 with 8x8; 32^3 x 64 9.2 ms with 8x4 and 8x8; clover S 48^3 x 96 29.4
-        // ms with 8x4, 28.7 with 6x6; with 2 to 8 rhs 12x6 or 12x12 are the fastest on 24^3
-        // x 48.  M^dag M (both): 24^3 x 48 2.86 ms with 8x8, 2.73 with 6x4; 32^3 x 64 9.74
-        // ms with 8x8, 8.95 with 4x4; up to 8 rhs 12x6 as for one parity.
-        best_tile(g, both && nrhs > 8 ? 288 : 900, &t.tile_y, &t.tile_z);
-        return t;
-    }
-    // FP32 and FP16: the site's links staged in LDS from four rhs on.  M, 20 x 18 x 14 x 30
-    // clover FP32: 5 rhs 114 us unstaged, 87 staged; 4 rhs 83 and 72; 3 rhs 63 unstaged, 68
-    // staged.  24^3 x 48: 6 rhs 493 and 403 us, 4 rhs 322 and 316.
-    t.stage = nrhs >= 4 && stage_ok(g, prec, nrhs, t) ? 1 : 0;
-    if (t.stage) {
-        // With staged links the lanes can walk time with the neighbours of their index in
-        // registers: chunks of 8 timeslices where at least 12 rounds of resident blocks
-        // remain, of 4 where 4 rounds do, else no walk.  S^dag S with 12 rhs: FP32 24^3 x 48
-        // 1.29 ms with 8x8 in chunks of 8, 1.19 with 12x12 in 4; 32^3 x 64 3.99 and 3.78
-        // with 16x8 in 4; clover S 48^3 x 96 11.24 and 11.09 with 12x6 in 8; FP16 24^3 x 48
-        // 790 and 712 us.  5 to 8 rhs on 24^3 x 48 (2 to 3 rounds): 0 to 7% faster without
-        // the walk.  Both parities (M^dag M): FP32 24^3 x 48 1.21 ms with 12x6.
-        best_tile(g, both ? 1024 : 2048, &t.tile_y, &t.tile_z);
-        const double blocks = (double)g.Vh * (both ? 2 : 1) / T;
-        t.tchunk = blocks / 8 >= 12 * 1024.0 ? 8 : blocks / 4 >= 4 * 1024.0 ? 4 : 1;
-        while (g.L[3] % t.tchunk) t.tchunk /= 2;
-        return t;
-    }
-    // two and three rhs per site (M, 24^3 x 48 FP16: 92 us untiled in 256-lane blocks, 78
-    // with 12x12 tiles of 64-site blocks)
-    if (T > 64) t.sites_per_block = 64;
-    best_tile(g, 2048, &t.tile_y, &t.tile_z);
-    return t;
-}
-
-// Launches of few lanes (sites of one parity x rhs) take the hop with a wavefront per
-// direction, up to where it was measured no slower (us, this against plain_entry's shape; m:
-// both parities, s: D_eo D_oe):
-//   one rhs FP32  16^3 x 32 s 16.6 / 28.8, 24^3 x 48 s 72 / 95, m 69 / 73, 28^3 x 48 s 125 / 161,
-//                 32^3 x 64 s 302 / 266; with clover 28^3 x 48 s 183 / 220, 20^3 x 32 m 42 / 41,
-//                 24^3 x 32 m 70 / 66
-//   one rhs FP64  16^3 x 32 s 37 / 43, m 28 / 40, 24^3 x 32 s 126 / 140, 24^3 x 48 s 224 / 208,
-//                 28^3 x 48 m 280 / 294; with clover 20^3 x 32 s 99 / 104, 24^3 x 32 s 182 / 179
-//   several rhs   12^3 x 16 FP32 5 rhs s 17 / 23, 12 rhs m 36 / 30; FP64 8 rhs s 39 / 42,
-//                 12 rhs with clover s 79 / 77
-bool few_lanes(const Geom &g, int prec, int nrhs, bool both, bool clover) {
-    const bool f32 = prec == COLA_FP32;
-    const double lanes = (double)g.Vh * nrhs;
-    if (nrhs > 1) return lanes <= (f32 ? 65536 : 131072);
-    if (clover && (both || !f32)) return lanes <= 131072;
-    return lanes <= (f32 || both ? 600000 : 262144);
-}
-
-TuneEntry default_entry(const Geom &g, int prec, int nrhs, bool both, bool clover) {
-    TuneEntry t;
-    t.stage = 2;
-    t.sites_per_block = kDirsSites / nrhs;
-    if (few_lanes(g, prec, nrhs, both, clover) && dirs_ok(g, prec, nrhs, t)) return t;
-    return plain_entry(g, prec, nrhs, both);
 }
 
 // The default shape, or the one COLA_HOP_SHAPE pins.
@@ -460,7 +324,7 @@ bool stored_entry(cola_handle_t *h, const std::string &key, int prec, int nrhs, 
                 for (auto &kv : t) ts.table.emplace(kv.first, kv.second);  // keep newer
         }
     }
-    auto it = ts.table.find(store_key(h, key));
+    auto it = ts.table.find(table_key(h->arch, h->num_cu, key));
     if (it == ts.table.end()) return false;
     TuneEntry e = it->second;
     if (!shape_valid(h->g, prec, nrhs, e)) return false;
@@ -471,63 +335,7 @@ bool stored_entry(cola_handle_t *h, const std::string &key, int prec, int nrhs, 
 
 int tune_hop(cola_handle_t *h, const HopCall &c, int prec, int nrhs, TuneEntry *best,
              hipStream_t st) {
-    std::vector<TuneEntry> cand;
-    for (int rpt : {1, 2, 3, 4}) {
-        if (nrhs % rpt) continue;
-        if (rpt > 1 && spinor_fmt(prec) == SpinorFmt::F64) continue;
-        const int G = nrhs / rpt;
-        // blocks of whole wavefronts when some block size allows it
-        bool whole = false;
-        for (int T : {4, 8, 16, 32, 64, 128, 256}) whole |= T * G <= 256 && (T * G) % 64 == 0;
-        for (int T : {4, 8, 16, 32, 64, 128, 256}) {
-            if (T * G > 256 || T * G < 64) continue;
-            if (whole && (T * G) % 64 != 0) continue;
-            for (int tc : {1, 2, 4, 8, 16}) {
-                if (h->g.L[3] % tc) continue;
-                for (int grid : {0, -1}) {
-                    TuneEntry t;
-                    t.rpt = rpt;
-                    t.sites_per_block = T;
-                    t.grid = grid;
-                    t.tchunk = tc;
-                    cand.push_back(t);
-                }
-            }
-            const int tiles[][2] = {{4, 4}, {8, 4}, {4, 8}, {8, 8}, {16, 8}, {8, 16}, {16, 16}};
-            for (const auto &tl : tiles) {
-                if (!tile_ok(h->g, tl[0], tl[1])) continue;
-                TuneEntry t;
-                t.rpt = rpt;
-                t.sites_per_block = T;
-                t.tile_y = tl[0];
-                t.tile_z = tl[1];
-                cand.push_back(t);
-            }
-        }
-    }
-    {
-        TuneEntry t;
-        t.stage = 2;
-        t.sites_per_block = kDirsSites / nrhs;
-        if (dirs_ok(h->g, prec, nrhs, t)) cand.push_back(t);
-    }
-    // each shape also with the site's links staged in LDS, where that applies
-    const size_t n0 = cand.size();
-    for (size_t k = 0; k < n0; ++k) {
-        if (cand[k].stage == 2 || !stage_ok(h->g, prec, nrhs, cand[k])) continue;
-        TuneEntry t = cand[k];
-        t.stage = 1;
-        cand.push_back(t);
-        // the time walk of staged FP32 / FP16 hops: tiles in chunks of 4 and 8 timeslices
-        if ((prec == COLA_FP32 || prec == COLA_FP16) && t.rpt == 1 && t.tile_y > 0) {
-            for (int tc : {4, 8}) {
-                if (h->g.L[3] % tc) continue;
-                TuneEntry w = t;
-                w.tchunk = tc;
-                cand.push_back(w);
-            }
-        }
-    }
+    std::vector<TuneEntry> cand = tune_candidates(h->g, prec, nrhs);
     hipEvent_t e0, e1;
     COLA_HIP(h, hipEventCreate(&e0));
     COLA_HIP(h, hipEventCreate(&e1));
@@ -613,7 +421,7 @@ int hop(cola_handle_t *h, const HopCall &call, int prec, int nrhs, hipStream_t s
         // into the process-wide table and its file (a failed write only loses the cache)
         TuneStore &ts = tune_store();
         std::lock_guard<std::mutex> lock(ts.mu);
-        ts.table[store_key(h, key)] = te;
+        ts.table[table_key(h->arch, h->num_cu, key)] = te;
         const std::string path = tune_cache_path();
         if (!path.empty()) write_table(path, ts.table);
     } else if (!stored_entry(h, key, prec, nrhs, !c.fixed, &te)) {

@@ -1,0 +1,73 @@
+"""The launch-shape rules (csrc/shapes.h, host code) on the CPU, over lattices from 2^4 to
+48^3 x 96, every precision and right-hand-side count: each default is a shape the kernels
+accept, and what the rules say of it holds."""
+import ctypes
+import itertools
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2302_00850_amd", "csrc")
+
+PROBE = r"""
+#include <cstring>
+#include "shapes.h"
+using namespace cola;
+static void put(const TuneEntry &t, int *o) {
+    const int v[7] = {t.rpt, t.sites_per_block, t.grid, t.tchunk, t.tile_y, t.tile_z, t.stage};
+    memcpy(o, v, sizeof v);
+}
+extern "C" {
+void probe_default(const int *d, int prec, int nrhs, int both, int clover, int *o) {
+    put(default_entry(make_geom(d), prec, nrhs, both, clover), o);
+}
+void probe_plain(const int *d, int prec, int nrhs, int both, int *o) {
+    put(plain_entry(make_geom(d), prec, nrhs, both), o);
+}
+int probe_valid(const int *d, int prec, int nrhs, const int *s) {
+    TuneEntry t;
+    t.rpt = s[0], t.sites_per_block = s[1], t.grid = s[2], t.tchunk = s[3];
+    t.tile_y = s[4], t.tile_z = s[5], t.stage = s[6];
+    const Geom g = make_geom(d);
+    return shape_valid(g, prec, nrhs, t) && (t.stage != 1 || stage_ok(g, prec, nrhs, t));
+}
+}
+"""
+
+LATTICES = [(2, 2, 2, 2), (4, 4, 4, 4), (6, 4, 4, 10), (20, 18, 14, 30), (16, 16, 16, 32),
+            (2, 46, 34, 8), (24, 24, 24, 48), (32, 32, 32, 64), (48, 48, 48, 96)]
+FP64, FP64_12, FP32, FP16 = range(4)
+KINDS = list(itertools.product(LATTICES, (FP64, FP64_12, FP32, FP16), range(1, 17), (0, 1)))
+
+
+@pytest.fixture(scope="module")
+def probe(tmp_path_factory):
+    d = tmp_path_factory.mktemp("shapes")
+    src, so = str(d / "probe.cpp"), str(d / "probe.so")
+    with open(src, "w") as f:
+        f.write(PROBE)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, src, "-o", so],
+                   check=True)
+    return ctypes.CDLL(so)
+
+
+def _dims(d):
+    return (ctypes.c_int * 4)(*d)
+
+
+def _shape(fn, *args):
+    out = (ctypes.c_int * 7)()
+    fn(*args, out)
+    return tuple(out)
+
+
+def test_defaults_are_accepted(probe):
+    for d, prec, nrhs, both in KINDS:
+        for clover in (0, 1):
+            s = _shape(probe.probe_default, _dims(d), prec, nrhs, both, clover)
+            assert probe.probe_valid(_dims(d), prec, nrhs, (ctypes.c_int * 7)(*s)), \
+                (d, prec, nrhs, both, clover, s)
+        s = _shape(probe.probe_plain, _dims(d), prec, nrhs, both)
+        assert s[6] != 2 and probe.probe_valid(_dims(d), prec, nrhs, (ctypes.c_int * 7)(*s))
