@@ -29,9 +29,9 @@ struct Loc {
 
 // The parity block of a lane is blockIdx.y, so every view is wavefront-uniform.
 template <SpinorFmt F>
-__device__ __forceinline__ SpinorBlock<F, true> view(const void *base, size_t bb, const Loc &l,
+__device__ __forceinline__ SpinorBlock<F, kWalk> view(const void *base, size_t bb, const Loc &l,
                                                      int S, int R) {
-    return SpinorBlock<F, true>((const char *)base + l.blk * bb, S, R);
+    return SpinorBlock<F, kWalk>((const char *)base + l.blk * bb, S, R);
 }
 
 // Generic grid-stride driver over one parity block per grid row (blockIdx.y):

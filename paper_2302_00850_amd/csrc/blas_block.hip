@@ -26,7 +26,7 @@ constexpr int kGramMaxBlocks = 2048;  // Gram partial rows (2 n^2 doubles each) 
 
 // element e (= i * n + b) of component c in compute precision T (FP16: times its scale)
 template <SpinorFmt F, typename T>
-__device__ __forceinline__ cpx<T> load_elem(const SpinorBlock<F, true> &v, int c, uint32_t e) {
+__device__ __forceinline__ cpx<T> load_elem(const SpinorBlock<F, kWalk> &v, int c, uint32_t e) {
     using E = typename SpinorT<F>::elem;
     const E h = bload<E, kCpolNT>(v.comp(c), e * (uint32_t)sizeof(E));
     if constexpr (F == SpinorFmt::F16) {
@@ -38,7 +38,7 @@ __device__ __forceinline__ cpx<T> load_elem(const SpinorBlock<F, true> &v, int c
 }
 
 template <SpinorFmt F, typename T>
-__device__ __forceinline__ void store_elem(const SpinorBlock<F, true> &v, int c, uint32_t e,
+__device__ __forceinline__ void store_elem(const SpinorBlock<F, kWalk> &v, int c, uint32_t e,
                                            cpx<T> z) {
     static_assert(F != SpinorFmt::F16, "element stores are for FP32 / FP64 blocks");
     using E = typename SpinorT<F>::elem;
@@ -102,8 +102,8 @@ __global__ void __launch_bounds__(256) gram_kernel(const void *A, const void *B,
     constexpr int W = kUnitSites * N;
     extern __shared__ double lds[];
     __shared__ cpx<T> sa[2][W];
-    const SpinorBlock<FA, true> va(A, S, N);
-    const SpinorBlock<FB, true> vb(B, S, N);
+    const SpinorBlock<FA, kWalk> va(A, S, N);
+    const SpinorBlock<FB, kWalk> vb(B, S, N);
     const int t = threadIdx.x, b = t % N, s0 = t - b;
     double acc[2 * N];
 #pragma unroll
@@ -136,8 +136,8 @@ __global__ void __launch_bounds__(256) block_axpy_kernel(void *X, const void *P,
     extern __shared__ double lds[];
     __shared__ cpx<TX> sp[2][W], sq[2][W];
     __shared__ cpx<TX> sr[GRAM ? 2 : 1][GRAM ? W : 1];
-    const SpinorBlock<FX, true> vx(X, S, N), vr(R, S, N);
-    const SpinorBlock<FP, true> vp(P, S, N), vq(Q, S, N);
+    const SpinorBlock<FX, kWalk> vx(X, S, N), vr(R, S, N);
+    const SpinorBlock<FP, kWalk> vp(P, S, N), vq(Q, S, N);
     const int t = threadIdx.x, b = t % N, s0 = t - b;
     cpx<TX> f[N];
     load_column<N>(al, b, f);
@@ -178,8 +178,8 @@ __global__ void __launch_bounds__(256) block_xpay_kernel(void *Pn, const void *R
     using TP = typename SpinorT<FP>::real;
     constexpr int W = kUnitSites * N;
     __shared__ cpx<TP> sp[2][W];
-    const SpinorBlock<FR, true> vr(R, S, N);
-    const SpinorBlock<FP, true> vp(P, S, N), vo(Pn, S, N);
+    const SpinorBlock<FR, kWalk> vr(R, S, N);
+    const SpinorBlock<FP, kWalk> vp(P, S, N), vo(Pn, S, N);
     const int t = threadIdx.x, b = t % N, s0 = t - b;
     cpx<TP> f[N];
     load_column<N>(be, b, f);
@@ -202,8 +202,8 @@ __global__ void __launch_bounds__(256) block_xpay_kernel(void *Pn, const void *R
 template <SpinorFmt FR>
 __global__ void __launch_bounds__(256) block_xpay_h_kernel(void *Pn, const void *R, const void *P,
                                                            const double *be, int S, int n) {
-    const SpinorBlock<FR, true> vr(R, S, n);
-    const SpinorBlock<SpinorFmt::F16, true> vp(P, S, n), vo(Pn, S, n);
+    const SpinorBlock<FR, kWalk> vr(R, S, n);
+    const SpinorBlock<SpinorFmt::F16, kWalk> vp(P, S, n), vo(Pn, S, n);
     const uint32_t total = (uint32_t)S * n;
     for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < total;
          t += gridDim.x * blockDim.x) {

@@ -202,26 +202,37 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_u(const void *base, uint32
                                              0x00020000);
 }
 
-// The arrays of one base a fixed stride apart, taken in order.  Base and stride are made
-// opaque here, so that the 64-bit base of each array is one scalar addition next to its
-// access; otherwise the compiler computes the bases of all arrays of all fields before the
-// site loop, keeps hundreds of scalar registers' worth of them in vector lanes, and spends
-// a readlane or two on every load.
-// UNI: the base is the same for every lane of a wavefront (else it is left alone).
-// FP64 hop with xpay: 304 -> 67 spilled scalar registers, M^dag M 32^3 x 64 1130 -> 1109 us;
-// 16^3 x 32 M^dag M x = b 34.5 -> 33.4 ms.
-template <bool UNI = true>
+// The arrays of one base a fixed stride apart, taken in order.  How their bases are formed:
+//   kPerLane  base may differ between the lanes of a wavefront
+//   kWalk     same base for all lanes.  Base and stride are made opaque here, so that the
+//             64-bit base of each array is one scalar addition next to its access; otherwise
+//             the compiler computes the bases of all arrays of all fields before the site
+//             loop, keeps hundreds of scalar registers' worth of them in vector lanes, and
+//             spends a readlane or two on every load.  FP64 hop with xpay: 304 -> 67 spilled
+//             scalar registers, M^dag M 32^3 x 64 1130 -> 1109 us; 16^3 x 32 M^dag M x = b
+//             34.5 -> 33.4 ms; FLIC FP64 M 32^3 x 64, 12 rhs, 8.68 -> 7.02 ms
+//   kBases    same base for all lanes, each array's base computed from it and made opaque:
+//             the additions do not wait for one another.  For the FP32 FLIC hops, which take
+//             48 link arrays per site: 32^3 x 64, 12 rhs, D_eo D_oe 3.15 -> 2.95 ms and M
+//             3.21 -> 3.00 ms, one rhs M 352 -> 316 us against kWalk
+constexpr int kPerLane = 0, kWalk = 1, kBases = 2;
+
+template <int M = kWalk>
 struct ArrayWalk {
     const char *b;
     uint64_t stride;
     uint32_t bytes;
+    uint32_t k = 0;  // arrays taken (kBases)
     __device__ __forceinline__ ArrayWalk(const void *base, uint64_t stride_bytes, uint32_t array_bytes)
         : b((const char *)base), stride(stride_bytes), bytes(array_bytes) {
-        if constexpr (UNI) asm volatile("" : "+s"(b), "+s"(stride));
+        if constexpr (M == kWalk) asm volatile("" : "+s"(b), "+s"(stride));
     }
     __device__ __forceinline__ __amdgpu_buffer_rsrc_t next() {
-        const __amdgpu_buffer_rsrc_t r =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(b), (short)0, (int)bytes, 0x00020000);
+        if constexpr (M == kBases) {
+            const char *q = b + (size_t)k++ * stride;
+            return buf_u(q, bytes);
+        }
+        const __amdgpu_buffer_rsrc_t r = buf(b, bytes);
         b += stride;
         return r;
     }
@@ -280,9 +291,9 @@ __device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, uint32_t off, c
     }
 }
 
-// View of one parity block of a packed spinor field.  UNI: the block base is the
-// same for every lane of a wavefront (true in the hop kernels).
-template <SpinorFmt F, bool UNI = false>
+// View of one parity block of a packed spinor field.  M: how the bases of its component
+// arrays are formed (see ArrayWalk).
+template <SpinorFmt F, int M = kPerLane>
 struct SpinorBlock {
     using E = typename SpinorT<F>::elem;
     using R = typename SpinorT<F>::real;
@@ -297,15 +308,15 @@ struct SpinorBlock {
     }
 
     __device__ __forceinline__ __amdgpu_buffer_rsrc_t comp(int c) const {
-        if constexpr (UNI) return buf_u(data + (size_t)c * SR, SR * (uint32_t)sizeof(E));
+        if constexpr (M != kPerLane) return buf_u(data + (size_t)c * SR, SR * (uint32_t)sizeof(E));
         return buf(data + (size_t)c * SR, SR * (uint32_t)sizeof(E));
     }
     // the 12 component arrays in order
-    __device__ __forceinline__ ArrayWalk<UNI> comps() const {
-        return ArrayWalk<UNI>(data, (uint64_t)SR * sizeof(E), SR * (uint32_t)sizeof(E));
+    __device__ __forceinline__ ArrayWalk<M> comps() const {
+        return ArrayWalk<M>(data, (uint64_t)SR * sizeof(E), SR * (uint32_t)sizeof(E));
     }
     __device__ __forceinline__ __amdgpu_buffer_rsrc_t nrm() const {
-        if constexpr (UNI) return buf_u(norm, SR * 4u);
+        if constexpr (M != kPerLane) return buf_u(norm, SR * 4u);
         return buf(norm, SR * 4u);
     }
 
@@ -464,25 +475,25 @@ __device__ __forceinline__ void rebuild_row2(cpx<T> u[3][3]) {
 
 // The chunk arrays of U_mu on parity p, in order.  The stride of the arrays is opaque before
 // the first base is formed from it, for the reason given at ArrayWalk.
-template <LinkFmt F, bool UNI>
-__device__ __forceinline__ ArrayWalk<UNI> link_arrays(const void *gauge, int S, int p, int mu) {
+template <LinkFmt F, int M>
+__device__ __forceinline__ ArrayWalk<M> link_arrays(const void *gauge, int S, int p, int mu) {
     using CH = typename LinkT<F>::chunk;
     uint64_t stride = (uint64_t)S * sizeof(CH);
-    if constexpr (UNI) asm volatile("" : "+s"(stride));
-    return ArrayWalk<UNI>((const char *)gauge + (uint64_t)((p * 4 + mu) * link_chunks(F)) * stride,
+    if constexpr (M == kWalk) asm volatile("" : "+s"(stride));
+    return ArrayWalk<M>((const char *)gauge + (uint64_t)((p * 4 + mu) * link_chunks(F)) * stride,
                           stride, (uint32_t)S * (uint32_t)sizeof(CH));
 }
 
 // Load U_mu at checkerboard site i of parity p; row 2 rebuilt as conj(row0 x row1)
 // for the 12-real formats.
-// UNI: parity p is the same for every lane of the wavefront.  CP: cache policy.
-template <LinkFmt F, typename T, bool UNI = true, int CP = 0>
+// M: see ArrayWalk (kPerLane: the parity may differ between lanes).  CP: cache policy.
+template <LinkFmt F, typename T, int M = kWalk, int CP = 0>
 __device__ __forceinline__ void load_link(const void *gauge, int S, int p, int mu, uint32_t i,
                                           cpx<T> u[3][3]) {
     using CH = typename LinkT<F>::chunk;
     constexpr int N = link_chunks(F);
     const uint32_t off = i * (uint32_t)sizeof(CH);
-    ArrayWalk<UNI> w = link_arrays<F, UNI>(gauge, S, p, mu);
+    ArrayWalk<M> w = link_arrays<F, M>(gauge, S, p, mu);
     if constexpr (F == LinkFmt::F64_18 || F == LinkFmt::F64_12) {
 #pragma unroll
         for (int k = 0; k < N; ++k) {
@@ -666,7 +677,7 @@ __device__ __forceinline__ void load_link_h2(const void *gauge, int S, int p, in
     using CH = LinkT<LinkFmt::F16_12>::chunk;
     const uint32_t off = i * (uint32_t)sizeof(CH);
     h2 u[3][3];
-    auto w = link_arrays<LinkFmt::F16_12, true>(gauge, S, p, mu);
+    auto w = link_arrays<LinkFmt::F16_12, kWalk>(gauge, S, p, mu);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         const CH c = bload<CH>(w.next(), off);
@@ -811,14 +822,14 @@ __device__ __forceinline__ void read_staged(const uint32_t *src, cpx<float> u[3]
 // ------------------------------------------------------------------ clover
 
 // out = C in, C = two Hermitian 6x6 chiral blocks (spins {0,1} and {2,3}).
-template <typename CR, typename T>
+template <typename CR, typename T, int M = kWalk>
 __device__ __forceinline__ void clover_apply(const void *clov, int S, int p, uint32_t i,
                                              const cpx<T> in[12], cpx<T> out[12]) {
     struct pair { CR a, b; };
     const uint32_t off = i * (uint32_t)sizeof(pair);
     uint64_t stride = (uint64_t)S * sizeof(pair);
-    asm volatile("" : "+s"(stride));
-    ArrayWalk<> w((const char *)clov + (uint64_t)(p * 36) * stride, stride,
+    if constexpr (M == kWalk) asm volatile("" : "+s"(stride));
+    ArrayWalk<M> w((const char *)clov + (uint64_t)(p * 36) * stride, stride,
                   (uint32_t)S * (uint32_t)sizeof(pair));
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk) {

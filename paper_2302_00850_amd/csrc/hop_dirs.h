@@ -56,7 +56,7 @@ __device__ __forceinline__ void sum_spin(T sg_f, const cpx<T> (*W)[6][kDirsSites
 
 // the half spinor of direction (MU, DIR) into w
 template <int MU, int DIR, SpinorFmt SF, LinkFmt LF, bool RPH>
-__device__ __forceinline__ void half_spinor(const HopArgs &a, const SpinorBlock<SF, true> &in,
+__device__ __forceinline__ void half_spinor(const HopArgs &a, const SpinorBlock<SF, kWalk> &in,
                                             int p, uint32_t i, const int x[4], uint32_t j,
                                             typename SpinorT<SF>::real sg_f,
                                             cpx<typename SpinorT<SF>::real> (*w)[kDirsSites],
@@ -185,7 +185,7 @@ __global__ void __launch_bounds__(8 * kDirsSites) hop_dirs_kernel(const HopArgs 
         if (d < 4 && a.cg_pi_n) partial_terms(a.cg_pi, a.cg_pi_n, (int)threadIdx.x, tp);
     }
     if (valid) {
-        const SpinorBlock<SF, true> in((const char *)a.in + no, g.S, a.nrhs);
+        const SpinorBlock<SF, kWalk> in((const char *)a.in + no, g.S, a.nrhs);
         int x[4];
         site_coords(g, i, p, x);
         switch (d) {

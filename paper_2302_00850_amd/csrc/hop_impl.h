@@ -65,8 +65,8 @@ struct Fetched {
 // loads in flight while it does arithmetic (the register fences between directions are
 // scheduling barriers: without this the loads of a direction would only start after
 // the previous direction finished).
-template <int MU, int DIR, SpinorFmt SF, int RPT>
-__device__ __forceinline__ void hop_fetch(const HopArgs &a, const SpinorBlock<SF, true> &in,
+template <int MU, int DIR, SpinorFmt SF, int RPT, int M>
+__device__ __forceinline__ void hop_fetch(const HopArgs &a, const SpinorBlock<SF, M> &in,
                                           uint32_t i, const int x[4], uint32_t j,
                                           Fetched<SF, RPT> &f) {
     const Geom &g = a.g;
@@ -83,8 +83,8 @@ __device__ __forceinline__ void hop_fetch(const HopArgs &a, const SpinorBlock<SF
 }
 
 // the spinor of site n (rhs j) into f, one rhs per lane (FP16: raw halves and scale)
-template <SpinorFmt SF>
-__device__ __forceinline__ void fetch_site(const SpinorBlock<SF, true> &in, uint32_t n, uint32_t j,
+template <SpinorFmt SF, int M>
+__device__ __forceinline__ void fetch_site(const SpinorBlock<SF, M> &in, uint32_t n, uint32_t j,
                                            Fetched<SF, 1> &f) {
     f.n = n;
     if constexpr (SF == SpinorFmt::F16) {
@@ -93,6 +93,12 @@ __device__ __forceinline__ void fetch_site(const SpinorBlock<SF, true> &in, uint
         typename SpinorT<SF>::real one;
         in.load_unscaled(n, j, f.s[0], &one);
     }
+}
+
+// How the bases of the arrays are formed (see ArrayWalk).
+template <SpinorFmt SF, bool FL>
+constexpr int hop_bases() {
+    return FL && SF == SpinorFmt::F32 ? kBases : kWalk;
 }
 
 // The order in which the eight directions d = 2 mu + dir are added: t backward first,
@@ -132,8 +138,9 @@ __device__ __forceinline__ void hop_dir(const HopArgs &a, int p, uint32_t i, con
         C u[3][3], fl[3][3];
         const int lpar = dir == 0 ? p : 1 - p;
         const uint32_t li = dir == 0 ? i : n;
-        load_link<LF, T>(a.gauge, g.S, lpar, mu, li, u);
-        load_link<LF, T>(a.gauge_fat, g.S, lpar, mu, li, fl);
+        constexpr int M = hop_bases<SF, FL>();
+        load_link<LF, T, M>(a.gauge, g.S, lpar, mu, li, u);
+        load_link<LF, T, M>(a.gauge_fat, g.S, lpar, mu, li, fl);
         // in place: fl = F + U (with the projector 1 + sg g_mu), u = F - U (1 - sg g_mu)
 #pragma unroll
         for (int r0 = 0; r0 < 3; ++r0)
@@ -193,7 +200,7 @@ __device__ __forceinline__ void hop_dir(const HopArgs &a, int p, uint32_t i, con
         if constexpr (SHL && LF == LinkFmt::F32_12)
             read_staged(staged + (2 * MU + DIR) * kStageWords, u);
         else if (a.groups == 1 && !a.both)  // one lane per site: each link is read once
-            load_link<LF, T, true, kCpolNT>(a.gauge, g.S, dir == 0 ? p : 1 - p, mu,
+            load_link<LF, T, kWalk, kCpolNT>(a.gauge, g.S, dir == 0 ? p : 1 - p, mu,
                                             dir == 0 ? i : n, u);
         else
             load_link<LF, T>(a.gauge, g.S, dir == 0 ? p : 1 - p, mu, dir == 0 ? i : n, u);
@@ -277,7 +284,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK ? 3
     const int p = a.both ? (int)(pch & 1u) : a.parity;
     const size_t po = a.both && p ? a.pstride : 0, no = a.both && !p ? a.pstride : 0;
     auto view = [&](const void *base, size_t o) {
-        return SpinorBlock<SF, true>((const char *)(base ? base : a.out) + o, g.S, a.nrhs);
+        return SpinorBlock<SF, hop_bases<SF, FL>()>((const char *)(base ? base : a.out) + o, g.S,
+                                                    a.nrhs);
     };
     const auto in = view(a.in, no), out = view(a.out, po), xin = view(a.x, po);
     const auto cgr = view(a.cg_r, po);
@@ -432,14 +440,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK ? 3
                 if constexpr (SCL)
                     clover_apply_lds<T>(cstaged, d, o);
                 else
-                    clover_apply<CR, T>(a.clov, g.S, p, i, d, o);
+                    clover_apply<CR, T, hop_bases<SF, FL>()>(a.clov, g.S, p, i, d, o);
             } else if constexpr (EPI == EPI_CLOV_XPAY || EPI == EPI_CLOV_XPAY_CG) {
                 C xv[12], cx[12];
                 xin.load(i, rr, xv);
                 if constexpr (SCL)
                     clover_apply_lds<T>(cstaged, xv, cx);
                 else
-                    clover_apply<CR, T>(a.clov, g.S, p, i, xv, cx);
+                    clover_apply<CR, T, hop_bases<SF, FL>()>(a.clov, g.S, p, i, xv, cx);
 #pragma unroll
                 for (int c = 0; c < 12; ++c) o[c] = add_s(cx[c], ca, o[c]);
             } else if constexpr (EPI == EPI_XPAY_CLOV) {
@@ -450,7 +458,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK ? 3
                 if constexpr (SCL)
                     clover_apply_lds<T>(cstaged, xv, o);
                 else
-                    clover_apply<CR, T>(a.clov, g.S, p, i, xv, o);
+                    clover_apply<CR, T, hop_bases<SF, FL>()>(a.clov, g.S, p, i, xv, o);
             }
             if constexpr (CG) {
                 // r -= alpha o; o becomes the stored r (for the norm)
