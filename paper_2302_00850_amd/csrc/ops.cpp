@@ -203,24 +203,38 @@ int write_table(const std::string &path, const std::map<std::string, TuneEntry> 
     return rename(tmp.c_str(), path.c_str()) == 0 ? (int)t.size() : -1;
 }
 
-// The default shape, or the one COLA_HOP_SHAPE pins.
+// Measurement knob: COLA_HOP_SHAPE="rpt,sites_per_block,grid,tchunk[,tile_y,tile_z[,stage]]"
+// pins the untuned launch shape (ignored unless every field is valid for this launch).
+bool pinned_entry(const Geom &g, int prec, int nrhs, TuneEntry *out) {
+    const char *env = getenv("COLA_HOP_SHAPE");
+    if (!env) return false;
+    TuneEntry e;
+    e.stage = -1;
+    const int n = sscanf(env, "%d,%d,%d,%d,%d,%d,%d", &e.rpt, &e.sites_per_block, &e.grid,
+                         &e.tchunk, &e.tile_y, &e.tile_z, &e.stage);
+    if ((n != 4 && n != 6 && n != 7) || !shape_valid(g, prec, nrhs, e)) return false;
+    // staging as asked where possible, else the default rule
+    const bool ok = stage_ok(g, prec, nrhs, e);
+    if (e.stage != 2) e.stage = e.stage < 0 ? (ok ? 1 : 0) : (e.stage && ok ? 1 : 0);
+    *out = e;
+    return true;
+}
+
+// The shape of a hop that is neither tuned nor stored.
 TuneEntry untuned_entry(const Geom &g, int prec, int nrhs, bool both, bool clover) {
-    TuneEntry t = default_entry(g, prec, nrhs, both, clover);
-    // Measurement knob: COLA_HOP_SHAPE="rpt,sites_per_block,grid,tchunk" pins the
-    // untuned launch shape (ignored unless every field is valid for this launch).
-    if (const char *env = getenv("COLA_HOP_SHAPE")) {
-        TuneEntry e;
-        e.stage = -1;
-        const int n = sscanf(env, "%d,%d,%d,%d,%d,%d,%d", &e.rpt, &e.sites_per_block, &e.grid,
-                             &e.tchunk, &e.tile_y, &e.tile_z, &e.stage);
-        if ((n == 4 || n == 6 || n == 7) && shape_valid(g, prec, nrhs, e)) {
-            // staging as asked where possible, else the default rule
-            const bool ok = stage_ok(g, prec, nrhs, e);
-            if (e.stage != 2) e.stage = e.stage < 0 ? (ok ? 1 : 0) : (e.stage && ok ? 1 : 0);
-            t = e;
-        }
+    TuneEntry t;
+    if (pinned_entry(g, prec, nrhs, &t)) return t;
+    return default_entry(g, prec, nrhs, both, clover);
+}
+
+// The shape of a FLIC hop: shapes tuned or stored are those of the other kernels.
+TuneEntry flic_shape(const Geom &g, int prec, int nrhs, bool both) {
+    TuneEntry t;
+    if (pinned_entry(g, prec, nrhs, &t)) {
+        if (t.stage == 1) t.stage = 0;
+        if (flic_ok(g, prec, nrhs, t)) return t;
     }
-    return t;
+    return flic_entry(g, prec, nrhs, both);
 }
 
 // One hop launch in shape te; with a norm, the partial-sum reduction follows unless
@@ -312,7 +326,7 @@ int fill_and_launch(cola_handle_t *h, const HopCall &c, int prec, int nrhs, cons
 // does not fit this launch; load: read the file once per process if not yet read.
 bool stored_entry(cola_handle_t *h, const std::string &key, int prec, int nrhs, bool load,
                   TuneEntry *out) {
-    if (getenv("COLA_HOP_SHAPE") || h->flic) return false;
+    if (getenv("COLA_HOP_SHAPE")) return false;
     TuneStore &ts = tune_store();
     std::lock_guard<std::mutex> lock(ts.mu);
     if (!ts.loaded && load) {
@@ -413,9 +427,11 @@ int hop(cola_handle_t *h, const HopCall &call, int prec, int nrhs, hipStream_t s
         tune_key(h, prec, nrhs, key_epi, c.norm_result != nullptr) + (c.both ? ":b" : "");
     TuneEntry te;
     auto it = h->tune.find(key);
-    if (it != h->tune.end() && (h->tune_mode != 2 || cg || c.fixed)) {
+    if (h->flic) {
+        te = flic_shape(h->g, prec, nrhs, c.both);
+    } else if (it != h->tune.end() && (h->tune_mode != 2 || cg || c.fixed)) {
         te = it->second;
-    } else if (h->tune_mode >= 1 && !cg && !c.fixed && !h->flic) {
+    } else if (h->tune_mode >= 1 && !cg && !c.fixed) {
         COLA_TRY(tune_hop(h, c, prec, nrhs, &te, st));
         h->tune[key] = te;
         // into the process-wide table and its file (a failed write only loses the cache)
@@ -431,12 +447,6 @@ int hop(cola_handle_t *h, const HopCall &call, int prec, int nrhs, hipStream_t s
     // a resident grid needs an occupancy query (cached in a host map): the fixed mode
     // takes the plain grid instead, which gives bitwise the same output
     if (c.fixed && te.grid < 0) te.grid = 0;
-    // FLIC hops: one rhs per lane, both links loaded per lane
-    if (h->flic) {
-        if (te.stage == 2) te = plain_entry(h->g, prec, nrhs, c.both);
-        te.rpt = 1;
-        te.stage = 0;
-    }
     // the other kernels take ready scalars
     if (te.stage != 2 && c.cg_pi_n > 0) {
         void *s;

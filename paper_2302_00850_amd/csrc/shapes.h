@@ -159,6 +159,40 @@ inline TuneEntry default_entry(const Geom &g, int prec, int nrhs, bool both, boo
     return plain_entry(g, prec, nrhs, both);
 }
 
+// The FLIC hops load both links per lane, one rhs per lane, and neither stage links nor walk
+// time: blocks of one wavefront where the rhs fill it, tiles of 1024 sites, or with both
+// parities in FP64 512 up to 8 rhs and 256 beyond.  One and three rhs as plain_entry, and in
+// FP32 every count that does not divide 64 (12 rhs: within 2% of the best of 80 shapes).
+// FP64 from five rhs on: blocks of at most one wavefront, with both parities of whole
+// wavefronts if some power of two sites makes them (12 rhs: 16 sites), and chunks of 4
+// timeslices where 4 rounds of resident blocks remain.  Against plain_entry, D_eo D_oe and M
+// at 32^3 x 64: FP64 12 rhs 8.68 -> 7.93 and 7.06 -> 6.61 ms, 8 rhs 4.99 -> 4.41 and 4.45 ->
+// 3.93, 4 rhs 2.64 -> 2.44 and 2.25 -> 2.07; FP32 4 rhs 1080 -> 1068 and 988 -> 973 us, at
+// 12^3 x 16 M 8% less.
+inline TuneEntry flic_entry(const Geom &g, int prec, int nrhs, bool both) {
+    TuneEntry t = plain_entry(g, prec, nrhs, both);
+    t.stage = 0;
+    if (nrhs == 1) return t;
+    const bool f64 = prec == COLA_FP64 || prec == COLA_FP64_12;
+    int T = 64;
+    while (T * nrhs > 64) T /= 2;
+    if (T * nrhs != 64 && (!f64 || nrhs == 3)) return t;
+    if (T * nrhs != 64 && both)
+        for (int w = 2 * T; w * nrhs <= 256; w *= 2)
+            if (w * nrhs % 64 == 0) T = w;
+    t.sites_per_block = T;
+    best_tile(g, !f64 || !both || nrhs == 2 ? 1024 : nrhs <= 8 ? 512 : 256, &t.tile_y, &t.tile_z);
+    const double blocks = (double)g.Vh * (both ? 2 : 1) / T;
+    t.tchunk = f64 && nrhs >= 5 && blocks / 4 >= 4 * 1024.0 ? 4 : 1;
+    while (g.L[3] % t.tchunk) t.tchunk /= 2;
+    return t;
+}
+
+// A shape that the FLIC hops take.
+inline bool flic_ok(const Geom &g, int prec, int nrhs, const TuneEntry &t) {
+    return t.rpt == 1 && t.stage == 0 && shape_valid(g, prec, nrhs, t);
+}
+
 // The shapes that the tuner times.
 inline std::vector<TuneEntry> tune_candidates(const Geom &g, int prec, int nrhs) {
     std::vector<TuneEntry> cand;

@@ -26,6 +26,9 @@ void probe_default(const int *d, int prec, int nrhs, int both, int clover, int *
 void probe_plain(const int *d, int prec, int nrhs, int both, int *o) {
     put(plain_entry(make_geom(d), prec, nrhs, both), o);
 }
+void probe_flic(const int *d, int prec, int nrhs, int both, int *o) {
+    put(flic_entry(make_geom(d), prec, nrhs, both), o);
+}
 int probe_valid(const int *d, int prec, int nrhs, const int *s) {
     TuneEntry t;
     t.rpt = s[0], t.sites_per_block = s[1], t.grid = s[2], t.tchunk = s[3];
@@ -71,3 +74,14 @@ def test_defaults_are_accepted(probe):
                 (d, prec, nrhs, both, clover, s)
         s = _shape(probe.probe_plain, _dims(d), prec, nrhs, both)
         assert s[6] != 2 and probe.probe_valid(_dims(d), prec, nrhs, (ctypes.c_int * 7)(*s))
+
+
+def test_flic_defaults_are_shapes_of_the_flic_kernel(probe):
+    """One rhs per lane, links neither staged nor split over wavefronts, and a block of at
+    most 256 lanes with that."""
+    for d, prec, nrhs, both in KINDS:
+        if prec == FP16:
+            continue
+        s = _shape(probe.probe_flic, _dims(d), prec, nrhs, both)
+        assert s[0] == 1 and s[6] == 0 and s[1] * nrhs <= 256, (d, prec, nrhs, both, s)
+        assert probe.probe_valid(_dims(d), prec, nrhs, (ctypes.c_int * 7)(*s))
