@@ -220,6 +220,8 @@ bool pinned_entry(const Geom &g, int prec, int nrhs, TuneEntry *out) {
     return true;
 }
 
+bool clover_epilogue(int epi) { return epi != EPI_NONE && epi != EPI_XPAY && epi != EPI_XPAY_CG; }
+
 // The shape of a hop that is neither tuned nor stored.
 TuneEntry untuned_entry(const Geom &g, int prec, int nrhs, bool both, bool clover) {
     TuneEntry t;
@@ -349,7 +351,8 @@ bool stored_entry(cola_handle_t *h, const std::string &key, int prec, int nrhs, 
 
 int tune_hop(cola_handle_t *h, const HopCall &c, int prec, int nrhs, TuneEntry *best,
              hipStream_t st) {
-    std::vector<TuneEntry> cand = tune_candidates(h->g, prec, nrhs);
+    std::vector<TuneEntry> cand =
+        tune_candidates(h->g, prec, nrhs, c.both, clover_epilogue(c.epi));
     hipEvent_t e0, e1;
     COLA_HIP(h, hipEventCreate(&e0));
     COLA_HIP(h, hipEventCreate(&e1));
@@ -441,8 +444,7 @@ int hop(cola_handle_t *h, const HopCall &call, int prec, int nrhs, hipStream_t s
         const std::string path = tune_cache_path();
         if (!path.empty()) write_table(path, ts.table);
     } else if (!stored_entry(h, key, prec, nrhs, !c.fixed, &te)) {
-        te = untuned_entry(h->g, prec, nrhs, c.both,
-                           c.epi != EPI_NONE && c.epi != EPI_XPAY && c.epi != EPI_XPAY_CG);
+        te = untuned_entry(h->g, prec, nrhs, c.both, clover_epilogue(c.epi));
     }
     // a resident grid needs an occupancy query (cached in a host map): the fixed mode
     // takes the plain grid instead, which gives bitwise the same output

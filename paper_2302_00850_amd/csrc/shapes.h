@@ -193,9 +193,29 @@ inline bool flic_ok(const Geom &g, int prec, int nrhs, const TuneEntry &t) {
     return t.rpt == 1 && t.stage == 0 && shape_valid(g, prec, nrhs, t);
 }
 
-// The shapes that the tuner times.
-inline std::vector<TuneEntry> tune_candidates(const Geom &g, int prec, int nrhs) {
+// The shapes that the tuner times: the defaults first, so that a tuned shape is never a slower
+// one; blocks by rhs per lane in plain order and chunks, with power-of-two tiles and, one rhs
+// per lane, the tiles that the defaults are made of; each also staged where that applies.
+inline std::vector<TuneEntry> tune_candidates(const Geom &g, int prec, int nrhs, bool both,
+                                              bool clover) {
     std::vector<TuneEntry> cand;
+    const auto add = [&](const TuneEntry &t) {
+        for (const TuneEntry &c : cand)
+            if (c.rpt == t.rpt && c.sites_per_block == t.sites_per_block && c.grid == t.grid &&
+                c.tchunk == t.tchunk && c.tile_y == t.tile_y && c.tile_z == t.tile_z &&
+                c.stage == t.stage)
+                return;
+        cand.push_back(t);
+    };
+    add(default_entry(g, prec, nrhs, both, clover));
+    add(plain_entry(g, prec, nrhs, both));
+    {
+        TuneEntry t;
+        t.stage = 2;
+        t.sites_per_block = kDirsSites / nrhs;
+        if (dirs_ok(g, prec, nrhs, t)) add(t);
+    }
+    std::vector<TuneEntry> base;
     for (int rpt : {1, 2, 3, 4}) {
         if (nrhs % rpt) continue;
         if (rpt > 1 && (prec == COLA_FP64 || prec == COLA_FP64_12)) continue;
@@ -206,49 +226,44 @@ inline std::vector<TuneEntry> tune_candidates(const Geom &g, int prec, int nrhs)
         for (int T : {4, 8, 16, 32, 64, 128, 256}) {
             if (T * G > 256 || T * G < 64) continue;
             if (whole && (T * G) % 64 != 0) continue;
+            TuneEntry t;
+            t.rpt = rpt;
+            t.sites_per_block = T;
             for (int tc : {1, 2, 4, 8, 16}) {
                 if (g.L[3] % tc) continue;
+                t.tchunk = tc;
                 for (int grid : {0, -1}) {
-                    TuneEntry t;
-                    t.rpt = rpt;
-                    t.sites_per_block = T;
                     t.grid = grid;
-                    t.tchunk = tc;
-                    cand.push_back(t);
+                    base.push_back(t);
                 }
             }
+            t.tchunk = 1;
+            t.grid = 0;
             const int tiles[][2] = {{4, 4}, {8, 4}, {4, 8}, {8, 8}, {16, 8}, {8, 16}, {16, 16}};
             for (const auto &tl : tiles) {
-                if (!tile_ok(g, tl[0], tl[1])) continue;
-                TuneEntry t;
-                t.rpt = rpt;
-                t.sites_per_block = T;
                 t.tile_y = tl[0];
                 t.tile_z = tl[1];
-                cand.push_back(t);
+                if (tile_ok(g, tl[0], tl[1])) base.push_back(t);
+            }
+            if (rpt > 1) continue;
+            for (int most : {288, 900, 1024, 2048, 4096, 8192}) {
+                best_tile(g, most, &t.tile_y, &t.tile_z);
+                base.push_back(t);
             }
         }
     }
-    {
-        TuneEntry t;
-        t.stage = 2;
-        t.sites_per_block = kDirsSites / nrhs;
-        if (dirs_ok(g, prec, nrhs, t)) cand.push_back(t);
-    }
-    // each shape also with the site's links staged in LDS, where that applies
-    const size_t n0 = cand.size();
-    for (size_t k = 0; k < n0; ++k) {
-        if (cand[k].stage == 2 || !stage_ok(g, prec, nrhs, cand[k])) continue;
-        TuneEntry t = cand[k];
+    for (const TuneEntry &b : base) add(b);
+    for (const TuneEntry &b : base) {
+        if (!stage_ok(g, prec, nrhs, b)) continue;
+        TuneEntry t = b;
         t.stage = 1;
-        cand.push_back(t);
+        add(t);
         // the time walk of staged FP32 / FP16 hops: tiles in chunks of 4 and 8 timeslices
         if ((prec == COLA_FP32 || prec == COLA_FP16) && t.rpt == 1 && t.tile_y > 0) {
             for (int tc : {4, 8}) {
                 if (g.L[3] % tc) continue;
-                TuneEntry w = t;
-                w.tchunk = tc;
-                cand.push_back(w);
+                t.tchunk = tc;
+                add(t);
             }
         }
     }

@@ -29,6 +29,11 @@ void probe_plain(const int *d, int prec, int nrhs, int both, int *o) {
 void probe_flic(const int *d, int prec, int nrhs, int both, int *o) {
     put(flic_entry(make_geom(d), prec, nrhs, both), o);
 }
+int probe_candidates(const int *d, int prec, int nrhs, int both, int clover, int *o, int most) {
+    const auto c = tune_candidates(make_geom(d), prec, nrhs, both, clover);
+    for (int k = 0; k < (int)c.size() && k < most; ++k) put(c[k], o + 7 * k);
+    return (int)c.size();
+}
 int probe_valid(const int *d, int prec, int nrhs, const int *s) {
     TuneEntry t;
     t.rpt = s[0], t.sites_per_block = s[1], t.grid = s[2], t.tchunk = s[3];
@@ -85,3 +90,20 @@ def test_flic_defaults_are_shapes_of_the_flic_kernel(probe):
         s = _shape(probe.probe_flic, _dims(d), prec, nrhs, both)
         assert s[0] == 1 and s[6] == 0 and s[1] * nrhs <= 256, (d, prec, nrhs, both, s)
         assert probe.probe_valid(_dims(d), prec, nrhs, (ctypes.c_int * 7)(*s))
+
+
+def test_tuner_times_the_defaults(probe):
+    """The default shape and the one-lane-per-(site, rhs) default are among the candidates, so
+    tuning cannot settle on a slower one; every candidate is a shape the kernels accept, and
+    none is timed twice."""
+    buf = (ctypes.c_int * (7 * 4096))()
+    for d, prec, nrhs, both in KINDS:
+        for clover in (0, 1):
+            n = probe.probe_candidates(_dims(d), prec, nrhs, both, clover, buf, 4096)
+            assert 0 < n <= 4096
+            cand = [tuple(buf[7 * k:7 * k + 7]) for k in range(n)]
+            assert len(set(cand)) == n
+            assert _shape(probe.probe_default, _dims(d), prec, nrhs, both, clover) in cand
+            assert _shape(probe.probe_plain, _dims(d), prec, nrhs, both) in cand
+            for s in cand:
+                assert probe.probe_valid(_dims(d), prec, nrhs, (ctypes.c_int * 7)(*s)), s
