@@ -436,14 +436,16 @@ int cola_reset_stats(cola_handle_t *h);
  * how lattice sites map to GPU threads, in its paragraph on the GPU execution model):
  * sites per block, rhs per thread, grid (natural or resident), time chunk, spatial tile
  * and LDS staging of the site's links.  Every shape gives bitwise the same result.
- * Keys are (lattice, precision, nrhs, epilogue, fused norm).
+ * Keys are (lattice, precision, nrhs, epilogue, fused norm, and ":b" for the hops of M and
+ * M^H, which compute both parities).
  * mode 0: off (defaults), 1: tune on first use of a key (each candidate timed on the
  * caller's buffers, so that first call takes longer), 2: re-tune every key.
  * Tuned shapes go into a per-handle table and into a process-wide table kept in a text
  * file ($COLA_TUNE_CACHE, empty for none; else $XDG_CACHE_HOME/cola/hop_tune.txt or
- * ~/.cache/cola/hop_tune.txt), one line per (device, key).  With tuning off, a hop takes
- * the handle's tuned shape, else the stored one (the file is read on the first hop of the
- * process), else the default: shapes tuned once are used by default afterwards.
+ * ~/.cache/cola/hop_tune.txt), one line per (device and library version, key).  With tuning
+ * off, a hop takes the handle's tuned shape, else the stored one (the file is read on the
+ * first hop of the process), else the default: shapes tuned once are used by default
+ * afterwards, until a version with other kernels ignores them.  FLIC hops are not tuned.
  * COLA_HOP_SHAPE (a measurement knob) overrides the stored shapes.
  * cola_tune_dump writes the handle's table as JSON text into buf (returns the length
  * needed, including the terminating NUL). */

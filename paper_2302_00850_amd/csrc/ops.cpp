@@ -154,10 +154,10 @@ void shape_for(const TuneEntry &t, int Vh, int nrhs, bool both, int *groups, int
 
 // ---- the persistent table of tuned shapes
 // Shared by every handle of the process and kept in a text file (one entry per line:
-// device tag, key, rpt, sites per block, grid, time chunk, tile y, tile z, staging, ms),
-// so that shapes tuned once are used by default afterwards, in this process and later
+// device and version tag, key, rpt, sites per block, grid, time chunk, tile y, tile z, staging,
+// ms), so that shapes tuned once are used by default afterwards, in this process and later
 // ones.  Every shape gives bitwise the same result, so a stale entry can only cost
-// time; entries that do not fit the launch are ignored.
+// time; entries of another version or that do not fit the launch are ignored.
 struct TuneStore {
     std::mutex mu;
     std::map<std::string, TuneEntry> table;

@@ -34,6 +34,11 @@ int probe_candidates(const int *d, int prec, int nrhs, int both, int clover, int
     for (int k = 0; k < (int)c.size() && k < most; ++k) put(c[k], o + 7 * k);
     return (int)c.size();
 }
+int probe_key(const char *arch, int num_cu, const char *key, char *o, int most) {
+    const std::string s = table_key(arch, num_cu, key);
+    strncpy(o, s.c_str(), most - 1);
+    return (int)s.size();
+}
 int probe_valid(const int *d, int prec, int nrhs, const int *s) {
     TuneEntry t;
     t.rpt = s[0], t.sites_per_block = s[1], t.grid = s[2], t.tchunk = s[3];
@@ -107,3 +112,22 @@ def test_tuner_times_the_defaults(probe):
             assert _shape(probe.probe_plain, _dims(d), prec, nrhs, both) in cand
             for s in cand:
                 assert probe.probe_valid(_dims(d), prec, nrhs, (ctypes.c_int * 7)(*s)), s
+
+
+def test_tables_of_earlier_kernels_are_not_used(probe):
+    """A line of a table written before the kernels and defaults changed (device, key, shape;
+    no version) does not answer a launch of today's library, and the keys still tell devices
+    and launches apart."""
+    def key(arch, cu, k):
+        buf = ctypes.create_string_buffer(256)
+        n = probe.probe_key(arch, cu, k, buf, 256)
+        assert n < 256
+        return buf.value
+    hop = b"hop:16x16x16x32:p2:r1:e1:n1"
+    line = b"gfx950:256 " + hop + b" 1 128 0 1 0 0 0 0.020000"
+    now = key(b"gfx950", 256, hop)
+    assert b" ".join(line.split()[:2]) != now
+    # what the file holds of it is read back as two words (of up to 127 and 159 bytes)
+    assert len(now.split()) == 2 and now.split()[1] == hop and len(now.split()[0]) < 128
+    others = [key(b"gfx950", 304, hop), key(b"gfx942", 256, hop), key(b"gfx950", 256, hop + b":b")]
+    assert len({now, *others}) == 4
