@@ -79,7 +79,7 @@ inline void best_tile(const Geom &g, int most, int *ty, int *tz) {
 // Launch shapes.  Tiles are walked through t, so that the timeslices in flight of a tile and
 // their links stay in one XCD's L2; the tile sizes below are where the times measured over
 // all divisors of 24^3 x 48, 32^3 x 64 and 48^3 x 96 are flat or lowest.
-inline TuneEntry plain_entry(const Geom &g, int prec, int nrhs, bool both) {
+inline TuneEntry plain_entry(const Geom &g, int prec, int nrhs, bool both, bool clover) {
     TuneEntry t;
     t.rpt = 1;
     const int G = nrhs;
@@ -108,10 +108,28 @@ inline TuneEntry plain_entry(const Geom &g, int prec, int nrhs, bool both) {
         best_tile(g, both && nrhs > 8 ? 288 : 900, &t.tile_y, &t.tile_z);
         return t;
     }
-    // FP32 and FP16: the site's links staged in LDS from four rhs on.  M, 20 x 18 x 14 x 30
-    // clover FP32: 5 rhs 114 us unstaged, 87 staged; 4 rhs 83 and 72; 3 rhs 63 unstaged, 68
-    // staged.  24^3 x 48: 6 rhs 493 and 403 us, 4 rhs 322 and 316.
-    t.stage = nrhs >= 4 && stage_ok(g, prec, nrhs, t) ? 1 : 0;
+    // FP32 and FP16: the site's links staged in LDS.  Four rhs without a clover block, in
+    // blocks of kStageSites sites walking time in chunks of 4 (one parity: where 4 rounds of
+    // resident blocks remain, else 2), if that leaves a block for each SIMD.  M and D_eo D_oe,
+    // unstaged and so: FP32 16^3 x 32 45.2 -> 41.1 and 53.7 -> 45.9 us, 24^3 x 48 254 -> 225
+    // and 249 -> 229, 32^3 x 64 798 -> 663 and 869 -> 716; FP16 31.9 -> 30.9 and 35.4 -> 35.6,
+    // 142 -> 128 and 157 -> 141, 468 -> 402 and 497 -> 434.  With clover blocks to stage as
+    // well M takes 315 and 323 us in FP32 at 24^3 x 48, and in FP16 191 and 240.
+    if (nrhs == 4 && !clover) {
+        TuneEntry s = t;
+        s.sites_per_block = kStageSites;
+        const double blocks = (double)g.Vh * (both ? 2 : 1) / kStageSites;
+        if (blocks / 2 >= 1024.0 && stage_ok(g, prec, nrhs, s)) {
+            s.stage = 1;
+            s.tchunk = blocks / 4 >= (both ? 1 : 4) * 1024.0 ? 4 : 2;
+            while (g.L[3] % s.tchunk) s.tchunk /= 2;
+            best_tile(g, 2048, &s.tile_y, &s.tile_z);
+            return s;
+        }
+    }
+    // From five rhs on always.  M, clover FP32, 5 rhs, unstaged and staged: 20 x 18 x 14 x 30
+    // 105 and 89 us, 24^3 x 48 452 and 411; FP16 74 and 69, 274 and 297.
+    t.stage = nrhs >= 5 && stage_ok(g, prec, nrhs, t) ? 1 : 0;
     if (t.stage) {
         // With staged links the lanes can walk time with the neighbours of their index in
         // registers: chunks of 8 timeslices where at least 12 rounds of resident blocks
@@ -126,7 +144,7 @@ inline TuneEntry plain_entry(const Geom &g, int prec, int nrhs, bool both) {
         while (g.L[3] % t.tchunk) t.tchunk /= 2;
         return t;
     }
-    // two and three rhs per site (M, 24^3 x 48 FP16: 92 us untiled in 256-lane blocks, 78
+    // two to four rhs per site (M, 24^3 x 48 FP16: 92 us untiled in 256-lane blocks, 78
     // with 12x12 tiles of 64-site blocks)
     if (T > 64) t.sites_per_block = 64;
     best_tile(g, 2048, &t.tile_y, &t.tile_z);
@@ -156,7 +174,7 @@ inline TuneEntry default_entry(const Geom &g, int prec, int nrhs, bool both, boo
     t.stage = 2;
     t.sites_per_block = kDirsSites / nrhs;
     if (few_lanes(g, prec, nrhs, both, clover) && dirs_ok(g, prec, nrhs, t)) return t;
-    return plain_entry(g, prec, nrhs, both);
+    return plain_entry(g, prec, nrhs, both, clover);
 }
 
 // The FLIC hops load both links per lane, one rhs per lane, and neither stage links nor walk
@@ -170,7 +188,7 @@ inline TuneEntry default_entry(const Geom &g, int prec, int nrhs, bool both, boo
 // 3.93, 4 rhs 2.64 -> 2.44 and 2.25 -> 2.07; FP32 4 rhs 1080 -> 1068 and 988 -> 973 us, at
 // 12^3 x 16 M 8% less.
 inline TuneEntry flic_entry(const Geom &g, int prec, int nrhs, bool both) {
-    TuneEntry t = plain_entry(g, prec, nrhs, both);
+    TuneEntry t = plain_entry(g, prec, nrhs, both, false);
     t.stage = 0;
     if (nrhs == 1) return t;
     const bool f64 = prec == COLA_FP64 || prec == COLA_FP64_12;
@@ -208,7 +226,7 @@ inline std::vector<TuneEntry> tune_candidates(const Geom &g, int prec, int nrhs,
         cand.push_back(t);
     };
     add(default_entry(g, prec, nrhs, both, clover));
-    add(plain_entry(g, prec, nrhs, both));
+    add(plain_entry(g, prec, nrhs, both, clover));
     {
         TuneEntry t;
         t.stage = 2;

@@ -23,8 +23,8 @@ extern "C" {
 void probe_default(const int *d, int prec, int nrhs, int both, int clover, int *o) {
     put(default_entry(make_geom(d), prec, nrhs, both, clover), o);
 }
-void probe_plain(const int *d, int prec, int nrhs, int both, int *o) {
-    put(plain_entry(make_geom(d), prec, nrhs, both), o);
+void probe_plain(const int *d, int prec, int nrhs, int both, int clover, int *o) {
+    put(plain_entry(make_geom(d), prec, nrhs, both, clover), o);
 }
 void probe_flic(const int *d, int prec, int nrhs, int both, int *o) {
     put(flic_entry(make_geom(d), prec, nrhs, both), o);
@@ -82,8 +82,8 @@ def test_defaults_are_accepted(probe):
             s = _shape(probe.probe_default, _dims(d), prec, nrhs, both, clover)
             assert probe.probe_valid(_dims(d), prec, nrhs, (ctypes.c_int * 7)(*s)), \
                 (d, prec, nrhs, both, clover, s)
-        s = _shape(probe.probe_plain, _dims(d), prec, nrhs, both)
-        assert s[6] != 2 and probe.probe_valid(_dims(d), prec, nrhs, (ctypes.c_int * 7)(*s))
+            s = _shape(probe.probe_plain, _dims(d), prec, nrhs, both, clover)
+            assert s[6] != 2 and probe.probe_valid(_dims(d), prec, nrhs, (ctypes.c_int * 7)(*s))
 
 
 def test_flic_defaults_are_shapes_of_the_flic_kernel(probe):
@@ -109,7 +109,7 @@ def test_tuner_times_the_defaults(probe):
             cand = [tuple(buf[7 * k:7 * k + 7]) for k in range(n)]
             assert len(set(cand)) == n
             assert _shape(probe.probe_default, _dims(d), prec, nrhs, both, clover) in cand
-            assert _shape(probe.probe_plain, _dims(d), prec, nrhs, both) in cand
+            assert _shape(probe.probe_plain, _dims(d), prec, nrhs, both, clover) in cand
             for s in cand:
                 assert probe.probe_valid(_dims(d), prec, nrhs, (ctypes.c_int * 7)(*s)), s
 
@@ -131,3 +131,16 @@ def test_tables_of_earlier_kernels_are_not_used(probe):
     assert len(now.split()) == 2 and now.split()[1] == hop and len(now.split()[0]) < 128
     others = [key(b"gfx950", 304, hop), key(b"gfx942", 256, hop), key(b"gfx950", 256, hop + b":b")]
     assert len({now, *others}) == 4
+
+
+def test_links_are_staged_from_the_stated_rhs_count(probe):
+    """FP32 and FP16 launches with one lane per (site, rhs) stage links from five rhs on, and
+    with four where no clover block is read and the launch keeps at least 1024 blocks; never
+    with fewer."""
+    for d, prec, nrhs, both in KINDS:
+        blocks = d[0] * d[1] * d[2] * d[3] // 2 * (2 if both else 1) / 32
+        for clover in (0, 1):
+            staged = _shape(probe.probe_plain, _dims(d), prec, nrhs, both, clover)[6] == 1
+            want = prec in (FP32, FP16) and (
+                nrhs >= 5 or (nrhs == 4 and not clover and blocks >= 2048))
+            assert staged == want, (d, prec, nrhs, both, clover)
