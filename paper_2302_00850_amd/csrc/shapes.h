@@ -152,21 +152,29 @@ inline TuneEntry plain_entry(const Geom &g, int prec, int nrhs, bool both, bool 
 }
 
 // Launches of few lanes (sites of one parity x rhs) take the hop with a wavefront per
-// direction, up to where it was measured no slower (us, this against plain_entry's shape; m:
-// both parities, s: D_eo D_oe):
-//   one rhs FP32  16^3 x 32 s 16.6 / 28.8, 24^3 x 48 s 72 / 95, m 69 / 73, 28^3 x 48 s 125 / 161,
-//                 32^3 x 64 s 302 / 266; with clover 28^3 x 48 s 183 / 220, 20^3 x 32 m 42 / 41,
-//                 24^3 x 32 m 70 / 66
-//   one rhs FP64  16^3 x 32 s 37 / 43, m 28 / 40, 24^3 x 32 s 126 / 140, 24^3 x 48 s 224 / 208,
-//                 28^3 x 48 m 280 / 294; with clover 20^3 x 32 s 99 / 104, 24^3 x 32 s 182 / 179
-//   several rhs   12^3 x 16 FP32 5 rhs s 17 / 23, 12 rhs m 36 / 30; FP64 8 rhs s 39 / 42,
-//                 12 rhs with clover s 79 / 77
+// direction.  The lines, from times of plain_entry's shape over times of this one (m: both
+// parities, s: D_eo D_oe; c: with clover; 12 = FP64_12):
+//   one rhs   FP32 s 28^3 x 48 1.29, c 1.20, 32^3 x 64 0.88; m 24^3 x 48 1.06; m c 16^3 x 32
+//             1.02, 18^3 x 30 0.98, 20^3 x 32 0.97
+//             FP64 s 24^3 x 32 1.12 (12: 1.18), 24^3 x 48 0.92 (1.03), 28^3 x 48 0.95 (0.98); m
+//             28^3 x 48 1.11 (1.09), 32^3 x 64 0.83 (0.85); s c 20^3 x 32 1.04 (1.02), 24^3 x 32
+//             0.98 (1.05); m c 16^3 x 32 1.19 (1.11), 20^3 x 24 1.05 (0.95), 20^3 x 32 1.07 (0.95),
+//             24^3 x 32 0.98 (0.95)
+//   more      (2 to 16 rhs, 4 thousand to 131 thousand lanes) FP32 at least 0.98 up to 65536;
+//             m c 1.05 up to 41 thousand, then 0.83 to 0.94 from six rhs on
+//             FP64 at least 0.97; m c 0.95 up to 41 thousand, 0.91 to 0.94 with 11 and 12 rhs
+//             at 45 and 49, 0.85 to 1.09 from 76 on; s c at least 1.01, but with three and four
+//             rhs 0.91 from 98 on
 inline bool few_lanes(const Geom &g, int prec, int nrhs, bool both, bool clover) {
-    const bool f32 = prec == COLA_FP32;
     const double lanes = (double)g.Vh * nrhs;
-    if (nrhs > 1) return lanes <= (f32 ? 65536 : 131072);
-    if (clover && (both || !f32)) return lanes <= 131072;
-    return lanes <= (f32 || both ? 600000 : 262144);
+    if (prec == COLA_FP32) {
+        if (nrhs == 1) return lanes <= (clover && both ? 65536 : 600000);
+        return lanes <= (clover && both && nrhs > 5 ? 43008 : 65536);
+    }
+    if (!clover) return lanes <= (nrhs > 1 ? 131072 : both ? 600000 : 262144);
+    if (nrhs == 1) return lanes <= (both && prec == COLA_FP64_12 ? 65536 : 131072);
+    if (both) return lanes <= (nrhs > 8 ? 43008 : 73728);
+    return lanes <= (nrhs == 3 || nrhs == 4 ? 90112 : 131072);
 }
 
 inline TuneEntry default_entry(const Geom &g, int prec, int nrhs, bool both, bool clover) {

@@ -144,3 +144,32 @@ def test_links_are_staged_from_the_stated_rhs_count(probe):
             want = prec in (FP32, FP16) and (
                 nrhs >= 5 or (nrhs == 4 and not clover and blocks >= 2048))
             assert staged == want, (d, prec, nrhs, both, clover)
+
+
+# (lattice, precision, both parities, clover): the kernel that was faster; one rhs, then rhs
+FASTER = [
+    ((16, 16, 16, 32), FP32, 1, 1, "directions"), ((18, 18, 18, 30), FP32, 1, 1, "sites"),
+    ((20, 20, 20, 32), FP32, 1, 1, "sites"), ((16, 16, 16, 32), FP64_12, 1, 1, "directions"),
+    ((20, 20, 20, 24), FP64_12, 1, 1, "sites"), ((20, 20, 20, 32), FP64_12, 1, 1, "sites"),
+    ((20, 20, 20, 32), FP64, 1, 1, "directions"), ((24, 24, 24, 32), FP64, 1, 1, "sites"),
+    ((24, 24, 24, 32), FP32, 0, 1, "directions"), ((20, 20, 20, 32), FP64, 0, 1, "directions"),
+    ((20, 20, 20, 32), FP64_12, 0, 1, "directions"), ((24, 24, 24, 32), FP64, 0, 1, "sites"),
+    ((28, 28, 28, 48), FP64_12, 1, 0, "directions"), ((28, 28, 28, 48), FP64, 1, 0, "directions"),
+    ((24, 24, 24, 32), FP64_12, 0, 0, "directions"), ((28, 28, 28, 48), FP64, 0, 0, "sites"),
+    ((32, 32, 32, 64), FP32, 0, 0, "sites"), ((32, 32, 32, 64), FP64, 1, 0, "sites"),
+]
+
+
+FASTER = [c[:4] + (1, c[4]) for c in FASTER] + [
+    ((12, 12, 12, 8), FP32, 1, 1, 8, "sites"), ((8, 8, 8, 16), FP32, 1, 1, 12, "sites"),
+    ((8, 8, 8, 16), FP32, 1, 1, 8, "directions"), ((12, 12, 12, 24), FP32, 1, 1, 3, "directions"),
+    ((8, 8, 8, 16), FP64, 1, 1, 12, "sites"), ((12, 12, 12, 12), FP64, 1, 1, 5, "directions"),
+    ((16, 16, 16, 16), FP64, 1, 1, 3, "sites"), ((16, 16, 16, 16), FP64_12, 0, 1, 3, "sites"),
+    ((12, 12, 12, 24), FP64, 0, 1, 5, "directions"), ((12, 12, 12, 12), FP64, 1, 0, 12, "directions"),
+]
+
+
+@pytest.mark.parametrize("lattice,prec,both,clover,nrhs,faster", FASTER)
+def test_default_is_the_kernel_measured_faster(probe, lattice, prec, both, clover, nrhs, faster):
+    s = _shape(probe.probe_default, _dims(lattice), prec, nrhs, both, clover)
+    assert (s[6] == 2) == (faster == "directions")
