@@ -65,15 +65,19 @@ inline bool shape_valid(const Geom &g, int prec, int nrhs, const TuneEntry &e) {
 // there is none.
 inline void best_tile(const Geom &g, int most, int *ty, int *tz) {
     *ty = *tz = 0;
-    for (int y = 2; y <= g.L[1]; ++y)
-        for (int z = 2; z <= g.L[2]; ++z) {
-            if (g.L[1] % y || g.L[2] % z || g.Lxh * y * z > most) continue;
-            const int now = y * z, had = *ty * *tz;
-            if (now > had || (now == had && abs(y - z) < abs(*ty - *tz))) {
-                *ty = y;
-                *tz = z;
-            }
+    // per divisor y the largest z that fits: a smaller z of the same y is a smaller tile
+    for (int y = 2; y <= g.L[1]; ++y) {
+        if (g.L[1] % y) continue;
+        int z = most / (g.Lxh * y);
+        if (z > g.L[2]) z = g.L[2];
+        while (z >= 2 && g.L[2] % z) --z;
+        if (z < 2) continue;
+        const int now = y * z, had = *ty * *tz;
+        if (now > had || (now == had && abs(y - z) < abs(*ty - *tz))) {
+            *ty = y;
+            *tz = z;
         }
+    }
 }
 
 // Launch shapes.  Tiles are walked through t, so that the timeslices in flight of a tile and

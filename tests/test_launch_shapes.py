@@ -5,6 +5,7 @@ import ctypes
 import itertools
 import os
 import subprocess
+import time
 
 import pytest
 
@@ -39,6 +40,7 @@ int probe_key(const char *arch, int num_cu, const char *key, char *o, int most) 
     strncpy(o, s.c_str(), most - 1);
     return (int)s.size();
 }
+void probe_tile(const int *d, int most, int *o) { best_tile(make_geom(d), most, o, o + 1); }
 int probe_valid(const int *d, int prec, int nrhs, const int *s) {
     TuneEntry t;
     t.rpt = s[0], t.sites_per_block = s[1], t.grid = s[2], t.tchunk = s[3];
@@ -173,3 +175,33 @@ FASTER = [c[:4] + (1, c[4]) for c in FASTER] + [
 def test_default_is_the_kernel_measured_faster(probe, lattice, prec, both, clover, nrhs, faster):
     s = _shape(probe.probe_default, _dims(lattice), prec, nrhs, both, clover)
     assert (s[6] == 2) == (faster == "directions")
+
+
+def _best_tile(d, most):
+    """The largest tile of `most` sites by trying every pair of extents."""
+    best = (0, 0)
+    for y in range(2, d[1] + 1):
+        for z in range(2, d[2] + 1):
+            if d[1] % y or d[2] % z or d[0] // 2 * y * z > most:
+                continue
+            if y * z > best[0] * best[1] or (
+                    y * z == best[0] * best[1] and abs(y - z) < abs(best[0] - best[1])):
+                best = (y, z)
+    return best
+
+
+def test_tile_search(probe):
+    """The search finds the tile that trying every pair finds, and where the extents are large
+    it does not cost a launch's time: it runs on every call that has no tuned shape.  All
+    pairs of 512 x 512 take 190 us, the divisors among them 5."""
+    out = (ctypes.c_int * 2)()
+    for d in LATTICES + [(2, 512, 96, 2), (4, 30, 210, 4), (6, 22, 26, 2)]:
+        for most in (0, 1, 4, 64, 288, 900, 1024, 2048, 4096, 8192):
+            probe.probe_tile(_dims(d), most, out)
+            assert tuple(out) == _best_tile(d, most), (d, most)
+    d, took = _dims((2, 512, 512, 2)), []
+    for _ in range(20):
+        t0 = time.perf_counter()
+        probe.probe_tile(d, 8192, out)
+        took.append(time.perf_counter() - t0)
+    assert min(took) < 60e-6
