@@ -430,7 +430,11 @@ int hop(cola_handle_t *h, const HopCall &call, int prec, int nrhs, hipStream_t s
         tune_key(h, prec, nrhs, key_epi, c.norm_result != nullptr) + (c.both ? ":b" : "");
     TuneEntry te;
     auto it = h->tune.find(key);
-    if (h->flic) {
+    if (c.cg_pi_n > 0) {
+        // only this kernel adds partial sums, and only it leaves them (fill_and_launch): the
+        // shapes stored meanwhile by another thread do not come between the two launches
+        te = dirs_entry(nrhs);
+    } else if (h->flic) {
         te = flic_shape(h->g, prec, nrhs, c.both);
     } else if (it != h->tune.end() && (h->tune_mode != 2 || cg || c.fixed)) {
         te = it->second;
@@ -449,14 +453,6 @@ int hop(cola_handle_t *h, const HopCall &call, int prec, int nrhs, hipStream_t s
     // a resident grid needs an occupancy query (cached in a host map): the fixed mode
     // takes the plain grid instead, which gives bitwise the same output
     if (c.fixed && te.grid < 0) te.grid = 0;
-    // the other kernels take ready scalars
-    if (te.stage != 2 && c.cg_pi_n > 0) {
-        void *s;
-        COLA_TRY(get_vec(h, "hop_sum", sizeof(double), &s));
-        COLA_HIP(h, launch_reduce_partials(c.cg_pi, c.cg_pi_n, 1, (double *)s, st));
-        c.cg_pi = (const double *)s;
-        c.cg_pi_n = 0;
-    }
     const bool timed = (h->flags & COLA_FLAG_TIMING) != 0 && !c.fixed;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (timed) {

@@ -181,10 +181,16 @@ inline bool few_lanes(const Geom &g, int prec, int nrhs, bool both, bool clover)
     return lanes <= (nrhs == 3 || nrhs == 4 ? 90112 : 131072);
 }
 
-inline TuneEntry default_entry(const Geom &g, int prec, int nrhs, bool both, bool clover) {
+// The shape of the hop with a wavefront per direction: as many whole sites as a block takes.
+inline TuneEntry dirs_entry(int nrhs) {
     TuneEntry t;
     t.stage = 2;
     t.sites_per_block = kDirsSites / nrhs;
+    return t;
+}
+
+inline TuneEntry default_entry(const Geom &g, int prec, int nrhs, bool both, bool clover) {
+    const TuneEntry t = dirs_entry(nrhs);
     if (few_lanes(g, prec, nrhs, both, clover) && dirs_ok(g, prec, nrhs, t)) return t;
     return plain_entry(g, prec, nrhs, both, clover);
 }
@@ -239,12 +245,7 @@ inline std::vector<TuneEntry> tune_candidates(const Geom &g, int prec, int nrhs,
     };
     add(default_entry(g, prec, nrhs, both, clover));
     add(plain_entry(g, prec, nrhs, both, clover));
-    {
-        TuneEntry t;
-        t.stage = 2;
-        t.sites_per_block = kDirsSites / nrhs;
-        if (dirs_ok(g, prec, nrhs, t)) add(t);
-    }
+    if (dirs_ok(g, prec, nrhs, dirs_entry(nrhs))) add(dirs_entry(nrhs));
     std::vector<TuneEntry> base;
     for (int rpt : {1, 2, 3, 4}) {
         if (nrhs % rpt) continue;
