@@ -41,8 +41,8 @@ int scalars(cola_handle_t *h, double **sc) {
 
 int work(cola_handle_t *h, bool fermions, HmcWork *w) {
     const size_t gb = (size_t)8 * 9 * 16 * h->g.S;
-    COLA_TRY(get_vec(h, "hmc_U0", gb, &w->U[0]));
-    COLA_TRY(get_vec(h, "hmc_U1", gb, &w->U[1]));
+    COLA_TRY(get_vec(h, "links_w0", gb, &w->U[0]));
+    COLA_TRY(get_vec(h, "links_w1", gb, &w->U[1]));
     COLA_TRY(get_vec(h, "hmc_P", gb, &w->P));
     COLA_TRY(scalars(h, &w->sc));
     if (!fermions) return COLA_OK;
