@@ -12,8 +12,8 @@
 //
 // One lane per link (or per site for the plaquette sum), grid-stride loops.  These serve the
 // single-step entry points; a trajectory runs on packed fields.
-#include "device.h"
 #include "launch.h"
+#include "m3.h"
 
 namespace cola {
 
@@ -24,12 +24,6 @@ using C = cpx<double>;
 // grid cap of the grid-stride kernels (also the partial count of their reductions)
 constexpr int kHmcGrid = 4096;
 static_assert(kHmcGrid <= kRedMaxBlocks, "reduction partials");
-
-struct M3 {
-    C a[3][3];
-};
-
-__device__ __forceinline__ C conj(C a) { return {a.x, -a.y}; }
 
 __device__ __forceinline__ M3 ld3(const C *p) {
     M3 m;
@@ -45,44 +39,6 @@ __device__ __forceinline__ void st3(C *p, const M3 &m) {
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j) p[3 * i + j] = m.a[i][j];
-}
-
-// A B, A B^H, A^H B
-__device__ __forceinline__ M3 mm(const M3 &A, const M3 &B) {
-    M3 r;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            C s = cmul(A.a[i][0], B.a[0][j]);
-            s = cmadd(s, A.a[i][1], B.a[1][j]);
-            r.a[i][j] = cmadd(s, A.a[i][2], B.a[2][j]);
-        }
-    return r;
-}
-__device__ __forceinline__ M3 mmd(const M3 &A, const M3 &B) {
-    M3 r;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            C s = cmul(A.a[i][0], conj(B.a[j][0]));
-            s = cmadd(s, A.a[i][1], conj(B.a[j][1]));
-            r.a[i][j] = cmadd(s, A.a[i][2], conj(B.a[j][2]));
-        }
-    return r;
-}
-__device__ __forceinline__ M3 mdm(const M3 &A, const M3 &B) {
-    M3 r;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            C s = cmul(conj(A.a[0][i]), B.a[0][j]);
-            s = cmadd(s, conj(A.a[1][i]), B.a[1][j]);
-            r.a[i][j] = cmadd(s, conj(A.a[2][i]), B.a[2][j]);
-        }
-    return r;
 }
 
 __device__ __forceinline__ void coords(const Geom &g, uint32_t s, int x[4]) {

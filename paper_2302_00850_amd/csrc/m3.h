@@ -1,7 +1,7 @@
-// 3 x 3 complex FP64 matrices and the links of a packed 18-real field, for the kernels that
-// work on links (clover blocks, smearing, gauge force, plaquette).
+// 3 x 3 complex FP64 matrices, and the links of a packed 18-real field for the kernels that
+// work on links (clover blocks, smearing, the trajectory).
 //
-// They read the packed field (chunk k of U_mu at (p, i) at ((p 4 + mu) 9 + k) S + i), in
+// Those read the packed field (chunk k of U_mu at (p, i) at ((p 4 + mu) 9 + k) S + i), in
 // which the 64 lanes of a wavefront, consecutive checkerboard sites of one parity and one
 // direction, load 64 consecutive 16-byte elements.  From the canonical field (144 bytes per
 // link) the same load touches 64 cache lines, and the L1's line rate, not memory, set the
