@@ -325,10 +325,15 @@ def cola_tune_dump(h) -> str:
 
 def _stream():
     # the raw handle of the current device's current stream: building a Stream object for it
-    # takes 2.7 of the 8.6 us that M on 4^4 spends on the host, the handle alone 0.3
-    if not torch.cuda.is_initialized():
-        return torch.cuda.current_stream().cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    # takes 2.7 of the 8.6 us that M on 4^4 spends on the host, the handle alone 0.3.  The
+    # query is internal to torch: without it, or before torch has initialised the device, the
+    # Stream object.
+    if torch.cuda.is_initialized():
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:
+            pass
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t: torch.Tensor) -> int:
