@@ -5,10 +5,10 @@
 #include <chrono>
 #include <cmath>
 #include <string>
-#include <vector>
 
 #include "cola.h"
 #include "handle.h"
+#include "hmc_stages.h"
 #include "launch.h"
 
 using namespace cola;
@@ -103,48 +103,6 @@ int fermion_kick(cola_handle_t *h, const void *U, const void *phi, const cola_hm
     COLA_HIP(h, launch_fermion_kick(h->g, U, w.Xp, w.Yp, w.P,
                                     p->eo ? h->kappa * h->kappa : h->kappa, h->phase, eps, st));
     return COLA_OK;
-}
-
-// One stage of the integrator at the current links: the fermion kick (if any), then the
-// gauge kick and, unless it is the last, the link update.
-struct Stage {
-    bool fermions;
-    double eps_f, eps_g, eps_u;
-};
-
-std::vector<Stage> stages(const cola_hmc_params_t *p) {
-    std::vector<Stage> v;
-    const double eps = p->eps;
-    if (p->integrator == 0) {
-        // leapfrog: P eps/2, then per step U eps and P eps (eps/2 after the last)
-        for (int k = 0; k <= p->nsteps; ++k) {
-            const double e = k == 0 || k == p->nsteps ? 0.5 * eps : eps;
-            v.push_back({true, e, e, eps});
-        }
-    } else if (p->integrator == 2) {
-        // two time scales: fermion kicks of eps around n_gauge gauge leapfrog sub-steps of
-        // eps / n_gauge; the half gauge kicks that end one step and start the next are one
-        const int m = p->n_gauge;
-        const double hs = eps / m;
-        for (int k = 0; k <= p->nsteps; ++k) {
-            const bool end = k == 0 || k == p->nsteps;
-            v.push_back({true, end ? 0.5 * eps : eps, end ? 0.5 * hs : hs, hs});
-            for (int j = 1; j < m && k < p->nsteps; ++j) v.push_back({false, 0.0, hs, hs});
-        }
-    } else {
-        // Omelyan: P lambda eps, then per step U eps/2, P (1 - 2 lambda) eps, U eps/2 and
-        // P 2 lambda eps (the next step's first momentum step merged; lambda eps after the
-        // last)
-        const double lam = 0.1931833275037836;
-        v.push_back({true, lam * eps, lam * eps, 0.5 * eps});
-        for (int k = 0; k < p->nsteps; ++k) {
-            const double mid = (1.0 - 2.0 * lam) * eps;
-            const double e = (k == p->nsteps - 1 ? lam : 2.0 * lam) * eps;
-            v.push_back({true, mid, mid, 0.5 * eps});
-            v.push_back({true, e, e, 0.5 * eps});
-        }
-    }
-    return v;
 }
 
 }  // namespace
@@ -258,11 +216,11 @@ int cola_hmc_trajectory(cola_handle_t *h, void *U, void *P, const void *phi,
     const size_t n = nlinks(h) * 9;
     COLA_HIP(h, launch_sqnorm(P, n, h->partial, w.sc + KIN0, st));
     COLA_HIP(h, launch_md_pack(h->g, U, P, w.U[0], w.P, st));
-    const std::vector<Stage> plan = stages(p);
+    const long long count = stage_count(*p);
     int cur = 0;
-    for (size_t k = 0; k < plan.size(); ++k) {
-        const Stage &s = plan[k];
-        const bool first = k == 0, last = k + 1 == plan.size();
+    for (long long k = 0; k < count; ++k) {
+        const Stage s = stage_at(*p, k);
+        const bool first = k == 0, last = k + 1 == count;
         if (phi && s.fermions)
             COLA_TRY(fermion_kick(h, w.U[cur], phi, p, w, first, s.eps_f,
                                   first  ? w.sc + SF0
