@@ -46,7 +46,7 @@ WORKLOAD = "clover_eo_48x48x48x96_12rhs_fp32defect"
 # bytes per launch); valid only for the hop sources it was taken with.
 COUNTERS = os.path.join(ROOT, "profiles", "hop_fp32_12rhs_clover_48x48x48x96_solve_counters.txt")
 HOP_SOURCES = ["hop_impl.h", "device.h", "common.h", "hop_f32_12.hip", "hop_dispatch.cpp",
-               "ops.cpp"]
+               "shapes.h", "ops.cpp"]
 
 
 def hop_sources_sha256():

@@ -151,8 +151,8 @@ struct HopArgs {
     // chunks Lt / tchunk
     int tile_y, tile_z;
     FastDiv div_tcols, div_nk, div_lxh, div_ty, div_nty;
-    // the site's links staged in LDS by its first eight lanes (groups >= 8, one rhs per
-    // lane, sites_per_block <= 32, 12-real FP16 / FP32 links)
+    // the site's links staged in LDS by its lanes (at least three of them, one or two rhs
+    // each, sites_per_block <= kStageSites, 12-real FP16 / FP32 links)
     int stage_links;
     // a wavefront per direction (hop_dirs.h): blocks of sites_per_block sites, groups = nrhs
     int by_dirs;

@@ -214,7 +214,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_u(const void *base, uint32
 //   kBases    same base for all lanes, each array's base computed from it and made opaque:
 //             the additions do not wait for one another.  For the FP32 FLIC hops, which take
 //             48 link arrays per site: 32^3 x 64, 12 rhs, D_eo D_oe 3.15 -> 2.95 ms and M
-//             3.21 -> 3.00 ms, one rhs M 352 -> 316 us against kWalk
+//             3.21 -> 3.00 ms, one rhs M 352 -> 316 us against kWalk.  Their clover blocks
+//             stay with kWalk (369 spilled scalar registers without): clover S, 8^4 to 20 x
+//             18 x 14 x 30, 1 to 12 rhs, 5% less time on average
 constexpr int kPerLane = 0, kWalk = 1, kBases = 2;
 
 template <int M = kWalk>
@@ -822,14 +824,14 @@ __device__ __forceinline__ void read_staged(const uint32_t *src, cpx<float> u[3]
 // ------------------------------------------------------------------ clover
 
 // out = C in, C = two Hermitian 6x6 chiral blocks (spins {0,1} and {2,3}).
-template <typename CR, typename T, int M = kWalk>
+template <typename CR, typename T>
 __device__ __forceinline__ void clover_apply(const void *clov, int S, int p, uint32_t i,
                                              const cpx<T> in[12], cpx<T> out[12]) {
     struct pair { CR a, b; };
     const uint32_t off = i * (uint32_t)sizeof(pair);
     uint64_t stride = (uint64_t)S * sizeof(pair);
-    if constexpr (M == kWalk) asm volatile("" : "+s"(stride));
-    ArrayWalk<M> w((const char *)clov + (uint64_t)(p * 36) * stride, stride,
+    asm volatile("" : "+s"(stride));
+    ArrayWalk<> w((const char *)clov + (uint64_t)(p * 36) * stride, stride,
                   (uint32_t)S * (uint32_t)sizeof(pair));
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk) {

@@ -128,7 +128,7 @@ __global__ void __launch_bounds__(kMdWaves *kMdSites)
             nrm *= sc;
 #pragma unroll
             for (int k = 0; k < 9; ++k) X.a[k / 3][k % 3] = scale(sc, X.a[k / 3][k % 3]);
-            // the order that leaves the truncation |X|^(n+1) / (n+1)! below 2e-20 on every lane
+            // the order that leaves the truncation |X|^(n+1) / (n+1)! below 2.2e-20 on every lane
             const int order_n = !__any(!(nrm < 0.027))   ? 8
                                 : !__any(!(nrm < 0.079)) ? 10
                                 : !__any(!(nrm < 0.172)) ? 12

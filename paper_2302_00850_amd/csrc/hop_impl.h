@@ -251,7 +251,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK ? 3
     constexpr bool WALK = WK;
     static_assert(!WK || hop_walks<SF, RPT, EPI, SHL, FL>(), "no time walk for this kernel");
     extern __shared__ double red[];
-    // SHL: the site's eight links staged in LDS by its first eight lanes, and with a clover
+    // SHL: the site's eight links staged in LDS by its lanes in turn, and with a clover
     // epilogue (FP32 blocks) the site's clover block by all its lanes
     constexpr bool CLV = EPI == EPI_CLOV || EPI == EPI_CLOV_XPAY || EPI == EPI_XPAY_CLOV ||
                          EPI == EPI_CLOV_XPAY_CG;
@@ -440,14 +440,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK ? 3
                 if constexpr (SCL)
                     clover_apply_lds<T>(cstaged, d, o);
                 else
-                    clover_apply<CR, T, hop_bases<SF, FL>()>(a.clov, g.S, p, i, d, o);
+                    clover_apply<CR, T>(a.clov, g.S, p, i, d, o);
             } else if constexpr (EPI == EPI_CLOV_XPAY || EPI == EPI_CLOV_XPAY_CG) {
                 C xv[12], cx[12];
                 xin.load(i, rr, xv);
                 if constexpr (SCL)
                     clover_apply_lds<T>(cstaged, xv, cx);
                 else
-                    clover_apply<CR, T, hop_bases<SF, FL>()>(a.clov, g.S, p, i, xv, cx);
+                    clover_apply<CR, T>(a.clov, g.S, p, i, xv, cx);
 #pragma unroll
                 for (int c = 0; c < 12; ++c) o[c] = add_s(cx[c], ca, o[c]);
             } else if constexpr (EPI == EPI_XPAY_CLOV) {
@@ -458,7 +458,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WK ? 3
                 if constexpr (SCL)
                     clover_apply_lds<T>(cstaged, xv, o);
                 else
-                    clover_apply<CR, T, hop_bases<SF, FL>()>(a.clov, g.S, p, i, xv, o);
+                    clover_apply<CR, T>(a.clov, g.S, p, i, xv, o);
             }
             if constexpr (CG) {
                 // r -= alpha o; o becomes the stored r (for the norm)

@@ -85,7 +85,8 @@ hipError_t launch_scalar_add(double *a, const double *b, int n, hipStream_t st);
 // alpha_q = active_q ? rho_q / pi_q : 0
 hipError_t launch_cg_xr(const BlasShape &b, SpinorFmt fx, SpinorFmt fp, SpinorFmt fr,
                         SpinorFmt fap, void *x, const void *p, void *r, const void *ap,
-                        const double *rho, const double *pi, const int *active, const Reduce &red, hipStream_t st);
+                        const double *rho, const double *pi, const int *active,
+                        const Reduce &red, hipStream_t st);
 // The vector updates that follow a CG step with r updated in the last hop, all fields in
 // format f: x += alpha p (x null: not done; alpha_q = active_q ? rho_q / pi_q : 0), then
 // p = r + beta p (r null: not done; beta_q = active_q ? rho_new_q / rho_q : 0)

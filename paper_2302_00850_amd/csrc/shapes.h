@@ -304,10 +304,10 @@ inline std::vector<TuneEntry> tune_candidates(const Geom &g, int prec, int nrhs,
 // The key of the table of tuned shapes: device and version, launch.  Entries of another
 // version, timed against other kernels and other defaults, stay in the file and are not used;
 // the number goes up whenever a kernel, a kind of shape or a default changes.
-constexpr int kShapeVersion = 2;
+constexpr const char *kShapeVersion = ":v2 ";
 
 inline std::string table_key(const std::string &arch, int num_cu, const std::string &key) {
-    return arch + ":" + std::to_string(num_cu) + ":v" + std::to_string(kShapeVersion) + " " + key;
+    return arch + ":" + std::to_string(num_cu) + kShapeVersion + key;
 }
 
 }  // namespace cola

@@ -271,13 +271,14 @@ struct Outcome {
 
 // ---------------------------------------------------------------- iteration blocks
 
-// Small solves are bound by launch latency (a 16^3 x 32 CG iteration runs ~90 us of
-// kernels in ~165 us), so with COLA_GRAPHS=1 the n iterations between two convergence
+// Small solves are bound by launch latency (an FP32 iteration at 16^3 x 32 is six dependent
+// launches of 9 to 12 us), so with COLA_GRAPHS=1 the n iterations between two convergence
 // checks -- (step, p update) x (n - 1), step -- are captured once as a HIP
 // graph and replayed (large solves check every iteration and launch directly).  Capture
 // needs every launch shape settled (the first block of a solve runs directly, which
-// tunes) and no per-launch timing.  Off by default: measured on 16^3 x 32 and 8^3 x 16,
-// the replays ran 4-10% slower than the direct launches.
+// tunes) and no per-launch timing.  Off by default: solves at 16^3 x 32 took 9 to 14% longer
+// with replays (FP32 with reliable updates 6.02 and 6.88 ms) and at 8^3 x 16 8 to 26%; replays
+// add their partial sums in launches of their own.
 bool graphs_wanted(const Ctx &c) {
     const char *env = getenv("COLA_GRAPHS");
     if (!env || env[0] != '1') return false;
@@ -683,7 +684,7 @@ int solve_defect(const Ctx &c, int inner_prec, const cola_cg_params_t &p, void *
                                    c.st));
         COLA_HIP(h, launch_convert(sh, fp, fxr, pv, rs, nullptr, 0, nullptr, c.st));
         COLA_HIP(h, hipMemsetAsync(xs, 0, c.bytes(fxr), c.st));
-            int its = 0, st = COLA_OK;
+        int its = 0, st = COLA_OK;
         if (p.block)
             COLA_TRY(inner_block_cg(c, prec, x32, r32, itol2, p.max_iter - o->iterations, act,
                                     check, &its, &st));
