@@ -80,6 +80,14 @@ inline void best_tile(const Geom &g, int most, int *ty, int *tz) {
     }
 }
 
+// A launch of few blocks takes smaller ones, down to a wavefront, so that more of the chip's
+// compute units have one: FLIC FP32 8^4 D_eo D_oe, 3 rhs 24.4 -> 21.5 us, 7 rhs 26.1 -> 22.0.
+inline void fill_chip(TuneEntry &t, double sites, int nrhs) {
+    while (t.sites_per_block > 1 && t.sites_per_block * nrhs > 64 &&
+           sites / t.tchunk / t.sites_per_block < 200.0)
+        t.sites_per_block /= 2;
+}
+
 // Launch shapes.  Tiles are walked through t, so that the timeslices in flight of a tile and
 // their links stay in one XCD's L2; the tile sizes below are where the times measured over
 // all divisors of 24^3 x 48, 32^3 x 64 and 48^3 x 96 are flat or lowest.
@@ -196,31 +204,46 @@ inline TuneEntry default_entry(const Geom &g, int prec, int nrhs, bool both, boo
 }
 
 // The FLIC hops load both links per lane, one rhs per lane, and neither stage links nor walk
-// time: blocks of one wavefront where the rhs fill it, tiles of 1024 sites, or with both
-// parities in FP64 512 up to 8 rhs and 256 beyond.  One and three rhs as plain_entry, and in
-// FP32 every count that does not divide 64 (12 rhs: within 2% of the best of 80 shapes).
-// FP64 from five rhs on: blocks of at most one wavefront, with both parities of whole
-// wavefronts if some power of two sites makes them (12 rhs: 16 sites), and chunks of 4
-// timeslices where 4 rounds of resident blocks remain.  Against plain_entry, D_eo D_oe and M
-// at 32^3 x 64: FP64 12 rhs 8.68 -> 7.93 and 7.06 -> 6.61 ms, 8 rhs 4.99 -> 4.41 and 4.45 ->
-// 3.93, 4 rhs 2.64 -> 2.44 and 2.25 -> 2.07; FP32 4 rhs 1080 -> 1068 and 988 -> 973 us, at
-// 12^3 x 16 M 8% less.
+// time.  Blocks: one wavefront where the rhs fill it (2, 4, 8, 16); else in FP64 up to one
+// wavefront, with both parities up to 256 lanes; FP32 and three rhs as plain_entry.  Tiles of
+// 1024 sites, in FP64 with both parities 512 up to 8 rhs, with both parities 256 beyond; FP32
+// counts that do not fill a wavefront keep the tile and chunk of plain_entry (12 rhs: within 2%
+// of the best of 80 shapes), three rhs in FP64 with one parity 2048.  FP64 takes chunks of 4
+// timeslices from five rhs on where 4 rounds of resident blocks remain, with three where one
+// does.  Against plain_entry, D_eo D_oe and M at 32^3 x 64: FP64 12 rhs 8.47 -> 7.76 and 6.95 ->
+// 6.50 ms, 8 rhs 4.89 -> 4.26 and 4.39 -> 3.88, 4 rhs 2.58 -> 2.34 and 2.25 -> 2.00, 3 rhs 2.32 ->
+// 2.13 and 1.95 -> 1.74, one rhs 1.20 -> 1.11 and 0.89 -> 0.74; FP32 (with the bases of its
+// arrays formed singly) 16 rhs 4.10 -> 3.82 and 4.25 -> 4.01, 4 rhs 1.18 -> 1.01 and 1.07 -> 0.94.
 inline TuneEntry flic_entry(const Geom &g, int prec, int nrhs, bool both) {
     TuneEntry t = plain_entry(g, prec, nrhs, both, false);
     t.stage = 0;
-    if (nrhs == 1) return t;
     const bool f64 = prec == COLA_FP64 || prec == COLA_FP64_12;
+    const double sites = (double)g.Vh * (both ? 2 : 1);
+    const auto chunk = [&](int rounds) {
+        t.tchunk = sites / t.sites_per_block / 4 >= rounds * 1024.0 ? 4 : 1;
+        while (g.L[3] % t.tchunk) t.tchunk /= 2;
+    };
+    if (nrhs == 1) {
+        if (f64 && t.sites_per_block == 256) {
+            t.sites_per_block = 128;
+            best_tile(g, both ? 2048 : 4096, &t.tile_y, &t.tile_z);
+        }
+        return t;
+    }
     int T = 64;
     while (T * nrhs > 64) T /= 2;
-    if (T * nrhs != 64 && (!f64 || nrhs == 3)) return t;
-    if (T * nrhs != 64 && both)
-        for (int w = 2 * T; w * nrhs <= 256; w *= 2)
-            if (w * nrhs % 64 == 0) T = w;
-    t.sites_per_block = T;
-    best_tile(g, !f64 || !both || nrhs == 2 ? 1024 : nrhs <= 8 ? 512 : 256, &t.tile_y, &t.tile_z);
-    const double blocks = (double)g.Vh * (both ? 2 : 1) / T;
-    t.tchunk = f64 && nrhs >= 5 && blocks / 4 >= 4 * 1024.0 ? 4 : 1;
-    while (g.L[3] % t.tchunk) t.tchunk /= 2;
+    const bool fills = T * nrhs == 64;
+    if (f64 && nrhs == 3) {
+        if (!both) best_tile(g, 2048, &t.tile_y, &t.tile_z);
+        chunk(1);
+    } else if (fills || f64) {
+        if (fills || !both) t.sites_per_block = T;
+        const int most = !both || nrhs == 2 ? 1024 : nrhs > 8 ? 256 : f64 ? 512 : 1024;
+        best_tile(g, most, &t.tile_y, &t.tile_z);
+        t.tchunk = 1;
+        if (f64 && nrhs >= 5) chunk(4);
+    }
+    fill_chip(t, sites, nrhs);
     return t;
 }
 

@@ -205,3 +205,17 @@ def test_tile_search(probe):
         probe.probe_tile(d, 8192, out)
         took.append(time.perf_counter() - t0)
     assert min(took) < 60e-6
+
+
+def test_flic_blocks(probe):
+    """FLIC launches of several rhs: a block is one wavefront where the rhs fill it, and no
+    launch leaves most compute units without a block while its blocks are of several
+    wavefronts."""
+    for d, prec, nrhs, both in KINDS:
+        if prec == FP16 or nrhs == 1:
+            continue
+        _, T, _, tchunk, *_ = _shape(probe.probe_flic, _dims(d), prec, nrhs, both)
+        sites = d[0] * d[1] * d[2] * d[3] // 2 * (2 if both else 1)
+        if nrhs in (2, 4, 8, 16):
+            assert T * nrhs == 64, (d, prec, nrhs, both)
+        assert T * nrhs <= 64 or sites / tchunk / T >= 200 or T * nrhs < 128, (d, prec, nrhs, both)
