@@ -80,6 +80,16 @@ inline void best_tile(const Geom &g, int most, int *ty, int *tz) {
     }
 }
 
+// The tile of at most `most` sites.  None where the whole timeslice is one, or but a quarter
+// more (several rhs): the order is that of one tile, the index cheaper, and cutting it in two
+// costs more than it keeps.  20 x 18 x 14 x 30 (2520 sites) against 9x14 tiles, D_eo D_oe: FP32 12
+// rhs 162 -> 148 us, 10 rhs 152 -> 134, 3 rhs 54 -> 50; FP16 12 rhs 102 -> 92.
+inline void set_tile(const Geom &g, int most, bool several, TuneEntry &t) {
+    const double slice = g.s3;
+    t.tile_y = t.tile_z = 0;
+    if (slice > (several ? 1.25 : 1.0) * most) best_tile(g, most, &t.tile_y, &t.tile_z);
+}
+
 // A launch of few blocks takes smaller ones, down to a wavefront, so that more of the chip's
 // compute units have one: FLIC FP32 8^4 D_eo D_oe, 3 rhs 24.4 -> 21.5 us, 7 rhs 26.1 -> 22.0.
 inline void fill_chip(TuneEntry &t, double sites, int nrhs) {
@@ -99,6 +109,7 @@ inline TuneEntry plain_entry(const Geom &g, int prec, int nrhs, bool both, bool 
     while (T * 2 * G <= 256) T *= 2;
     t.sites_per_block = T;
     t.grid = 0;
+    const double sites = (double)g.Vh * (both ? 2 : 1);
     if (nrhs == 1) {
         // 8192 sites, or 4096 where both parities run side by side.  M^dag M (both): FP64
         // 48^3 x 96 7.12 ms with 16x16 tiles of 64-site blocks, 5.06 with 24x6 (256); 32^3 x
@@ -107,8 +118,8 @@ inline TuneEntry plain_entry(const Geom &g, int prec, int nrhs, bool both, bool 
         // parity): FP64 48^3 x 96 7.30 -> 6.81 ms, 32^3 x 64 1.27 -> 1.23; FP32 2.94 -> 2.78
         // ms and 528 -> 515 us.  Blocks of 256 sites where that leaves each CU several of
         // them, else 64.
-        best_tile(g, both ? 4096 : 8192, &t.tile_y, &t.tile_z);
-        t.sites_per_block = (double)g.Vh * (both ? 2 : 1) >= 524288.0 ? 256 : 64;
+        set_tile(g, both ? 4096 : 8192, false, t);
+        t.sites_per_block = sites >= 524288.0 ? 256 : 64;
         return t;
     }
     if (prec == COLA_FP64 || prec == COLA_FP64_12) {
@@ -116,8 +127,11 @@ inline TuneEntry plain_entry(const Geom &g, int prec, int nrhs, bool both, bool 
         // 12x6, 2.82 with 8x8; 32^3 x 64 9.2 ms with 8x4 and 8x8; clover S 48^3 x 96 29.4
         // ms with 8x4, 28.7 with 6x6; with 2 to 8 rhs 12x6 or 12x12 are the fastest on 24^3
         // x 48.  M^dag M (both): 24^3 x 48 2.86 ms with 8x8, 2.73 with 6x4; 32^3 x 64 9.74
-        // ms with 8x8, 8.95 with 4x4; up to 8 rhs 12x6 as for one parity.
-        best_tile(g, both && nrhs > 8 ? 288 : 900, &t.tile_y, &t.tile_z);
+        // ms with 8x8, 8.95 with 4x4; up to 8 rhs 12x6 as for one parity.  Two rhs, and three
+        // with one parity, up to 2048 sites: 32^3 x 64 2 rhs D_eo D_oe 1076 us untiled, 1275 with
+        // 8x4, 948 with 16x8; 48 x 24 x 24 x 32 430 with 6x6, 415 with 12x6; 3 rhs 569 and 547.
+        const bool wide = nrhs == 2 || (nrhs == 3 && !both);
+        set_tile(g, wide ? 2048 : both && nrhs > 8 ? 288 : 900, true, t);
         return t;
     }
     // FP32 and FP16: the site's links staged in LDS.  Four rhs without a clover block, in
@@ -130,12 +144,12 @@ inline TuneEntry plain_entry(const Geom &g, int prec, int nrhs, bool both, bool 
     if (nrhs == 4 && !clover) {
         TuneEntry s = t;
         s.sites_per_block = kStageSites;
-        const double blocks = (double)g.Vh * (both ? 2 : 1) / kStageSites;
+        const double blocks = sites / kStageSites;
         if (blocks / 2 >= 1024.0 && stage_ok(g, prec, nrhs, s)) {
             s.stage = 1;
             s.tchunk = blocks / 4 >= (both ? 1 : 4) * 1024.0 ? 4 : 2;
             while (g.L[3] % s.tchunk) s.tchunk /= 2;
-            best_tile(g, 2048, &s.tile_y, &s.tile_z);
+            set_tile(g, 2048, true, s);
             return s;
         }
     }
@@ -150,8 +164,9 @@ inline TuneEntry plain_entry(const Geom &g, int prec, int nrhs, bool both, bool 
         // with 16x8 in 4; clover S 48^3 x 96 11.24 and 11.09 with 12x6 in 8; FP16 24^3 x 48
         // 790 and 712 us.  5 to 8 rhs on 24^3 x 48 (2 to 3 rounds): 0 to 7% faster without
         // the walk.  Both parities (M^dag M): FP32 24^3 x 48 1.21 ms with 12x6.
-        best_tile(g, both ? 1024 : 2048, &t.tile_y, &t.tile_z);
-        const double blocks = (double)g.Vh * (both ? 2 : 1) / T;
+        set_tile(g, both ? 1024 : 2048, true, t);
+        fill_chip(t, sites, nrhs);
+        const double blocks = sites / t.sites_per_block;
         t.tchunk = blocks / 8 >= 12 * 1024.0 ? 8 : blocks / 4 >= 4 * 1024.0 ? 4 : 1;
         while (g.L[3] % t.tchunk) t.tchunk /= 2;
         return t;
@@ -159,7 +174,8 @@ inline TuneEntry plain_entry(const Geom &g, int prec, int nrhs, bool both, bool 
     // two to four rhs per site (M, 24^3 x 48 FP16: 92 us untiled in 256-lane blocks, 78
     // with 12x12 tiles of 64-site blocks)
     if (T > 64) t.sites_per_block = 64;
-    best_tile(g, 2048, &t.tile_y, &t.tile_z);
+    set_tile(g, 2048, true, t);
+    fill_chip(t, sites, nrhs);
     return t;
 }
 
@@ -170,13 +186,13 @@ inline TuneEntry plain_entry(const Geom &g, int prec, int nrhs, bool both, bool 
 //             1.02, 18^3 x 30 0.98, 20^3 x 32 0.97
 //             FP64 s 24^3 x 32 1.12 (12: 1.18), 24^3 x 48 0.92 (1.03), 28^3 x 48 0.95 (0.98); m
 //             28^3 x 48 1.11 (1.09), 32^3 x 64 0.83 (0.85); s c 20^3 x 32 1.04 (1.02), 24^3 x 32
-//             0.98 (1.05); m c 16^3 x 32 1.19 (1.11), 20^3 x 24 1.05 (0.95), 20^3 x 32 1.07 (0.95),
-//             24^3 x 32 0.98 (0.95)
+//             0.98 (1.05); m c 16^3 x 32 1.19 (1.11), 20 x 18 x 14 x 30 (1.10), 20^3 x 24 1.05
+//             (0.95), 20^3 x 32 1.07 (0.95), 24^3 x 32 0.98 (0.95)
 //   more      (2 to 16 rhs, 4 thousand to 131 thousand lanes) FP32 at least 0.98 up to 65536;
 //             m c 1.05 up to 41 thousand, then 0.83 to 0.94 from six rhs on
-//             FP64 at least 0.97; m c 0.95 up to 41 thousand, 0.91 to 0.94 with 11 and 12 rhs
-//             at 45 and 49, 0.85 to 1.09 from 76 on; s c at least 1.01, but with three and four
-//             rhs 0.91 from 98 on
+//             FP64 at least 0.97; m c 0.95 up to 41 thousand, then 0.91 to 0.94 with 11 and 12
+//             rhs, 0.85 to 0.98 from 76 on, but with 7 and 8 rhs 1.03 to 1.09 up to 110 and with
+//             16 1.08 at 110; s c at least 1.01, but with three and four rhs 0.91 from 98 on
 inline bool few_lanes(const Geom &g, int prec, int nrhs, bool both, bool clover) {
     const double lanes = (double)g.Vh * nrhs;
     if (prec == COLA_FP32) {
@@ -184,8 +200,8 @@ inline bool few_lanes(const Geom &g, int prec, int nrhs, bool both, bool clover)
         return lanes <= (clover && both && nrhs > 5 ? 43008 : 65536);
     }
     if (!clover) return lanes <= (nrhs > 1 ? 131072 : both ? 600000 : 262144);
-    if (nrhs == 1) return lanes <= (both && prec == COLA_FP64_12 ? 65536 : 131072);
-    if (both) return lanes <= (nrhs > 8 ? 43008 : 73728);
+    if (nrhs == 1) return lanes <= (both && prec == COLA_FP64_12 ? 81920 : 131072);
+    if (both && nrhs < 16) return lanes <= (nrhs > 8 ? 43008 : nrhs > 6 ? 114688 : 73728);
     return lanes <= (nrhs == 3 || nrhs == 4 ? 90112 : 131072);
 }
 
@@ -226,7 +242,7 @@ inline TuneEntry flic_entry(const Geom &g, int prec, int nrhs, bool both) {
     if (nrhs == 1) {
         if (f64 && t.sites_per_block == 256) {
             t.sites_per_block = 128;
-            best_tile(g, both ? 2048 : 4096, &t.tile_y, &t.tile_z);
+            set_tile(g, both ? 2048 : 4096, false, t);
         }
         return t;
     }
@@ -234,12 +250,12 @@ inline TuneEntry flic_entry(const Geom &g, int prec, int nrhs, bool both) {
     while (T * nrhs > 64) T /= 2;
     const bool fills = T * nrhs == 64;
     if (f64 && nrhs == 3) {
-        if (!both) best_tile(g, 2048, &t.tile_y, &t.tile_z);
+        if (!both) set_tile(g, 2048, true, t);
         chunk(1);
     } else if (fills || f64) {
         if (fills || !both) t.sites_per_block = T;
         const int most = !both || nrhs == 2 ? 1024 : nrhs > 8 ? 256 : f64 ? 512 : 1024;
-        best_tile(g, most, &t.tile_y, &t.tile_z);
+        set_tile(g, most, true, t);
         t.tchunk = 1;
         if (f64 && nrhs >= 5) chunk(4);
     }

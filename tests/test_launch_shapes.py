@@ -168,6 +168,8 @@ FASTER = [c[:4] + (1, c[4]) for c in FASTER] + [
     ((8, 8, 8, 16), FP64, 1, 1, 12, "sites"), ((12, 12, 12, 12), FP64, 1, 1, 5, "directions"),
     ((16, 16, 16, 16), FP64, 1, 1, 3, "sites"), ((16, 16, 16, 16), FP64_12, 0, 1, 3, "sites"),
     ((12, 12, 12, 24), FP64, 0, 1, 5, "directions"), ((12, 12, 12, 12), FP64, 1, 0, 12, "directions"),
+    ((12, 12, 12, 16), FP64, 1, 1, 7, "directions"), ((12, 12, 12, 8), FP64, 1, 1, 16, "directions"),
+    ((20, 18, 14, 30), FP64_12, 1, 1, 1, "directions"),
 ]
 
 
@@ -219,3 +221,17 @@ def test_flic_blocks(probe):
         if nrhs in (2, 4, 8, 16):
             assert T * nrhs == 64, (d, prec, nrhs, both)
         assert T * nrhs <= 64 or sites / tchunk / T >= 200 or T * nrhs < 128, (d, prec, nrhs, both)
+
+
+def test_tiles_cut_the_timeslice_only_where_it_is_large(probe):
+    """A tile is never the whole timeslice (the plain order is the same and cheaper), and with
+    several rhs a timeslice of up to 1.25 times the tile size stays whole: 20 x 18 x 14 has
+    2520 sites of a parity."""
+    for d, prec, nrhs, both in KINDS:
+        for fn, more in ((probe.probe_plain, (0,)), (probe.probe_flic, ())):
+            s = _shape(fn, _dims(d), prec, nrhs, both, *more)
+            assert (s[4], s[5]) != (d[1], d[2])
+    for prec, nrhs in ((FP32, 3), (FP32, 12), (FP16, 12), (FP64, 2), (FP64, 3)):
+        s = _shape(probe.probe_plain, _dims((20, 18, 14, 30)), prec, nrhs, 0, 0)
+        assert s[4:6] == (0, 0)
+    assert _shape(probe.probe_plain, _dims((24, 24, 24, 48)), FP32, 12, 0, 0)[4:6] == (12, 12)
