@@ -238,15 +238,16 @@ int cola_ape_smear(cola_handle_t *h, void *F, const void *U, double alpha, int n
         return COLA_OK;
     }
     // the sweeps run on packed copies, from one to the other (the two link fields that a
-    // trajectory steps between: never live together)
-    void *w[2];
+    // trajectory steps between: never live together), the last one into F
+    void *w[2] = {};
     const size_t pb = (size_t)8 * 9 * 16 * h->g.S;
     COLA_TRY(get_vec(h, "links_w0", pb, &w[0]));
-    COLA_TRY(get_vec(h, "links_w1", pb, &w[1]));
+    if (nsweeps > 1) COLA_TRY(get_vec(h, "links_w1", pb, &w[1]));
     COLA_HIP(h, launch_md_pack(h->g, U, nullptr, w[0], nullptr, st));
-    for (int k = 0; k < nsweeps; ++k)
-        COLA_HIP(h, launch_ape_sweep(h->g, w[k & 1], w[(k + 1) & 1], alpha, st));
-    COLA_HIP(h, launch_md_unpack(h->g, F, nullptr, w[nsweeps & 1], nullptr, st));
+    for (int k = 0; k < nsweeps; ++k) {
+        const bool last = k == nsweeps - 1;
+        COLA_HIP(h, launch_ape_sweep(h->g, w[k & 1], last ? F : w[(k + 1) & 1], last, alpha, st));
+    }
     return COLA_OK;
 }
 

@@ -195,8 +195,8 @@ hipError_t launch_fermion_kick(const Geom &g, const void *U, const void *X, cons
                                double kappa, const Cplx64 phase[4], double eps, hipStream_t st);
 
 // one APE smearing sweep Out = P_SU3[(1 - alpha) U + alpha/6 staples] of packed 18-real
-// links (Out != U)
-hipError_t launch_ape_sweep(const Geom &g, const void *U, void *Out, double alpha,
+// links (Out != U); Out is packed, or canonical
+hipError_t launch_ape_sweep(const Geom &g, const void *U, void *Out, bool canonical, double alpha,
                             hipStream_t st);
 // *result (device) = sum over sites and mu < nu of Re Tr U_plaq
 hipError_t launch_plaquette_sum(const Geom &g, const void *U, double *partial, double *result,

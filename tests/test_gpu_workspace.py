@@ -41,3 +41,16 @@ def test_smearing_and_trajectory_share_link_fields():
     assert torch.equal(again, want.ape_smear(F, 0.7, 1))
     want.close()
     lat.close()
+
+
+@pytest.mark.parametrize("nsweeps", [1, 2, 3])
+def test_smearing_in_place(nsweeps):
+    """F may be U: the links are copied before the last sweep writes its result; same bits."""
+    dims = (6, 10, 4, 6)
+    lat = cola.Lattice(dims, 0.12, bc_phases((0, 0, 0, np.pi)))
+    U = Synth(94).gauge(dims, mix=0.5).cuda()
+    want = lat.ape_smear(U, 0.7, nsweeps)
+    cola.cola_ape_smear(lat.h, U.data_ptr(), U.data_ptr(), 0.7, nsweeps,
+                        torch.cuda.current_stream().cuda_stream)
+    assert torch.equal(U, want)
+    lat.close()
